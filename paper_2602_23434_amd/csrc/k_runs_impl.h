@@ -36,6 +36,10 @@ namespace pl {
 // two-cell field halo only particles two cells out of their tile land there.
 __host__ __device__ constexpr int gq_cap(int hf) { return hf == 2 ? 64 : 256; }
 
+// Type of a batch's deposit sums.
+template <int PREC, bool DACC> struct AccOf { using T = typename RealOf<PREC>::T; };
+template <int PREC> struct AccOf<PREC, true> { using T = double; };
+
 template <int PREC> struct RunsQ { static constexpr int DQ = PREC == PL_F32_OFFSET ? 256 : 128; };
 
 // LDS field records, read with 16-byte loads.  Lanes of a wave read
@@ -212,10 +216,12 @@ template <int PREC> struct RunShared {
     double *lds_d;
     int *gq;
     uint32_t *dq_c;
-    R *dq_d;      // 3 x DQ
-    R *dq_mu;     // nslot x DQ
+    R *dq_d;      // 3 x dq
+    R *dq_mu;     // nslot x dq
     int *ctl;     // [0] claimed unit, [1] queued particles, [2] queued deposits
-    double *sums; // 8 particle-side sums of the unit
+    int dq;       // capacity of the deposit queue
+    double *sums; // 8 particle-side sums of the unit, smask + 1 partial sums each
+    int smask;
 };
 
 // Particle-side conservation sums (only with SF_SUMS): LDS accumulation per
@@ -225,7 +231,8 @@ __device__ __forceinline__ void add_sums(const RunShared<PREC> &S, const typenam
 {
 #pragma unroll
     for (int k = 0; k < 8; ++k)
-        __hip_atomic_fetch_add(S.sums + k, (double)mu[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(S.sums + k * (S.smask + 1) + ((int)threadIdx.x & S.smask), (double)mu[k],
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Interpolate the fields of the LDS field tile to a particle whose stencil
@@ -328,7 +335,7 @@ template <int PREC, int SHAPE, int DIM, int CHS>
 __device__ __forceinline__ void record_deposit(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S, int i)
 {
     using R = typename RealOf<PREC>::T;
-    constexpr int DQ = RunsQ<PREC>::DQ;
+    const int DQ = S.dq;
     int c[3];
     unpack_cell(S.dq_c[i], c[0], c[1], c[2]);
     R d[3] = {S.dq_d[i], S.dq_d[DQ + i], S.dq_d[2 * DQ + i]};
@@ -342,21 +349,25 @@ __device__ __forceinline__ void record_deposit(const UnitC<PREC> &U, const RunGe
 }
 
 // Deposit of the batch particles in the reference cell (dco[j]): their values
-// are summed per stencil point and channel before each LDS atomic.
-template <int PREC, int SHAPE, int DIM, int CHS, int KR>
+// are summed per stencil point and channel before each LDS atomic, in the
+// particles' type, or in float64 (DACC: the precision of one float64 atomic
+// per particle, for the kernels that stand in for that).
+template <int PREC, int SHAPE, int DIM, int CHS, int KR, bool DACC>
 __device__ __forceinline__ void batch_deposit(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S, int db,
                                               const Pos<PREC, DIM> pos[KR], typename RealOf<PREC>::T mu[KR][kMaxCh],
                                               const bool dco[KR])
 {
     using R = typename RealOf<PREC>::T;
+    using A = typename AccOf<PREC, DACC>::T;
     constexpr int SY = Stencil<DIM>::SY, SZ = Stencil<DIM>::SZ;
     R wx[KR][3], wy[KR][3], wz[KR][3];
+    A mua[KR][kMaxCh];
 #pragma unroll
     for (int j = 0; j < KR; ++j) {
         R dn[3] = {(R)pos[j].d[0], (R)pos[j].d[1], (R)pos[j].d[2]};
         stencil_weights<PREC, SHAPE, DIM>(dn, wx[j], wy[j], wz[j]);
 #pragma unroll
-        for (int ch = 0; ch < kMaxCh; ++ch) mu[j][ch] = dco[j] ? mu[j][ch] : R(0);
+        for (int ch = 0; ch < kMaxCh; ++ch) mua[j][ch] = dco[j] ? (A)mu[j][ch] : A(0);
     }
 #pragma unroll
     for (int k = 0; k < SZ; ++k)
@@ -368,16 +379,16 @@ __device__ __forceinline__ void batch_deposit(const UnitC<PREC> &U, const RunGeo
             const int row = db + k * G.dxy + jj * G.dx;
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                R wt[KR];
+                A wt[KR];
 #pragma unroll
-                for (int j = 0; j < KR; ++j) wt[j] = wyz[j] * wx[j][i];
+                for (int j = 0; j < KR; ++j) wt[j] = (A)(wyz[j] * wx[j][i]);
 #pragma unroll
                 for (int ch = 0; ch < kMaxCh; ++ch) {
                     const int so = ch_off<CHS>(U, ch, G.Ld);
                     if (so < 0) continue;
-                    R s = wt[0] * mu[0][ch];
+                    A s = wt[0] * mua[0][ch];
 #pragma unroll
-                    for (int j = 1; j < KR; ++j) s = fma(wt[j], mu[j][ch], s);
+                    for (int j = 1; j < KR; ++j) s = fma(wt[j], mua[j][ch], s);
                     __hip_atomic_fetch_add(S.lds_d + so + row + i, (double)s, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
@@ -461,20 +472,21 @@ __device__ __forceinline__ void store_batch(const UnitC<PREC> &U, int start, con
 
 // Gather, push and deposit of the batch particles whose stencil lies in the
 // LDS field tile (co[j]); fb[j] is the field record of stencil point
-// (-1,-1,-1) of particle j.
-template <int PREC, int SHAPE, int DIM, int KIND, int CHS, int KR>
-__device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S, int start,
-                                           const int fb[KR], Pos<PREC, DIM> pos[KR], typename RealOf<PREC>::T u[KR][3],
+// (-1,-1,-1) of particle j, pi[j] its index (SEQ: pi[0] + j).
+template <int PREC, int SHAPE, int DIM, int KIND, int CHS, int KR, bool SEQ, bool DACC>
+__device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S,
+                                           const int pi[KR], const int fb[KR], Pos<PREC, DIM> pos[KR], typename RealOf<PREC>::T u[KR][3],
                                            const typename RealOf<PREC>::T w[KR], const bool co[KR], bool do_sums, int &err)
 {
     using R = typename RealOf<PREC>::T;
     constexpr int NC = FieldRec<PREC, KIND>::NC;
     constexpr int SY = Stencil<DIM>::SY, SZ = Stencil<DIM>::SZ;
-    constexpr int DQ = RunsQ<PREC>::DQ;
+    const int DQ = S.dq;
 
-    // a batch whose slots are all handled here is written back at the end with
-    // one access per array; otherwise every slot is stored on its own
-    bool whole = true;
+    // a batch of consecutive particles whose slots are all handled here is
+    // written back at the end with one access per array; otherwise every slot
+    // is stored on its own
+    bool whole = SEQ;
 #pragma unroll
     for (int j = 0; j < KR; ++j) whole = whole && co[j];
 
@@ -483,7 +495,7 @@ __device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G
     R mu[KR][kMaxCh];
 #pragma unroll
     for (int j = 0; j < KR; ++j) {
-        const int p = start + j;
+        const int p = SEQ ? pi[0] + j : pi[j];
         R wx[3], wy[3], wz[3];
         R d0[3] = {(R)pos[j].d[0], (R)pos[j].d[1], (R)pos[j].d[2]};
         stencil_weights<PREC, SHAPE, DIM>(d0, wx, wy, wz);
@@ -510,7 +522,7 @@ __device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G
             if (do_sums) add_sums(S, mu[j]);
         }
     }
-    if (whole) store_batch<PREC, DIM, KR>(U, start, pos, u, mu);
+    if (whole) store_batch<PREC, DIM, KR>(U, pi[0], pos, u, mu);
 
     // deposit: the batch particles in the reference cell are summed before
     // each LDS atomic; the others are queued.  The reference is the new cell
@@ -579,7 +591,7 @@ __device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G
             deposit_single<PREC, SHAPE, DIM, CHS>(U, G, S.lds_d, pos[j].c, dn, mud);
         }
     }
-    if (any_dco) batch_deposit<PREC, SHAPE, DIM, CHS, KR>(U, G, S, db, pos, mu, dco);
+    if (any_dco) batch_deposit<PREC, SHAPE, DIM, CHS, KR, DACC>(U, G, S, db, pos, mu, dco);
 }
 
 // Stored state of one batch (up to KR consecutive particles), fetched from
@@ -647,13 +659,13 @@ __device__ __forceinline__ void fetch_batch(const UnitC<PREC> &U, int start, int
     }
 }
 
-// One batch of up to KR particles of one run.
-template <int PREC, int SHAPE, int DIM, int KIND, int CHS, int KR>
+// One batch of up to KR particles of one run, of indices pi[j] (SEQ: pi[0] + j).
+template <int PREC, int SHAPE, int DIM, int KIND, int CHS, int KR, bool SEQ, bool DACC>
 __device__ __forceinline__ void run_batch(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S,
-                                          const BatchRaw<PREC, DIM, KR> &Bt, bool do_sums, int &err)
+                                          const BatchRaw<PREC, DIM, KR> &Bt, const int pi[KR], bool do_sums, int &err)
 {
     using R = typename RealOf<PREC>::T;
-    const int start = Bt.start, len = Bt.len;
+    const int len = Bt.len;
     Pos<PREC, DIM> pos[KR];
     R u[KR][3], w[KR];
 #pragma unroll
@@ -680,18 +692,24 @@ __device__ __forceinline__ void run_batch(const UnitC<PREC> &U, const RunGeo &G,
     for (int j = 0; j < KR; ++j) {
         if (j < len && !co[j]) {
             int q = atomicAdd(&S.ctl[1], 1);
-            if (q < gq_cap(G.hf)) S.gq[q] = start + j;
+            if (q < gq_cap(G.hf)) S.gq[q] = SEQ ? pi[0] + j : pi[j];
             else ovf_g |= 1u << j;
         }
     }
     bool any = false;
 #pragma unroll
     for (int j = 0; j < KR; ++j) any = any || co[j];
-    if (any) batch_body<PREC, SHAPE, DIM, KIND, CHS, KR>(U, G, S, start, fb, pos, u, w, co, do_sums, err);
+    if (any) batch_body<PREC, SHAPE, DIM, KIND, CHS, KR, SEQ, DACC>(U, G, S, pi, fb, pos, u, w, co, do_sums, err);
     while (ovf_g) {
         const int j = __builtin_ctz(ovf_g);
         ovf_g &= ovf_g - 1u;
-        particle_single<PREC, SHAPE, DIM, KIND, CHS>(U, G, S, start + j, do_sums, err);
+        int p = pi[0] + j;
+        if constexpr (!SEQ) {
+#pragma unroll
+            for (int k = 1; k < KR; ++k)
+                if (k == j) p = pi[k];
+        }
+        particle_single<PREC, SHAPE, DIM, KIND, CHS>(U, G, S, p, do_sums, err);
     }
 }
 
@@ -779,6 +797,101 @@ __device__ __forceinline__ void tracer_particle(const UnitC<PREC> &U, const RunG
     for (int a = 0; a < 3; ++a) U.u[a][p] = v[a];
 }
 
+// Stage the field records of a tile (hf-cell halo) and clear its deposit tile
+// (ndep values).  Float32 form: two-deep pipeline, a record's loads are issued
+// before the previous record is stored, and the first loads overlap the
+// clearing.  The caller synchronises.
+template <int PREC, int DIM, int KIND>
+__device__ __forceinline__ void stage_unit(const UnitC<PREC> &U, const RunGeo &G, typename RealOf<PREC>::T *lds_f,
+                                           double *lds_d, int ndep)
+{
+    using R = typename RealOf<PREC>::T;
+    using FR = FieldRec<PREC, KIND>;
+    constexpr int NC = FR::NC, FS = FR::FS;
+    const int Ly = G.T[1] + 2 * G.hf;
+    auto rec_cell = [&](int e) -> long {
+        int lx = e % G.fx;
+        int ly = (e / G.fx) % Ly;
+        int lz = e / G.fxy;
+        int gx = wrap_any(G.lo[0] + lx - G.hf, U.n[0]);
+        int gy = DIM >= 2 ? wrap_any(G.lo[1] + ly - G.hf, U.n[1]) : 0;
+        int gz = DIM >= 3 ? wrap_any(G.lo[2] + lz - G.hf, U.n[2]) : 0;
+        return gx + (long)U.n[0] * (gy + (long)U.n[1] * gz);
+    };
+    auto rec_load = [&](int e, double (&v)[NC]) {
+        const long gc = rec_cell(e);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) v[q] = U.gf[q][gc];
+    };
+    // one 16-byte LDS store per 16 bytes of record (conflict-free:
+    // consecutive threads write consecutive records)
+    auto rec_store = [&](int e, const double (&v)[NC]) {
+        if constexpr (FR::PLANES) {
+            *reinterpret_cast<float4 *>(lds_f + FR::at(e, 0, G.Lf)) =
+                make_float4((R)v[0], (R)v[1], (R)v[2], 0.0f);
+            *reinterpret_cast<float4 *>(lds_f + FR::at(e, 3, G.Lf)) =
+                make_float4((R)v[3], (R)v[4], (R)v[5], 0.0f);
+        } else {
+            R w[FS];
+#pragma unroll
+            for (int q = 0; q < FS; ++q) w[q] = q < NC ? (R)v[q] : R(0);
+            if constexpr (PREC == PL_F32_OFFSET) {
+                *reinterpret_cast<float4 *>(lds_f + FS * e) = make_float4(w[0], w[1], w[2], w[3]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < FS / 2; ++k)
+                    *reinterpret_cast<double2 *>(lds_f + FS * e + 2 * k) = make_double2(w[2 * k], w[2 * k + 1]);
+            }
+        }
+    };
+    if constexpr (PREC == PL_F32_OFFSET) {
+        double cur[NC];
+        int e = threadIdx.x;
+        if (e < G.Lf) rec_load(e, cur);
+        for (int k = threadIdx.x; k < ndep; k += blockDim.x) lds_d[k] = 0.0;
+        for (; e < G.Lf; e += blockDim.x) {
+            double nxt[NC];
+            const int en = e + (int)blockDim.x;
+            if (en < G.Lf) rec_load(en, nxt);
+            rec_store(e, cur);
+#pragma unroll
+            for (int q = 0; q < NC; ++q) cur[q] = nxt[q];
+        }
+    } else {
+        // float64 records: one at a time (the pipeline's registers spill there)
+        for (int e = threadIdx.x; e < G.Lf; e += blockDim.x) {
+            double v[NC];
+            rec_load(e, v);
+            rec_store(e, v);
+        }
+        for (int k = threadIdx.x; k < ndep; k += blockDim.x) lds_d[k] = 0.0;
+    }
+}
+
+// Flush of a deposit tile: one float64 global atomic per touched cell and
+// channel.
+template <int PREC, int DIM, int CHS>
+__device__ __forceinline__ void flush_unit(const UnitC<PREC> &U, const RunGeo &G, const double *lds_d)
+{
+    const int Ly = G.T[1] + 4;
+    for (int e = threadIdx.x; e < G.Ld; e += blockDim.x) {
+        int lx = e % G.dx;
+        int ly = (e / G.dx) % Ly;
+        int lz = e / G.dxy;
+        int gx = wrap_any(G.lo[0] + lx - 2, U.n[0]);
+        int gy = DIM >= 2 ? wrap_any(G.lo[1] + ly - 2, U.n[1]) : 0;
+        int gz = DIM >= 3 ? wrap_any(G.lo[2] + lz - 2, U.n[2]) : 0;
+        long gc = gx + (long)U.n[0] * (gy + (long)U.n[1] * gz);
+#pragma unroll
+        for (int ch = 0; ch < kMaxCh; ++ch) {
+            const int so = ch_off<CHS>(U, ch, G.Ld);
+            if (so < 0) continue;
+            double val = lds_d[so + e];
+            if (val != 0.0) global_add(U.M[ch] + gc, val * U.inv_dv);
+        }
+    }
+}
+
 // One work unit of the run kernel (a piece of tile t of item I): stage the
 // tile's field records (and clear its deposit tile), advance the piece's
 // runs, and flush the deposits; passive tracers are advanced one particle at
@@ -834,72 +947,13 @@ __device__ __forceinline__ void runs_unit(const ItemDesc &I, int t, int piece, i
     S.dq_c = reinterpret_cast<uint32_t *>(smem_raw + offs[3]);
     S.dq_d = reinterpret_cast<R *>(smem_raw + offs[4]);
     S.dq_mu = S.dq_d + 3 * RunsQ<PREC>::DQ;
+    S.dq = RunsQ<PREC>::DQ;
     S.ctl = ctl;
     S.sums = reinterpret_cast<double *>(smem_raw + offs[5]);
+    S.smask = 0;
 
-    // stage the field records (hf-cell halo) and clear the deposit tile.
-    // Float32 form: two-deep pipeline, a record's loads are issued before
-    // the previous record is stored, and the first loads overlap the
-    // clearing.
+    stage_unit<PREC, DIM, KIND>(U, G, lds_f, S.lds_d, G.Ld * nslot);
     {
-        const int Ly = G.T[1] + 2 * G.hf;
-        auto rec_cell = [&](int e) -> long {
-            int lx = e % G.fx;
-            int ly = (e / G.fx) % Ly;
-            int lz = e / G.fxy;
-            int gx = wrap_any(G.lo[0] + lx - G.hf, U.n[0]);
-            int gy = DIM >= 2 ? wrap_any(G.lo[1] + ly - G.hf, U.n[1]) : 0;
-            int gz = DIM >= 3 ? wrap_any(G.lo[2] + lz - G.hf, U.n[2]) : 0;
-            return gx + (long)U.n[0] * (gy + (long)U.n[1] * gz);
-        };
-        auto rec_load = [&](int e, double (&v)[NC]) {
-            const long gc = rec_cell(e);
-#pragma unroll
-            for (int q = 0; q < NC; ++q) v[q] = U.gf[q][gc];
-        };
-        // one 16-byte LDS store per 16 bytes of record (conflict-free:
-        // consecutive threads write consecutive records)
-        auto rec_store = [&](int e, const double (&v)[NC]) {
-            if constexpr (FR::PLANES) {
-                *reinterpret_cast<float4 *>(lds_f + FR::at(e, 0, G.Lf)) =
-                    make_float4((R)v[0], (R)v[1], (R)v[2], 0.0f);
-                *reinterpret_cast<float4 *>(lds_f + FR::at(e, 3, G.Lf)) =
-                    make_float4((R)v[3], (R)v[4], (R)v[5], 0.0f);
-            } else {
-                R w[FS];
-#pragma unroll
-                for (int q = 0; q < FS; ++q) w[q] = q < NC ? (R)v[q] : R(0);
-                if constexpr (PREC == PL_F32_OFFSET) {
-                    *reinterpret_cast<float4 *>(lds_f + FS * e) = make_float4(w[0], w[1], w[2], w[3]);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < FS / 2; ++k)
-                        *reinterpret_cast<double2 *>(lds_f + FS * e + 2 * k) = make_double2(w[2 * k], w[2 * k + 1]);
-                }
-            }
-        };
-        if constexpr (PREC == PL_F32_OFFSET) {
-            double cur[NC];
-            int e = threadIdx.x;
-            if (e < G.Lf) rec_load(e, cur);
-            for (int k = threadIdx.x; k < G.Ld * nslot; k += blockDim.x) S.lds_d[k] = 0.0;
-            for (; e < G.Lf; e += blockDim.x) {
-                double nxt[NC];
-                const int en = e + (int)blockDim.x;
-                if (en < G.Lf) rec_load(en, nxt);
-                rec_store(e, cur);
-#pragma unroll
-                for (int q = 0; q < NC; ++q) cur[q] = nxt[q];
-            }
-        } else {
-            // float64 records: one at a time (the pipeline's registers spill there)
-            for (int e = threadIdx.x; e < G.Lf; e += blockDim.x) {
-                double v[NC];
-                rec_load(e, v);
-                rec_store(e, v);
-            }
-            for (int k = threadIdx.x; k < G.Ld * nslot; k += blockDim.x) S.lds_d[k] = 0.0;
-        }
         if (threadIdx.x == 0) {
             ctl[1] = 0;
             ctl[2] = 0;
@@ -950,7 +1004,8 @@ __device__ __forceinline__ void runs_unit(const ItemDesc &I, int t, int piece, i
                 const bool nhave = nr < s1;
                 BatchRaw<PREC, DIM, KR> nxt;
                 if (nhave) fetch_batch<PREC, DIM, KR>(U, nrs + nb, min(KR, nrl - nb), nxt);
-                run_batch<PREC, SHAPE, DIM, KIND, CHS, KR>(U, G, S, cur, do_sums, err);
+                const int pi[KR] = {cur.start};
+                run_batch<PREC, SHAPE, DIM, KIND, CHS, KR, true, false>(U, G, S, cur, pi, do_sums, err);
                 cur = nxt;
                 r = nr;
                 b = nb;
@@ -983,25 +1038,7 @@ __device__ __forceinline__ void runs_unit(const ItemDesc &I, int t, int piece, i
         if (threadIdx.x == 0) ctl[0] = (int)atomicAdd(counter + (blockIdx.x + ctl[3]) % kQueues, 1u);
         pre = true;
         if (do_sums && threadIdx.x < 8 && S.sums[threadIdx.x] != 0.0) global_add(I.psum + threadIdx.x, S.sums[threadIdx.x]);
-        {
-            const int Ly = G.T[1] + 4;
-            for (int e = threadIdx.x; e < G.Ld; e += blockDim.x) {
-                int lx = e % G.dx;
-                int ly = (e / G.dx) % Ly;
-                int lz = e / G.dxy;
-                int gx = wrap_any(G.lo[0] + lx - 2, U.n[0]);
-                int gy = DIM >= 2 ? wrap_any(G.lo[1] + ly - 2, U.n[1]) : 0;
-                int gz = DIM >= 3 ? wrap_any(G.lo[2] + lz - 2, U.n[2]) : 0;
-                long gc = gx + (long)U.n[0] * (gy + (long)U.n[1] * gz);
-#pragma unroll
-                for (int ch = 0; ch < kMaxCh; ++ch) {
-                    const int so = ch_off<CHS>(U, ch, G.Ld);
-                    if (so < 0) continue;
-                    double val = S.lds_d[so + e];
-                    if (val != 0.0) global_add(U.M[ch] + gc, val * U.inv_dv);
-                }
-            }
-        }
+        flush_unit<PREC, DIM, CHS>(U, G, S.lds_d);
     }
 }
 

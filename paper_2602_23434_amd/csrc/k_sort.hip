@@ -49,7 +49,7 @@ __device__ __forceinline__ void count_runs(const uint32_t *keys, int e0, int end
 __global__ void k_keys(SortArgs a, uint32_t *keys)
 {
     const int tx = a.tile[0], ty = a.tile[1], tz = a.tile[2];
-    const int ntx = a.n[0] / tx, nty = a.n[1] / ty;
+    const int ntx = (a.n[0] + tx - 1) / tx, nty = (a.n[1] + ty - 1) / ty;     // (the plain algorithm's may not divide)
     const int per_tile = tx * ty * tz;
     const bool p2 = ((tx & (tx - 1)) | (ty & (ty - 1)) | (tz & (tz - 1))) == 0;
     for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < a.np; p += gridDim.x * blockDim.x) {
@@ -714,6 +714,36 @@ static int radix_passes(Ctx *c, int np, int src, bool identity, int bits)
         src = 1 - src;
     }
     return src;
+}
+
+int bins_buffer(int ntiles)
+{
+    const int bits = std::max(bits_for((uint64_t)ntiles), 1);
+    return ((bits + kMaxDigitBits - 1) / kMaxDigitBits) & 1;
+}
+
+hipError_t launch_bins(Ctx *c, const ItemDesc &it)
+{
+    SortArgs a;
+    memset(&a, 0, sizeof(a));
+    a.prec = c->d.prec;
+    a.ndim = c->d.ndim;
+    a.key_mode = PL_KEY_TILE;
+    for (int k = 0; k < 3; ++k) {
+        a.n[k] = it.n[k];
+        a.tile[k] = it.tile[k];
+        a.x[k] = a.prec == PL_F64 && k < a.ndim ? (const double *)it.x[k] : nullptr;
+    }
+    a.np = it.np;
+    a.ntiles = it.ntiles;
+    a.cell = it.cell;
+    const int grid_e = std::min((a.np + 255) / 256, 16 * c->num_cu);
+    hipLaunchKernelGGL(k_keys, dim3(grid_e), dim3(256), 0, c->stream, a, c->keys[0]);
+    const int src = radix_passes(c, a.np, 0, true, bits_for((uint64_t)a.ntiles));
+    hipLaunchKernelGGL(k_tile_start, dim3(grid_e), dim3(256), 0, c->stream, c->keys[src], a.np, 0, 1, a.ntiles,
+                       it.tile_start);
+    c->stats[0] += 2;
+    return hipGetLastError();
 }
 
 hipError_t launch_sort(Ctx *c, const SortArgs &a)

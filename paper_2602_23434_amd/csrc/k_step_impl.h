@@ -128,10 +128,11 @@ __device__ __forceinline__ void load_unit(const ItemDesc &I, UnitC<PREC> &U, int
 
 // Compile-time channel -> LDS slot maps for the common channel sets (CHS):
 // 0 runtime (UnitC::soff), 1 charged rho, J, F (slots 0..6), 2 dust rho, F
-// (slots 0..3).
+// (slots 0..3), 3 every channel of charged particles (slots 0..7).
 __host__ __device__ constexpr int chs_slot(int CHS, int ch)
 {
-    return CHS == 1 ? (ch < 7 ? ch : -1) : CHS == 2 ? (ch == 0 ? 0 : (ch >= 4 && ch <= 6 ? ch - 3 : -1)) : -1;
+    return CHS == 1 ? (ch < 7 ? ch : -1)
+                    : CHS == 2 ? (ch == 0 ? 0 : (ch >= 4 && ch <= 6 ? ch - 3 : -1)) : CHS == 3 ? ch : -1;
 }
 
 // Compile-time tile shapes (TS): 0 runtime, 1 = 8x8x8, 2 = 8x8x4.

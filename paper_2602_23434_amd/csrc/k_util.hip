@@ -17,14 +17,79 @@ hipError_t launch_runs_f32(Ctx *c, const ItemDesc *table, const ItemDesc *host, 
                            unsigned sf, unsigned *counter);
 hipError_t launch_runs_f64(Ctx *c, const ItemDesc *table, const ItemDesc *host, int nitems, int total_units,
                            unsigned sf, unsigned *counter);
+hipError_t launch_local_f32(Ctx *c, const ItemDesc *table, const ItemDesc *host, int nitems, const LocalPlan &pl,
+                            unsigned sf, unsigned *counter);
+hipError_t launch_local_f64(Ctx *c, const ItemDesc *table, const ItemDesc *host, int nitems, const LocalPlan &pl,
+                            unsigned sf, unsigned *counter);
+
+// Plain algorithm: particles from which binning an item's indices costs less
+// than it saves (with a deposit, without one), and per tile of the bins.
+constexpr int kBinMinDeposit = 8192;
+constexpr int kBinMinPush = 65536;
+constexpr int kBinMinPerTile = 64;
+
+// Items of one launch: those of one species kind; an item whose indices the
+// call bins (plain algorithm) has one of its own.
+int group_end(const std::vector<ItemDesc> &host, int i0)
+{
+    int i1 = i0 + 1;
+    if (host[i0].idx) return i1;
+    while (i1 < (int)host.size() && host[i1].kind == host[i0].kind && !host[i1].idx) ++i1;
+    return i1;
+}
+
+// Fused run-based steps of charged and dust species take the run-based kernel
+// (its tables come from the sort).  Everything else that has tiles takes a
+// self-grouping kernel where the tile and its LDS allow it: it needs only the
+// tile offsets, and a quarter to a half of the LDS atomics of the
+// one-particle-per-thread kernel.
+Route group_route(const Ctx *c, const ItemDesc *host, int nitems, bool push, bool deposit, LocalPlan &pl)
+{
+    RunsPlan rp;
+    if (c->d.algo == PL_ALGO_RUNS && push && deposit && host[0].kind != PL_TRACER && runs_plan(c, host, nitems, rp))
+        return ROUTE_RUNS;
+    if ((c->d.algo != PL_ALGO_PLAIN || host[0].idx) && local_plan(c, host, nitems, push, deposit, pl))
+        return ROUTE_LOCAL;
+    return ROUTE_STEP;
+}
+
+// Tiles of a binned item: 8^3 cells (float32) or 8 x 8 x 4 (float64), 32 x 32
+// or 32 x 16 in 2D, the largest whose LDS leaves chunks of a tile's particles;
+// they need not divide the box (a tile past its edge wraps).
+bool plain_bins(const Ctx *c, ItemDesc &it, bool push, bool deposit)
+{
+    if (c->d.algo != PL_ALGO_PLAIN) return false;
+    const bool dep = deposit && it.kind != PL_TRACER && it.nslot > 0;
+    if (!push && !dep) return false;
+    if (it.np < (dep ? kBinMinDeposit : kBinMinPush)) return false;
+    ItemDesc d = it;
+    const bool f64 = c->d.prec == PL_F64;
+    d.tile[0] = c->d.ndim == 3 ? 8 : 32;
+    d.tile[1] = c->d.ndim == 3 ? 8 : (f64 ? 16 : 32);
+    d.tile[2] = c->d.ndim == 3 ? (f64 || it.nslot > 7 ? 4 : 8) : 1;
+    int64_t nt = 1;
+    for (int a = 0; a < 3; ++a) {
+        d.ntile[a] = (d.n[a] + d.tile[a] - 1) / d.tile[a];
+        nt *= d.ntile[a];
+    }
+    if (nt > c->bin_cap || it.np / kBinMinPerTile < nt) return false;
+    d.ntiles = (int)nt;
+    d.tile_start = c->bin_start;
+    d.idx = c->idx[bins_buffer(d.ntiles)];
+    LocalPlan pl;
+    if (!local_plan(c, &d, 1, push, deposit, pl)) return false;
+    it = d;
+    return true;
+}
 
 // The host table is ordered by species kind, then by particle count.  A fused
-// run-based step is one launch over every item; otherwise every run of one
-// kind is one launch with its own work counter.
+// run-based step is one launch over every item; otherwise every group of items
+// (group_end) is one launch with a work counter of its kind.
 hipError_t launch_step(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc> &host, int nitems,
                        int total_units, unsigned flags, bool deposit, bool push)
 {
     (void)total_units;
+    const bool f64 = c->d.prec == PL_F64;
     unsigned sf = (push ? SF_PUSH : 0u) | (deposit ? SF_DEPOSIT : 0u) | ((flags & PL_SUMS) ? SF_SUMS : 0u) |
                   (c->runs ? SF_RUNS : 0u);
     // a fused run-based step with every kind in one launch (the item table
@@ -33,34 +98,32 @@ hipError_t launch_step(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc
     if (c->one_launch && c->d.algo == PL_ALGO_RUNS && push && deposit && runs_plan(c, host.data(), nitems, pl)) {
         int units = 0;
         for (int i = 0; i < nitems; ++i) units += host[i].nunits;
-        return c->d.prec == PL_F64 ? launch_runs_f64(c, table, host.data(), nitems, units, sf, c->counters)
-                                   : launch_runs_f32(c, table, host.data(), nitems, units, sf, c->counters);
+        return f64 ? launch_runs_f64(c, table, host.data(), nitems, units, sf, c->counters)
+                   : launch_runs_f32(c, table, host.data(), nitems, units, sf, c->counters);
     }
-    int i0 = 0, group = 0;
-    while (i0 < nitems) {
-        int i1 = i0;
+    for (int i0 = 0, i1 = 0; i0 < nitems; i0 = i1) {
+        i1 = group_end(host, i0);
+        const ItemDesc *h = host.data() + i0, *t = table + i0;
+        const int n = i1 - i0;
+        unsigned *counter = c->counters + kCounterStride * h->kind;
         int units = 0;
-        while (i1 < nitems && host[i1].kind == host[i0].kind) units += host[i1++].nunits;
-        // the run-based kernel takes fused steps of charged and dust species;
-        // everything else (and a tile too large for its LDS) takes the tiled one
-        hipError_t e = hipErrorInvalidConfiguration;
-        if (c->d.algo == PL_ALGO_RUNS && push && deposit && host[i0].kind != PL_TRACER)
-            e = c->d.prec == PL_F64 ? launch_runs_f64(c, table + i0, host.data() + i0, i1 - i0, units, sf,
-                                                      c->counters + kCounterStride * group)
-                                    : launch_runs_f32(c, table + i0, host.data() + i0, i1 - i0, units, sf,
-                                                      c->counters + kCounterStride * group);
-        if (e == hipErrorInvalidConfiguration && c->d.algo == PL_ALGO_RUNS && push && deposit &&
-            host[i0].kind != PL_TRACER)
-            c->stats[5]++;
-        if (e == hipErrorInvalidConfiguration)
-            e = c->d.prec == PL_F64
-                    ? launch_group_f64(c, table + i0, host.data() + i0, i1 - i0, units, sf, push, deposit,
-                                       c->counters + kCounterStride * group)
-                    : launch_group_f32(c, table + i0, host.data() + i0, i1 - i0, units, sf, push, deposit,
-                                       c->counters + kCounterStride * group);
+        for (int i = 0; i < n; ++i) units += h[i].nunits;
+        LocalPlan lp;
+        const Route r = group_route(c, h, n, push, deposit, lp);
+        hipError_t e = hipSuccess;
+        if (h->idx) e = launch_bins(c, *h);
         if (e != hipSuccess) return e;
-        i0 = i1;
-        ++group;
+        if (r == ROUTE_RUNS) {
+            e = f64 ? launch_runs_f64(c, t, h, n, units, sf, counter) : launch_runs_f32(c, t, h, n, units, sf, counter);
+        } else {
+            if (c->d.algo == PL_ALGO_RUNS && push && deposit && h->kind != PL_TRACER) c->stats[5]++;
+            if (r == ROUTE_LOCAL)
+                e = f64 ? launch_local_f64(c, t, h, n, lp, sf, counter) : launch_local_f32(c, t, h, n, lp, sf, counter);
+            else
+                e = f64 ? launch_group_f64(c, t, h, n, units, sf, push, deposit, counter)
+                        : launch_group_f32(c, t, h, n, units, sf, push, deposit, counter);
+        }
+        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }

@@ -129,6 +129,7 @@ void free_ctx(Ctx *c)
     (void)hipFree(c->hist);
     (void)hipFree(c->hist_scan);
     (void)hipFree(c->cell_start);
+    (void)hipFree(c->bin_start);
     for (int k = 0; k < Ctx::kRing; ++k)
         if (c->ring_ev[k]) (void)hipEventDestroy(c->ring_ev[k]);
     if (c->pinned) (void)hipHostFree(c->pinned);
@@ -295,17 +296,27 @@ pl_status build_table(Ctx *c, const pl_item *items, int nitems, double dt, Mode 
         RunsPlan pl;
         one_launch = runs_plan(c, all.data(), nitems, pl);
     }
-    int group_units = 0;
+    const bool push = mode == MODE_STEP;
     for (int k = 0; k < nitems; ++k) {
         ItemDesc D = descs[order[k]];
-        if (k > 0 && D.kind != host.back().kind && !one_launch) group_units = 0;
-        D.unit_begin = group_units;
-        D.chunk = chunk;
-        D.nunits = tiled ? D.ntiles : (D.np + chunk - 1) / chunk;
-        if (D.np == 0) D.nunits = 0;
-        group_units += D.nunits;
-        total_units += D.nunits;
+        plain_bins(c, D, push, deposit);
         host.push_back(D);
+    }
+    for (int i0 = 0, i1 = 0; i0 < nitems; i0 = i1) {
+        i1 = one_launch ? nitems : group_end(host, i0);
+        LocalPlan lp;
+        const Route r = one_launch ? ROUTE_RUNS : group_route(c, host.data() + i0, i1 - i0, push, deposit, lp);
+        int group_units = 0;
+        for (int k = i0; k < i1; ++k) {
+            ItemDesc &D = host[k];
+            D.unit_begin = group_units;
+            D.chunk = chunk;
+            // self-grouping kernels: one slot per tile and one per full chunk (k_local_impl.h, local_tile)
+            D.nunits = r == ROUTE_LOCAL ? D.ntiles + D.np / lp.cap : tiled ? D.ntiles : (D.np + chunk - 1) / chunk;
+            if (D.np == 0) D.nunits = 0;
+            group_units += D.nunits;
+            total_units += D.nunits;
+        }
     }
     return PL_OK;
 }
@@ -541,6 +552,15 @@ pl_status pl_part_init(pl_ctx **out, const pl_init_desc *d)
              hipMalloc(&c->idx[k], np * sizeof(uint32_t)) == hipSuccess;
     if (ok && d->key_mode == PL_KEY_TILE_RANK)
         ok = hipMalloc(&c->cell_start, (size_t)max_cells * sizeof(int32_t)) == hipSuccess;
+    if (ok && d->algo == PL_ALGO_PLAIN) {
+        // tiles of the calls' index bins: at least 4 cells along x and y, and no
+        // more than one per 64 particles
+        int64_t nt = 0;
+        for (const auto &b : c->boxes)
+            nt = std::max<int64_t>(nt, (int64_t)((b.n[0] + 3) / 4) * ((b.n[1] + 3) / 4) * ((b.n[2] + 3) / 4));
+        c->bin_cap = std::min<int64_t>(nt, (int64_t)np / 64 + 1);
+        ok = hipMalloc(&c->bin_start, (size_t)(c->bin_cap + 1) * sizeof(int32_t)) == hipSuccess;
+    }
     for (int k = 0; ok && k < Ctx::kGraphs; ++k)
         ok = hipMalloc(&c->graphs[k].table, mi * sizeof(ItemDesc)) == hipSuccess;
     for (int k = 0; ok && k < Ctx::kRing; ++k)

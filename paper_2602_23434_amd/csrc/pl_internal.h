@@ -88,6 +88,9 @@ struct ItemDesc {
     double *M[kMaxCh];
     int slot[kMaxCh];        // LDS slot of each active channel, -1 if inactive
     int nslot;
+    // plain algorithm, binned: the particles' indices by tile (null: the
+    // particles of a tile are consecutive)
+    const uint32_t *idx;
     // work decomposition
     int unit_begin;          // first global work unit of this item
     int nunits;
@@ -132,6 +135,8 @@ struct Ctx {
     int64_t hist_cap = 0;
     int64_t max_np = 0;
     int max_ntiles = 0;
+    int32_t *bin_start = nullptr;    // plain algorithm: tile offsets of a call's binned indices
+    int64_t bin_cap = 0;             // their capacity in tiles
 
     // pinned staging ring for item tables
     static constexpr int kRing = 8;
@@ -164,6 +169,24 @@ struct RunsPlan {
     bool mixed = false;
 };
 bool runs_plan(const Ctx *c, const ItemDesc *host, int nitems, RunsPlan &pl);
+
+// Launch configuration of a self-grouping tile kernel (k_local_impl.h) for
+// items of one species kind: mode, field halo, particles per chunk, LDS bytes.
+struct LocalPlan {
+    int mode = 0, hf = 1, cap = 0;
+    size_t lds = 0;
+};
+bool local_plan(const Ctx *c, const ItemDesc *host, int nitems, bool push, bool deposit, LocalPlan &pl);
+
+// Which kernel takes the items [i0, i1) of a call's ordered table in one
+// launch: the run-based kernel, a self-grouping tile kernel, or the
+// one-particle-per-thread kernel.
+enum Route { ROUTE_RUNS, ROUTE_LOCAL, ROUTE_STEP };
+int group_end(const std::vector<ItemDesc> &host, int i0);
+Route group_route(const Ctx *c, const ItemDesc *host, int nitems, bool push, bool deposit, LocalPlan &pl);
+// Plain algorithm: whether the call bins this item's particle indices by tile
+// first; sets the item's tiles, tile offsets and index list if so.
+bool plain_bins(const Ctx *c, ItemDesc &it, bool push, bool deposit);
 
 // Kernel launchers (k_step.hip)
 hipError_t launch_step(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc> &host, int nitems,
@@ -209,6 +232,11 @@ struct SortArgs {
     double *rdst[2];
 };
 hipError_t launch_sort(Ctx *c, const SortArgs &a);
+// Indices of an item's particles by tile (stable) into the item's idx, offsets
+// of the tiles into its tile_start; idx_buffer: which of the context's index
+// buffers the passes leave them in.
+int bins_buffer(int ntiles);
+hipError_t launch_bins(Ctx *c, const ItemDesc &it);
 // The same sort with its scratch in the library's fixed device array (set up
 // on the first call on each device); c supplies the stream only.
 hipError_t launch_sort_noalloc(Ctx *c, const SortArgs &a);
