@@ -162,7 +162,8 @@ typedef struct {
     int max_items;                   /* most items any one call passes (>= 1) */
     int64_t max_np;                  /* most particles in any one item (sizes the sort scratch) */
     int block;                       /* threads per block of the particle kernels (64..512, multiple of 64;
-                                        with PL_ALGO_RUNS: 512, the run-based kernel's block);
+                                        with PL_ALGO_RUNS: 512, the run-based kernel's block (on small
+                                        2D tiles it takes its own choice));
                                         0 = default */
     void *stream;                    /* hipStream_t for all work; NULL = the null stream */
     const char *tune_cache;          /* nullable: file written by the autotuner ("key value" lines: block,
@@ -439,8 +440,9 @@ pl_status pl_part_set_stream(pl_ctx *ctx, void *stream);
  * compiled for a fixed tile shape and channel set, out[7] the variant of the
  * last run-based launch: ts | chs << 4 | hf << 8 | mixed << 12, with mixed = 1
  * when the launch took items of several kinds (or tracers), ts the fixed tile
- * (1: 8x8x8, 2: 8x8x4, 0: taken at run time), chs the fixed channel set
- * (1: rho J F of charged particles, 2: rho F of dust, 0: taken at run time;
+ * (1: 8x8x8, 2: 8x8x4, 3: 8x8 in 2D, 0: taken at run time), chs the fixed channel set
+ * (1: rho J F of charged particles, 2: rho F of dust, 3: every channel of
+ * charged particles, 0: taken at run time;
  * a mixed launch reports its charged items' set)
  * and hf the field halo in cells (1 or 2). */
 #define PL_NSTATS 8

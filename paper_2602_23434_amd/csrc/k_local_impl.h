@@ -606,7 +606,7 @@ bool local_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, bool push, 
         np += host[i].np;
         nt += host[i].ntiles;
     }
-    if (np < kLocalMinPerTile * nt) return false;
+    if (!host[0].idx && np < kLocalMinPerTile * nt) return false;
     // chunks: what the LDS holds, and no more than leave each CU one
     const int64_t share = (np / c->num_cu + 255) / 256 * 256;
     pl.hf = 1;

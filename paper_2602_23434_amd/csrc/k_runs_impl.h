@@ -736,6 +736,7 @@ __host__ __device__ inline size_t runs_lds_bytes(int Lf, int Ld, int nslot, int 
 // most of the 160 KB), so two waves per SIMD: the compiler may spend registers
 // on reads in flight.
 constexpr int kRunsThreads = 512;
+constexpr int kRunsSmall = 256;
 
 // Gas velocity at a position of the Runge-Kutta scheme: from the LDS field
 // records when the stencil lies in the tile's field tile, else from the grid.
@@ -1131,9 +1132,9 @@ __device__ __forceinline__ void runs_latch(int err, int *errflags)
 
 // HF: field halo width (1 or 2) fixed at compile time, or 0 to take it from
 // the launch flags; TS and HF fixed make every LDS stencil offset an
-// immediate.
-template <int PREC, int SHAPE, int DIM, int KIND, int HF, int TS, int CHS>
-__global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_runs(const ItemDesc *__restrict__ items, int nitems, int total_units,
+// immediate.  NT: threads per block; with kRunsSmall two blocks share a CU.
+template <int PREC, int SHAPE, int DIM, int KIND, int HF, int TS, int CHS, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_runs(const ItemDesc *__restrict__ items, int nitems, int total_units,
                                              unsigned *counter, int *errflags, unsigned flags, int lds_bytes)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1190,29 +1191,38 @@ __global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2,
 // ---------------------------------------------------------------------------
 
 template <int PREC>
-static StepKernel pick_runs(int shape, int dim, int kind, int hf, int ts, int chs)
+static StepKernel pick_runs(int shape, int dim, int kind, int hf, int ts, int chs, int nt)
 {
-#define PL_R(S, D, K, HF_, TS_, CHS_) \
-    if (shape == S && dim == D && kind == K && hf == HF_ && ts == TS_ && chs == CHS_) \
-        return k_runs<PREC, S, D, K, HF_, TS_, CHS_>;
+#define PL_RN(S, D, K, HF_, TS_, CHS_, NT_) \
+    if (shape == S && dim == D && kind == K && hf == HF_ && ts == TS_ && chs == CHS_ && nt == NT_) \
+        return k_runs<PREC, S, D, K, HF_, TS_, CHS_, NT_>;
+#define PL_R(S, D, K, HF_, TS_, CHS_) PL_RN(S, D, K, HF_, TS_, CHS_, kRunsThreads)
 #define PL_RG(S, D) PL_R(S, D, PL_LORENTZ, 0, 0, 0) PL_R(S, D, PL_DUST, 0, 0, 0)
 #define PL_RF(HF_, TS_) PL_R(PL_TSC, 3, PL_LORENTZ, HF_, TS_, 1) PL_R(PL_TSC, 3, PL_DUST, HF_, TS_, 2)
     PL_RG(PL_TSC, 3) PL_RG(PL_TSC, 2) PL_RG(PL_CIC, 3) PL_RG(PL_CIC, 2)
     PL_RF(1, 1) PL_RF(2, 1) PL_RF(1, 2) PL_RF(2, 2)
+    // every charged channel (on 8^3 tiles only a one-cell field halo leaves the LDS for it)
+    PL_RN(PL_TSC, 2, PL_LORENTZ, 0, 0, 0, kRunsSmall) PL_RN(PL_TSC, 2, PL_DUST, 0, 0, 0, kRunsSmall)
+    PL_RN(PL_CIC, 2, PL_LORENTZ, 0, 0, 0, kRunsSmall) PL_RN(PL_CIC, 2, PL_DUST, 0, 0, 0, kRunsSmall)
+    PL_RN(PL_TSC, 2, PL_LORENTZ, 2, 3, 1, kRunsSmall) PL_RN(PL_TSC, 2, PL_LORENTZ, 2, 3, 3, kRunsSmall)
+    PL_RN(PL_TSC, 2, PL_DUST, 2, 3, 2, kRunsSmall)
+    PL_R(PL_TSC, 3, PL_LORENTZ, 1, 1, 3) PL_R(PL_TSC, 3, PL_LORENTZ, 1, 2, 3) PL_R(PL_TSC, 3, PL_LORENTZ, 2, 2, 3)
 #undef PL_RF
 #undef PL_RG
 #undef PL_R
+#undef PL_RN
     return nullptr;
 }
 
 template <int PREC>
-static StepKernel pick_runs_mix(int shape, int dim, int hf, int ts, int chl, int chd)
+StepKernel pick_runs_mix(int shape, int dim, int hf, int ts, int chl, int chd)
 {
 #define PL_M(S, D, HF_, TS_, CL, CD) \
     if (shape == S && dim == D && hf == HF_ && ts == TS_ && chl == CL && chd == CD) \
         return k_runs_mix<PREC, S, D, HF_, TS_, CL, CD>;
     PL_M(PL_TSC, 3, 0, 0, 0, 0) PL_M(PL_TSC, 2, 0, 0, 0, 0) PL_M(PL_CIC, 3, 0, 0, 0, 0) PL_M(PL_CIC, 2, 0, 0, 0, 0)
     PL_M(PL_TSC, 3, 1, 1, 1, 2) PL_M(PL_TSC, 3, 2, 1, 1, 2) PL_M(PL_TSC, 3, 1, 2, 1, 2) PL_M(PL_TSC, 3, 2, 2, 1, 2)
+    PL_M(PL_TSC, 3, 1, 1, 3, 2) PL_M(PL_TSC, 3, 1, 2, 3, 2) PL_M(PL_TSC, 3, 2, 2, 3, 2)
 #undef PL_M
     return nullptr;
 }
@@ -1234,28 +1244,43 @@ template <int PREC>
 bool runs_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, RunsPlan &pl)
 {
     pl = RunsPlan{};
+    pl.nt = kRunsThreads;
     if (nitems < 1) return false;
     bool kinds[3] = {false, false, false};
     for (int i = 0; i < nitems; ++i) kinds[host[i].kind] = true;
     pl.mixed = kinds[PL_TRACER] || (kinds[PL_LORENTZ] && kinds[PL_DUST]);
     // compile-time tile shape (8^3 or 8x8x4) and channel sets when every item
-    // allows them: charged rho J F, dust rho F
-    if (c->d.shape == PL_TSC && c->d.ndim == 3) {
+    // allows them: charged rho J F or all eight, dust rho F.  (With run-time
+    // shapes the LDS offsets are registers and the kernel spills: 5.3e6
+    // charged particles on 96^3 and eight 32^3 boxes, eight channels, 980 us
+    // against 806 us fixed; float64 on 96^3, 7.1e6 particles: 1105 us
+    // against 940 us.)
+    const bool d2 = c->d.ndim == 2;
+    if (c->d.shape == PL_TSC && !(d2 && pl.mixed)) {
+        auto set_of = [&](const ItemDesc &it, int want) {
+            for (int ch = 0; ch < kMaxCh; ++ch)
+                if (it.slot[ch] != chs_slot(want, ch)) return false;
+            return true;
+        };
+        int chl = 0;
         bool chall = true;
         for (int i = 0; i < nitems && chall; ++i) {
-            const int want = host[i].kind == PL_LORENTZ ? 1 : (host[i].kind == PL_DUST ? 2 : 0);
-            for (int ch = 0; ch < kMaxCh && want; ++ch) chall = chall && host[i].slot[ch] == chs_slot(want, ch);
+            if (host[i].kind == PL_DUST) chall = set_of(host[i], 2);
+            if (host[i].kind != PL_LORENTZ) continue;
+            const int got = set_of(host[i], 1) ? 1 : set_of(host[i], 3) ? 3 : 0;
+            chall = got && (chl == 0 || chl == got);
+            chl = got;
         }
-        for (int cand = 1; cand <= 2 && pl.ts == 0 && chall; ++cand) {
+        for (int cand = d2 ? 3 : 1; cand <= (d2 ? 3 : 2) && pl.ts == 0 && chall; ++cand) {
             bool all = true;
             for (int i = 0; i < nitems; ++i)
                 for (int a = 0; a < 3; ++a) all = all && host[i].tile[a] == ts_dim(cand, a);
             if (all) pl.ts = cand;
         }
-    }
-    if (pl.ts) {
-        pl.chl = 1;
-        pl.chd = 2;
+        if (pl.ts) {
+            pl.chl = chl ? chl : 1;
+            pl.chd = 2;
+        }
     }
     // LDS of the launch: a two-cell field halo when it fits, else one cell
     for (int hf = 2; hf >= 1; --hf) {
@@ -1264,6 +1289,14 @@ bool runs_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, RunsPlan &pl
         if (lds <= (size_t)c->lds_max) {
             pl.hf = hf;
             pl.lds = lds;
+            // 2D tiles whose LDS lets two blocks share a CU: a unit of an 8 x 8
+            // tile has fewer runs than a large block has threads, and its
+            // staging, runs and flush wait on each other (512^2 cells, 16
+            // particles per cell: 285 us per launch with one large block of
+            // run-time shape, 235 us with two small ones of fixed shape; four
+            // at half the registers spill: 313 us)
+            if (d2 && !pl.mixed && 2 * lds <= (size_t)c->lds_max) pl.nt = kRunsSmall;
+            else if (d2) pl.ts = pl.chl = pl.chd = 0;
             return true;
         }
     }
@@ -1287,10 +1320,10 @@ hipError_t launch_runs_impl(Ctx *c, const ItemDesc *table, const ItemDesc *host,
     } else {
         const int kind = host[0].kind;
         chs = pl.ts ? (kind == PL_LORENTZ ? pl.chl : pl.chd) : 0;
-        k = pick_runs<PREC>(c->d.shape, c->d.ndim, kind, pl.ts ? pl.hf : 0, pl.ts, chs);
+        k = pick_runs<PREC>(c->d.shape, c->d.ndim, kind, pl.ts ? pl.hf : 0, pl.ts, chs, pl.nt);
     }
     if (!k) return hipErrorInvalidConfiguration;
-    const int rb = kRunsThreads;
+    const int rb = pl.nt;
     // every item has kRunsSplit units beyond its tiles for the pieces of crowded tiles
     const int units = total_units + nitems * kRunsSplit;
     int grid = std::min(units, resident_blocks(c, k, rb, pl.lds));

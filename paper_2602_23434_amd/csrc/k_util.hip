@@ -22,11 +22,19 @@ hipError_t launch_local_f32(Ctx *c, const ItemDesc *table, const ItemDesc *host,
 hipError_t launch_local_f64(Ctx *c, const ItemDesc *table, const ItemDesc *host, int nitems, const LocalPlan &pl,
                             unsigned sf, unsigned *counter);
 
-// Plain algorithm: particles from which binning an item's indices costs less
-// than it saves (with a deposit, without one), and per tile of the bins.
-constexpr int kBinMinDeposit = 8192;
-constexpr int kBinMinPush = 65536;
-constexpr int kBinMinPerTile = 64;
+// Plain algorithm: when binning an item's indices costs less than it saves.
+// The direct kernel's deposits are global atomics (2.4e10/s at random, and a
+// chain of 370 us for even one particle per lane in 3D); a bin's tile costs a
+// work unit (about 10 us on one of 256 CUs).  Measured per step in us, direct
+// and binned (float64, 3D unless said):
+//   with a deposit: 2048 particles on 16^3 cells 370 and 59, on 64^3 (1024
+//     tiles) 512 and 145; in 2D 137 and 56.  So: a few hundred particles, and
+//     at least 6 per tile unless the tiles are few;
+//   push only (tracers): 131072 particles on 32^3 88 and 80, on 64^3 170 and
+//     140, but on 16^3, whose fields stay in the caches, 68 and 104; in 2D
+//     262144 on 256^2 63 and 84, 1048576 250 and 186.
+constexpr int kBinMinDeposit = 512, kBinMinPerTile = 6, kBinFewTiles = 4096;
+constexpr int kBinMinPush = 131072, kBinMinPush2D = 524288, kBinMinPushCells = 20000, kBinMinPushPerTile = 32;
 
 // Items of one launch: those of one species kind; an item whose indices the
 // call bins (plain algorithm) has one of its own.
@@ -61,18 +69,21 @@ bool plain_bins(const Ctx *c, ItemDesc &it, bool push, bool deposit)
     if (c->d.algo != PL_ALGO_PLAIN) return false;
     const bool dep = deposit && it.kind != PL_TRACER && it.nslot > 0;
     if (!push && !dep) return false;
-    if (it.np < (dep ? kBinMinDeposit : kBinMinPush)) return false;
+    const bool d3 = c->d.ndim == 3;
+    if (it.np < (dep ? kBinMinDeposit : d3 ? kBinMinPush : kBinMinPush2D)) return false;
+    if (!dep && (int64_t)it.n[0] * it.n[1] * it.n[2] < kBinMinPushCells) return false;
     ItemDesc d = it;
     const bool f64 = c->d.prec == PL_F64;
-    d.tile[0] = c->d.ndim == 3 ? 8 : 32;
-    d.tile[1] = c->d.ndim == 3 ? 8 : (f64 ? 16 : 32);
-    d.tile[2] = c->d.ndim == 3 ? (f64 || it.nslot > 7 ? 4 : 8) : 1;
+    d.tile[0] = d3 ? 8 : 32;
+    d.tile[1] = d3 ? 8 : (f64 ? 16 : 32);
+    d.tile[2] = d3 ? (f64 || it.nslot > 7 ? 4 : 8) : 1;
     int64_t nt = 1;
     for (int a = 0; a < 3; ++a) {
         d.ntile[a] = (d.n[a] + d.tile[a] - 1) / d.tile[a];
         nt *= d.ntile[a];
     }
-    if (nt > c->bin_cap || it.np / kBinMinPerTile < nt) return false;
+    if (nt > c->bin_cap) return false;
+    if (dep ? (it.np / kBinMinPerTile < nt && nt > kBinFewTiles) : it.np / kBinMinPushPerTile < nt) return false;
     d.ntiles = (int)nt;
     d.tile_start = c->bin_start;
     d.idx = c->idx[bins_buffer(d.ntiles)];

@@ -286,7 +286,8 @@ pl_status build_table(Ctx *c, const pl_item *items, int nitems, double dt, Mode 
     host.clear();
     total_units = 0;
     const bool tiled = c->d.algo != PL_ALGO_PLAIN;
-    const int chunk = c->block * 4;
+    // plain: one to four particles per thread, as many as fill the chip
+    const int64_t wide = (int64_t)c->block * c->num_cu * 4;
     // a fused run-based step whose LDS fits takes every kind in one launch
     // (units numbered across all items); otherwise one launch per kind
     bool one_launch = false;
@@ -310,6 +311,7 @@ pl_status build_table(Ctx *c, const pl_item *items, int nitems, double dt, Mode 
         for (int k = i0; k < i1; ++k) {
             ItemDesc &D = host[k];
             D.unit_begin = group_units;
+            const int chunk = c->block * (int)std::min<int64_t>(4, 1 + D.np / wide);
             D.chunk = chunk;
             // self-grouping kernels: one slot per tile and one per full chunk (k_local_impl.h, local_tile)
             D.nunits = r == ROUTE_LOCAL ? D.ntiles + D.np / lp.cap : tiled ? D.ntiles : (D.np + chunk - 1) / chunk;
@@ -553,12 +555,12 @@ pl_status pl_part_init(pl_ctx **out, const pl_init_desc *d)
     if (ok && d->key_mode == PL_KEY_TILE_RANK)
         ok = hipMalloc(&c->cell_start, (size_t)max_cells * sizeof(int32_t)) == hipSuccess;
     if (ok && d->algo == PL_ALGO_PLAIN) {
-        // tiles of the calls' index bins: at least 4 cells along x and y, and no
-        // more than one per 64 particles
+        // tiles of the calls' index bins: at least 4 cells along each dimension, and
+        // no more than one per 4 particles unless they are few
         int64_t nt = 0;
         for (const auto &b : c->boxes)
             nt = std::max<int64_t>(nt, (int64_t)((b.n[0] + 3) / 4) * ((b.n[1] + 3) / 4) * ((b.n[2] + 3) / 4));
-        c->bin_cap = std::min<int64_t>(nt, (int64_t)np / 64 + 1);
+        c->bin_cap = std::min<int64_t>(nt, std::max<int64_t>((int64_t)np / 4, 8192));
         ok = hipMalloc(&c->bin_start, (size_t)(c->bin_cap + 1) * sizeof(int32_t)) == hipSuccess;
     }
     for (int k = 0; ok && k < Ctx::kGraphs; ++k)

@@ -161,10 +161,10 @@ struct Ctx {
 
 // Launch configuration of the run kernel for one launch's items: field halo,
 // compile-time tile shape (0 generic, 1 8^3, 2 8x8x4), channel sets of the
-// charged (1: rho J F) and dust (2: rho F) items, LDS bytes, and whether the
-// items mix species kinds (one launch dispatching per unit).
+// charged (1: rho J F, 3: every channel) and dust (2: rho F) items, LDS bytes, and whether the
+// items mix species kinds (one launch dispatching per unit); threads per block.
 struct RunsPlan {
-    int hf = 0, ts = 0, chl = 0, chd = 0;
+    int hf = 0, ts = 0, chl = 0, chd = 0, nt = 0;
     size_t lds = 0;
     bool mixed = false;
 };
