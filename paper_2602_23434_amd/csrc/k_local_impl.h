@@ -301,6 +301,7 @@ __device__ __forceinline__ void local_unit(const ItemDesc &I, int t, int pbeg, i
     S.dq_d = reinterpret_cast<R *>(smem + L.work + runs_section((size_t)LocalBatch<PREC>::DQ * 4));
     S.dq_mu = S.dq_d + 3 * LocalBatch<PREC>::DQ;
     S.dq = LocalBatch<PREC>::DQ;
+    S.narrow = false;
     S.ctl = reinterpret_cast<int *>(smem + ctl_at);
     S.sums = reinterpret_cast<double *>(smem + L.sums);
     S.smask = kLocalSums - 1;
@@ -410,8 +411,8 @@ __device__ __forceinline__ void local_unit(const ItemDesc &I, int t, int pbeg, i
         }
         __syncthreads();
 
-        // the chunk's runs, one batch each; the next batch is fetched before
-        // the current one is worked on
+        // the chunk's runs, one batch each; the next batch is fetched while the
+        // current one deposits
         auto run_at = [&](int r, int (&pi)[KR]) -> int {
             const unsigned v = list[r];
             const int s = (int)(v >> 2), len = (int)(v & 3u) + 1;
@@ -428,48 +429,48 @@ __device__ __forceinline__ void local_unit(const ItemDesc &I, int t, int pbeg, i
             fetch_indexed<PREC, DIM, KR>(U, pi, len, cur);
         }
         while (have) {
-            const int rn = r + bd;
-            const bool nhave = rn < nruns;
-            int ni[KR];
-            BatchRaw<PREC, DIM, KR> nxt;
-            if (nhave) {
-                const int len = run_at(rn, ni);
-                fetch_indexed<PREC, DIM, KR>(U, ni, len, nxt);
-            }
+            r += bd;
+            have = r < nruns;
+            const BatchRaw<PREC, DIM, KR> now = cur;
+            int pn[KR];
+#pragma unroll
+            for (int j = 0; j < KR; ++j) pn[j] = pi[j];
+            auto fetch = [&]() {
+                if (have) {
+                    const int len = run_at(r, pi);
+                    fetch_indexed<PREC, DIM, KR>(U, pi, len, cur);
+                }
+            };
             if constexpr (MODE == LM_FUSED) {
-                run_batch<PREC, SHAPE, DIM, KIND, CHS, KR, false, true>(U, G, S, cur, pi, do_sums, err);
+                run_batch<PREC, SHAPE, DIM, KIND, CHS, KR, false, true>(U, G, S, now, pn, do_sums, err, fetch);
             } else {
                 Pos<PREC, DIM> ps[KR];
                 R mu[KR][kMaxCh];
                 bool in[KR];
 #pragma unroll
                 for (int j = 0; j < KR; ++j) {
-                    in[j] = j < cur.len;
+                    in[j] = j < now.len;
                     if (in[j]) {
-                        ps[j].set(cur.pr[j], U, err);
-                        state_values<PREC, KIND>(U, pi[j], cur.u[j], cur.w[j], mu[j]);
+                        ps[j].set(now.pr[j], U, err);
+                        state_values<PREC, KIND>(U, pn[j], now.u[j], now.w[j], mu[j]);
                     } else {
                         ps[j] = ps[0];
 #pragma unroll
                         for (int ch = 0; ch < kMaxCh; ++ch) mu[j][ch] = R(0);
                     }
                 }
+                fetch();
                 int db = 0;
                 if (dep_base<DIM>(G, U.n, ps[0].c, db))
                     batch_deposit<PREC, SHAPE, DIM, CHS, KR, true>(U, G, S, db, ps, mu, in);
             }
-            cur = nxt;
-#pragma unroll
-            for (int j = 0; j < KR; ++j) pi[j] = ni[j];
-            r = rn;
-            have = nhave;
         }
         if constexpr (MODE == LM_FUSED) {
             __syncthreads();
             const int ng = min(ctl[1], gq_cap(1)), nd = min(ctl[2], S.dq);
             for (int i = threadIdx.x; i < ng; i += blockDim.x)
                 particle_single<PREC, SHAPE, DIM, KIND, CHS>(U, G, S, S.gq[i], do_sums, err);
-            for (int i = threadIdx.x; i < nd; i += blockDim.x) record_deposit<PREC, SHAPE, DIM, CHS>(U, G, S, i);
+            drain_deposits<PREC, SHAPE, DIM, CHS>(U, G, S, nd);
         }
     }
     __syncthreads();

@@ -40,23 +40,22 @@ __host__ __device__ constexpr int gq_cap(int hf) { return hf == 2 ? 64 : 256; }
 template <int PREC, bool DACC> struct AccOf { using T = typename RealOf<PREC>::T; };
 template <int PREC> struct AccOf<PREC, true> { using T = double; };
 
-template <int PREC> struct RunsQ { static constexpr int DQ = PREC == PL_F32_OFFSET ? 256 : 128; };
+// Capacity of the queue of deposits outside their batch's cell (float32: what
+// the LDS leaves beside every channel and a two-cell field halo on 8^3 tiles).
+template <int PREC> struct RunsQ { static constexpr int DQ = PREC == PL_F32_OFFSET ? 192 : 128; };
 
-// LDS field records, read with 16-byte loads.  Lanes of a wave read
-// records of neighbouring cells, so the record stride decides the bank
-// pattern: float32 charged particles use two planes of 16-byte records
-// (E0 E1 E2 0 | B0 B1 B2 0, the B plane Lf records after the E plane), so 16
-// lanes of one pass cover all 64 banks; float64 charged: one 48-byte record
-// E0 E1 E2 B0 B1 B2; three-component kinds: v0 v1 v2 0.
+// LDS field records.  Lanes of a wave read records of neighbouring cells, so
+// the record stride decides the bank pattern: float32 charged particles use a
+// plane of 16-byte records and a plane of 8-byte ones (E0 E1 E2 B0 | B1 B2,
+// the second after the Lf records of the first), read with one 16- and one
+// 8-byte access each: the gather is bound by the LDS bandwidth (a point's
+// records take 16 of its cycles per wave at 32 bytes, 12 at 24, against 32
+// cycles of fused multiply-adds shared by four SIMDs); float64 charged: one
+// 48-byte record E0 E1 E2 B0 B1 B2; three-component kinds: v0 v1 v2 0.
 template <int PREC, int KIND> struct FieldRec {
     static constexpr int NC = KIND == PL_LORENTZ ? 6 : 3;
-    static constexpr int FS = PREC == PL_F32_OFFSET ? (NC == 6 ? 8 : 4) : (NC == 6 ? 6 : 4);
+    static constexpr int FS = PREC == PL_F32_OFFSET ? (NC == 6 ? 6 : 4) : (NC == 6 ? 6 : 4);
     static constexpr bool PLANES = PREC == PL_F32_OFFSET && NC == 6;
-    // position of component q of cell e in a tile of Lf records
-    __host__ __device__ static constexpr int at(int e, int q, int Lf)
-    {
-        return PLANES ? (q < 3 ? 4 * e + q : 4 * Lf + 4 * e + (q - 3)) : FS * e + q;
-    }
 };
 
 template <int PREC, int KIND>
@@ -65,12 +64,11 @@ __device__ __forceinline__ void load_rec(const typename RealOf<PREC>::T *lds_f, 
 {
     if constexpr (PREC == PL_F32_OFFSET) {
         const float4 *p = reinterpret_cast<const float4 *>(lds_f);
+        const float4 a = p[cell];
+        f[0] = a.x; f[1] = a.y; f[2] = a.z;
         if constexpr (KIND == PL_LORENTZ) {
-            float4 a = p[cell], b = p[Lf + cell];
-            f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = b.x; f[4] = b.y; f[5] = b.z;
-        } else {
-            float4 a = p[cell];
-            f[0] = a.x; f[1] = a.y; f[2] = a.z;
+            const float2 b = reinterpret_cast<const float2 *>(p + Lf)[cell];
+            f[3] = a.w; f[4] = b.x; f[5] = b.y;
         }
     } else {
         const double2 *p = reinterpret_cast<const double2 *>(lds_f);
@@ -88,6 +86,14 @@ __device__ __forceinline__ int wrap_any(int i, int n)
 {
     int r = i % n;
     return r < 0 ? r + n : r;
+}
+
+// The same for an index at most one box length outside, as a tile's halo
+// cells mostly are (without the division).
+__device__ __forceinline__ int wrap_near(int i, int n)
+{
+    const int r = i < 0 ? i + n : (i >= n ? i - n : i);
+    return (unsigned)r < (unsigned)n ? r : wrap_any(i, n);
 }
 
 // Geometry of one tile: field tile with an hf-cell halo (1 or 2), deposit
@@ -117,6 +123,15 @@ __device__ __forceinline__ bool field_base(const RunGeo &g, const int n[3], cons
         l[a] = v + h;
     }
     base = l[0] + (DIM >= 2 ? l[1] * g.fx : 0) + (DIM >= 3 ? l[2] * g.fxy : 0);
+    return ok;
+}
+
+template <int DIM>
+__device__ __forceinline__ bool inside_tile(const RunGeo &g, const int c[3])
+{
+    bool ok = true;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) ok = ok && (unsigned)(c[a] - g.lo[a]) < (unsigned)g.T[a];
     return ok;
 }
 
@@ -218,8 +233,9 @@ template <int PREC> struct RunShared {
     uint32_t *dq_c;
     R *dq_d;      // 3 x dq
     R *dq_mu;     // nslot x dq
-    int *ctl;     // [0] claimed unit, [1] queued particles, [2] queued deposits
+    int *ctl;     // [1] queued particles, [2] queued deposits
     int dq;       // capacity of the deposit queue
+    bool narrow;  // only particles inside the tile join their batch's deposit sums
     double *sums; // 8 particle-side sums of the unit, smask + 1 partial sums each
     int smask;
 };
@@ -330,22 +346,57 @@ __device__ __forceinline__ void particle_single(const UnitC<PREC> &U, const RunG
     deposit_single<PREC, SHAPE, DIM, CHS>(U, G, S.lds_d, pos.c, dn, mud);
 }
 
-// Deposit of a queued record.
+// Deposit of the queued records: one stencil row of one record per lane, so
+// that a few dozen records keep every wave of the block busy for a few atomics
+// instead of one wave for all of theirs (the block waits for the queue's end).
 template <int PREC, int SHAPE, int DIM, int CHS>
-__device__ __forceinline__ void record_deposit(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S, int i)
+__device__ __forceinline__ void drain_deposits(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S, int nd)
 {
     using R = typename RealOf<PREC>::T;
+    constexpr int SY = Stencil<DIM>::SY, SZ = Stencil<DIM>::SZ, NROW = SY * SZ;
     const int DQ = S.dq;
-    int c[3];
-    unpack_cell(S.dq_c[i], c[0], c[1], c[2]);
-    R d[3] = {S.dq_d[i], S.dq_d[DQ + i], S.dq_d[2 * DQ + i]};
-    double mu[kMaxCh];
+    for (int task = threadIdx.x; task < nd * NROW; task += blockDim.x) {
+        const int i = task / NROW, row = task % NROW, kk = row / 3, jj = row % 3;
+        int c[3];
+        unpack_cell(S.dq_c[i], c[0], c[1], c[2]);
+        const R d[3] = {S.dq_d[i], S.dq_d[DQ + i], S.dq_d[2 * DQ + i]};
+        R wx[3], wy[3], wz[3];
+        stencil_weights<PREC, SHAPE, DIM>(d, wx, wy, wz);
+        auto pick = [](const R w[3], int k) -> R { return k == 0 ? w[0] : k == 1 ? w[1] : w[2]; };
+        const R wyz = pick(wz, kk) * pick(wy, jj);
+        double mu[kMaxCh];
 #pragma unroll
-    for (int ch = 0; ch < kMaxCh; ++ch) {
-        int so = ch_off<CHS>(U, ch, G.Ld);
-        mu[ch] = so >= 0 ? (double)S.dq_mu[(so / G.Ld) * DQ + i] : 0.0;
+        for (int ch = 0; ch < kMaxCh; ++ch) {
+            const int so = ch_off<CHS>(U, ch, G.Ld);
+            mu[ch] = so >= 0 ? (double)S.dq_mu[(so / G.Ld) * DQ + i] : 0.0;
+        }
+        int base = 0;
+        if (dep_base<DIM>(G, U.n, c, base)) {
+            double *at = S.lds_d + base + kk * G.dxy + jj * G.dx;
+#pragma unroll
+            for (int ii = 0; ii < 3; ++ii) {
+                const double w = (double)(wyz * wx[ii]);
+#pragma unroll
+                for (int ch = 0; ch < kMaxCh; ++ch) {
+                    const int so = ch_off<CHS>(U, ch, G.Ld);
+                    if (so >= 0)
+                        __hip_atomic_fetch_add(at + so + ii, w * mu[ch], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+        } else {
+            const int gy = DIM >= 2 ? wrap_cell(c[1] + jj - 1, U.n[1]) : 0;
+            const int gz = DIM >= 3 ? wrap_cell(c[2] + kk - 1, U.n[2]) : 0;
+            const long grow = (long)U.n[0] * (gy + (long)U.n[1] * gz);
+#pragma unroll
+            for (int ii = 0; ii < 3; ++ii) {
+                const double w = (double)(wyz * wx[ii]) * U.inv_dv;
+                const long gc = grow + wrap_cell(c[0] + ii - 1, U.n[0]);
+#pragma unroll
+                for (int ch = 0; ch < kMaxCh; ++ch)
+                    if (ch_off<CHS>(U, ch, G.Ld) >= 0) global_add(U.M[ch] + gc, w * mu[ch]);
+            }
+        }
     }
-    deposit_single<PREC, SHAPE, DIM, CHS>(U, G, S.lds_d, c, d, mu);
 }
 
 // Deposit of the batch particles in the reference cell (dco[j]): their values
@@ -408,21 +459,36 @@ template <class T, int K> struct Vec {
     typedef const __attribute__((address_space(1))) V *CP;
 };
 
-template <class T, int K>
-__device__ __forceinline__ void load_vec(gptr<const T> p, T (&out)[K])
+// (n < 2^29 with the run-based algorithm, so a 32-bit byte offset from an
+// array's base holds every element: one scalar base and one offset register per
+// batch instead of a 64-bit address per array)
+template <class T>
+__device__ __forceinline__ gptr<T> at32(gptr<T> base, int i)
 {
-    const typename Vec<T, K>::V v = *reinterpret_cast<typename Vec<T, K>::CP>(p);
+    return (gptr<T>)((gptr<char>)base + (uint32_t)((uint32_t)i * (uint32_t)sizeof(T)));
+}
+
+template <class T>
+__device__ __forceinline__ gptr<const T> at32c(gptr<const T> base, int i)
+{
+    return (gptr<const T>)((gptr<const char>)base + (uint32_t)((uint32_t)i * (uint32_t)sizeof(T)));
+}
+
+template <class T, int K>
+__device__ __forceinline__ void load_vec(gptr<const T> base, int i, T (&out)[K])
+{
+    const typename Vec<T, K>::V v = *reinterpret_cast<typename Vec<T, K>::CP>(at32c<T>(base, i));
 #pragma unroll
     for (int k = 0; k < K; ++k) out[k] = v[k];
 }
 
 template <class T, int K>
-__device__ __forceinline__ void store_vec(gptr<T> p, const T (&in)[K])
+__device__ __forceinline__ void store_vec(gptr<T> base, int i, const T (&in)[K])
 {
     typename Vec<T, K>::V v;
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = in[k];
-    *reinterpret_cast<typename Vec<T, K>::P>(p) = v;
+    *reinterpret_cast<typename Vec<T, K>::P>(at32<T>(base, i)) = v;
 }
 
 // State of a whole batch (every slot handled in place) written back with one
@@ -439,49 +505,48 @@ __device__ __forceinline__ void store_batch(const UnitC<PREC> &U, int start, con
 #pragma unroll
         for (int j = 0; j < KR; ++j)
             cv[j] = pack_cell(pos[j].c[0], DIM > 1 ? pos[j].c[1] : 0, DIM > 2 ? pos[j].c[2] : 0);
-        store_vec<uint32_t, KR>(U.cell + start, cv);
+        store_vec<uint32_t, KR>(U.cell, start, cv);
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
 #pragma unroll
             for (int j = 0; j < KR; ++j) t[j] = pos[j].d[a];
-            store_vec<R, KR>(U.x[a] + start, t);
+            store_vec<R, KR>(U.x[a], start, t);
         }
     } else {
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
 #pragma unroll
             for (int j = 0; j < KR; ++j) t[j] = pos[j].x[a];
-            store_vec<R, KR>(U.x[a] + start, t);
+            store_vec<R, KR>(U.x[a], start, t);
         }
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
 #pragma unroll
         for (int j = 0; j < KR; ++j) t[j] = u[j][a];
-        store_vec<R, KR>(U.u[a] + start, t);
+        store_vec<R, KR>(U.u[a], start, t);
     }
     if (U.fp[0]) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
 #pragma unroll
             for (int j = 0; j < KR; ++j) t[j] = mu[j][4 + a];
-            store_vec<R, KR>(U.fp[a] + start, t);
+            store_vec<R, KR>(U.fp[a], start, t);
         }
     }
 }
 
-// Gather, push and deposit of the batch particles whose stencil lies in the
+// Gather and push of the batch particles whose stencil lies in the
 // LDS field tile (co[j]); fb[j] is the field record of stencil point
 // (-1,-1,-1) of particle j, pi[j] its index (SEQ: pi[0] + j).
-template <int PREC, int SHAPE, int DIM, int KIND, int CHS, int KR, bool SEQ, bool DACC>
-__device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S,
+template <int PREC, int SHAPE, int DIM, int KIND, int KR, bool SEQ>
+__device__ __forceinline__ void batch_push(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S,
                                            const int pi[KR], const int fb[KR], Pos<PREC, DIM> pos[KR], typename RealOf<PREC>::T u[KR][3],
-                                           const typename RealOf<PREC>::T w[KR], const bool co[KR], bool do_sums, int &err)
+                                           const typename RealOf<PREC>::T w[KR], const bool co[KR],
+                                           typename RealOf<PREC>::T mu[KR][kMaxCh], bool do_sums, int &err)
 {
     using R = typename RealOf<PREC>::T;
     constexpr int NC = FieldRec<PREC, KIND>::NC;
-    constexpr int SY = Stencil<DIM>::SY, SZ = Stencil<DIM>::SZ;
-    const int DQ = S.dq;
 
     // a batch of consecutive particles whose slots are all handled here is
     // written back at the end with one access per array; otherwise every slot
@@ -492,7 +557,6 @@ __device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G
 
     // gather and push one particle at a time (each stencil point is one
     // interleaved LDS record read); keep what the batched deposit needs
-    R mu[KR][kMaxCh];
 #pragma unroll
     for (int j = 0; j < KR; ++j) {
         const int p = SEQ ? pi[0] + j : pi[j];
@@ -511,27 +575,43 @@ __device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G
         if (co[j]) {
             err |= e2;
             if (!whole) {
-                pos[j].store(U, p);
+                if constexpr (SEQ) {
+                    const Pos<PREC, DIM> one[1] = {pos[j]};
+                    const R uo[1][3] = {{u[j][0], u[j][1], u[j][2]}};
+                    const R mo[1][kMaxCh] = {{R(0), R(0), R(0), R(0), mu[j][4], mu[j][5], mu[j][6], R(0)}};
+                    store_batch<PREC, DIM, 1>(U, p, one, uo, mo);
+                } else {
+                    pos[j].store(U, p);
 #pragma unroll
-                for (int a = 0; a < 3; ++a) U.u[a][p] = u[j][a];
-                if (U.fp[0]) {
+                    for (int a = 0; a < 3; ++a) U.u[a][p] = u[j][a];
+                    if (U.fp[0]) {
 #pragma unroll
-                    for (int a = 0; a < 3; ++a) U.fp[a][p] = mu[j][4 + a];
+                        for (int a = 0; a < 3; ++a) U.fp[a][p] = mu[j][4 + a];
+                    }
                 }
             }
             if (do_sums) add_sums(S, mu[j]);
         }
     }
     if (whole) store_batch<PREC, DIM, KR>(U, pi[0], pos, u, mu);
+}
 
-    // deposit: the batch particles in the reference cell are summed before
-    // each LDS atomic; the others are queued.  The reference is the new cell
-    // of the first batch particle, or of the second when the first shares its
-    // cell with no other batch particle.
+// Deposit of a pushed batch.  The batch particles in the reference cell are
+// summed before each LDS atomic; the others are queued.  The reference is the
+// new cell of the first batch particle, or of the second when the first shares
+// its cell with no other batch particle.  co: the batch particles handled here,
+// own: those of them that may join the sums.
+template <int PREC, int SHAPE, int DIM, int CHS, int KR, bool DACC>
+__device__ __forceinline__ void batch_dep(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S,
+                                          const Pos<PREC, DIM> pos[KR], typename RealOf<PREC>::T mu[KR][kMaxCh],
+                                          const bool co[KR], const bool own[KR])
+{
+    using R = typename RealOf<PREC>::T;
+    const int DQ = S.dq;
     int f0 = -1, f1 = -1;
 #pragma unroll
     for (int j = KR - 1; j >= 0; --j) {
-        if (co[j]) {
+        if (own[j]) {
             f1 = f0;
             f0 = j;
         }
@@ -544,7 +624,7 @@ __device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G
             for (int a = 0; a < 3; ++a) rc[a] = pos[j].c[a];
     bool alone = true;
 #pragma unroll
-    for (int j = 0; j < KR; ++j) alone = alone && (j == f0 || !(co[j] && same_cell<DIM>(pos[j].c, rc)));
+    for (int j = 0; j < KR; ++j) alone = alone && (j == f0 || !(own[j] && same_cell<DIM>(pos[j].c, rc)));
     if (alone && f1 >= 0) {
 #pragma unroll
         for (int j = 0; j < KR; ++j)
@@ -553,12 +633,12 @@ __device__ __forceinline__ void batch_body(const UnitC<PREC> &U, const RunGeo &G
                 for (int a = 0; a < 3; ++a) rc[a] = pos[j].c[a];
     }
     int db = 0;
-    const bool dep_in = dep_base<DIM>(G, U.n, rc, db);
+    const bool dep_in = f0 >= 0 && dep_base<DIM>(G, U.n, rc, db);
     bool dco[KR];
     bool any_dco = false;
 #pragma unroll
     for (int j = 0; j < KR; ++j) {
-        dco[j] = co[j] && dep_in && same_cell<DIM>(pos[j].c, rc);
+        dco[j] = own[j] && dep_in && same_cell<DIM>(pos[j].c, rc);
         any_dco = any_dco || dco[j];
     }
     unsigned ovf_d = 0;
@@ -614,31 +694,31 @@ __device__ __forceinline__ void fetch_batch(const UnitC<PREC> &U, int start, int
         R t[KR];
         if constexpr (PREC == PL_F32_OFFSET) {
             uint32_t cv[KR];
-            load_vec<uint32_t, KR>((gptr<const uint32_t>)(U.cell + start), cv);
+            load_vec<uint32_t, KR>((gptr<const uint32_t>)U.cell, start, cv);
 #pragma unroll
             for (int j = 0; j < KR; ++j) B.pr[j].cell = cv[j];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                if (a < DIM) load_vec<R, KR>((gptr<const R>)(U.x[a] + start), t);
+                if (a < DIM) load_vec<R, KR>((gptr<const R>)U.x[a], start, t);
 #pragma unroll
                 for (int j = 0; j < KR; ++j) B.pr[j].o[a] = a < DIM ? t[j] : 0.0f;
             }
         } else {
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                if (a < DIM) load_vec<R, KR>((gptr<const R>)(U.x[a] + start), t);
+                if (a < DIM) load_vec<R, KR>((gptr<const R>)U.x[a], start, t);
 #pragma unroll
                 for (int j = 0; j < KR; ++j) B.pr[j].x[a] = a < DIM ? t[j] : 0.0;
             }
         }
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            load_vec<R, KR>((gptr<const R>)(U.u[a] + start), t);
+            load_vec<R, KR>((gptr<const R>)U.u[a], start, t);
 #pragma unroll
             for (int j = 0; j < KR; ++j) B.u[j][a] = t[j];
         }
         if (U.w) {
-            load_vec<R, KR>(U.w + start, t);
+            load_vec<R, KR>(U.w, start, t);
 #pragma unroll
             for (int j = 0; j < KR; ++j) B.w[j] = t[j];
         } else {
@@ -650,19 +730,35 @@ __device__ __forceinline__ void fetch_batch(const UnitC<PREC> &U, int start, int
 #pragma unroll
     for (int j = 0; j < KR; ++j) {
         const int p = start + j;
-        const bool in = j < len;
-        if (in) Pos<PREC, DIM>::fetch(U, p, B.pr[j]);
-        else B.pr[j] = B.pr[0];
+        if (j < len) {
+            if constexpr (PREC == PL_F32_OFFSET) {
+                B.pr[j].cell = *at32<uint32_t>(U.cell, p);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) B.u[j][a] = in ? U.u[a][p] : R(0);
-        B.w[j] = in ? (U.w ? U.w[p] : U.wdef) : R(0);
+                for (int a = 0; a < 3; ++a) B.pr[j].o[a] = a < DIM ? *at32<R>(U.x[a], p) : 0.0f;
+            } else {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) B.pr[j].x[a] = a < DIM ? *at32<R>(U.x[a], p) : 0.0;
+            }
+#pragma unroll
+            for (int a = 0; a < 3; ++a) B.u[j][a] = *at32<R>(U.u[a], p);
+            B.w[j] = U.w ? *at32c<R>(U.w, p) : U.wdef;
+        } else {
+            B.pr[j] = B.pr[0];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) B.u[j][a] = R(0);
+            B.w[j] = R(0);
+        }
     }
 }
 
 // One batch of up to KR particles of one run, of indices pi[j] (SEQ: pi[0] + j).
-template <int PREC, int SHAPE, int DIM, int KIND, int CHS, int KR, bool SEQ, bool DACC>
+// mid() is called between the push and the deposit: the caller issues the next
+// batch's loads there, where the gather's registers are free and the deposit
+// covers them.
+template <int PREC, int SHAPE, int DIM, int KIND, int CHS, int KR, bool SEQ, bool DACC, class Mid>
 __device__ __forceinline__ void run_batch(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S,
-                                          const BatchRaw<PREC, DIM, KR> &Bt, const int pi[KR], bool do_sums, int &err)
+                                          const BatchRaw<PREC, DIM, KR> &Bt, const int pi[KR], bool do_sums, int &err,
+                                          Mid mid)
 {
     using R = typename RealOf<PREC>::T;
     const int len = Bt.len;
@@ -679,10 +775,11 @@ __device__ __forceinline__ void run_batch(const UnitC<PREC> &U, const RunGeo &G,
     // every particle whose stencil lies in the LDS field tile is gathered in
     // the batch from its own cell (lanes read distinct records anyway)
     int fb[KR];
-    bool co[KR];
+    bool co[KR], own[KR];
 #pragma unroll
     for (int j = 0; j < KR; ++j) {
         co[j] = field_base<DIM>(G, U.n, pos[j].c, fb[j]) && j < len;
+        own[j] = co[j] && !(S.narrow && !inside_tile<DIM>(G, pos[j].c));
         if (!co[j]) fb[j] = 0;       // computed but unused: keep its reads inside the field tile
     }
     // particles outside the tile: queue for the single-particle path (when
@@ -699,7 +796,10 @@ __device__ __forceinline__ void run_batch(const UnitC<PREC> &U, const RunGeo &G,
     bool any = false;
 #pragma unroll
     for (int j = 0; j < KR; ++j) any = any || co[j];
-    if (any) batch_body<PREC, SHAPE, DIM, KIND, CHS, KR, SEQ, DACC>(U, G, S, pi, fb, pos, u, w, co, do_sums, err);
+    R mu[KR][kMaxCh];
+    if (any) batch_push<PREC, SHAPE, DIM, KIND, KR, SEQ>(U, G, S, pi, fb, pos, u, w, co, mu, do_sums, err);
+    mid();
+    if (any) batch_dep<PREC, SHAPE, DIM, CHS, KR, DACC>(U, G, S, pos, mu, co, own);
     while (ovf_g) {
         const int j = __builtin_ctz(ovf_g);
         ovf_g &= ovf_g - 1u;
@@ -713,15 +813,28 @@ __device__ __forceinline__ void run_batch(const UnitC<PREC> &U, const RunGeo &G,
     }
 }
 
+// Threads of the small blocks, and the deposit queue of a block.
+constexpr int kRunsSmall = 256;
+template <int PREC> __host__ __device__ constexpr int runs_queue(int threads)
+{
+    return threads == kRunsSmall ? 64 : RunsQ<PREC>::DQ;
+}
+
 // LDS bytes of one work unit: field records, float64 deposit tile, queues,
-// a 16-byte control tail.
+// sums, and a control tail (RunsCtl).
+// Control words: queued particles, queued deposits, chunks passed, and
+// the two next units (item or -1, tile, particles, runs).
+enum RunsCtl { RC_QP = 1, RC_QD = 2, RC_QI = 3, RC_UNIT = 4 };
+enum RunsUnit { RU_ITEM = 0, RU_TILE, RU_PBEG, RU_PEND, RU_RLO, RU_RHI, RU_WORDS };
+constexpr int kRunsGroups = 64;        // entries of the launch's unit table
+constexpr int kRunsCtlBytes = 64 + 4 * kRunsGroups;
+enum { RC_ENDS = 16 };                 // unit table: first word
 __host__ __device__ inline size_t runs_section(size_t b) { return (b + 15) & ~(size_t)15; }
 
 template <int PREC, int KIND>
-__host__ __device__ inline size_t runs_lds_bytes(int Lf, int Ld, int nslot, int hf, size_t offs[6])
+__host__ __device__ inline size_t runs_lds_bytes(int Lf, int Ld, int nslot, int hf, int DQ, size_t offs[6])
 {
     using R = typename RealOf<PREC>::T;
-    constexpr int DQ = RunsQ<PREC>::DQ;
     size_t o = 0;
     offs[0] = o; o += runs_section((size_t)Lf * FieldRec<PREC, KIND>::FS * sizeof(R));
     offs[1] = o; o += runs_section((size_t)Ld * nslot * sizeof(double));
@@ -729,14 +842,13 @@ __host__ __device__ inline size_t runs_lds_bytes(int Lf, int Ld, int nslot, int 
     offs[3] = o; o += runs_section((size_t)DQ * sizeof(uint32_t));
     offs[4] = o; o += runs_section((size_t)DQ * (3 + nslot) * sizeof(R));
     offs[5] = o; o += 8 * sizeof(double);
-    return o + 16;
+    return o + kRunsCtlBytes;
 }
 
 // Threads per block of the run kernel.  One block per CU (the LDS tiles take
 // most of the 160 KB), so two waves per SIMD: the compiler may spend registers
 // on reads in flight.
 constexpr int kRunsThreads = 512;
-constexpr int kRunsSmall = 256;
 
 // Gas velocity at a position of the Runge-Kutta scheme: from the LDS field
 // records when the stencil lies in the tile's field tile, else from the grid.
@@ -798,63 +910,72 @@ __device__ __forceinline__ void tracer_particle(const UnitC<PREC> &U, const RunG
     for (int a = 0; a < 3; ++a) U.u[a][p] = v[a];
 }
 
-// Stage the field records of a tile (hf-cell halo) and clear its deposit tile
-// (ndep values).  Float32 form: two-deep pipeline, a record's loads are issued
-// before the previous record is stored, and the first loads overlap the
-// clearing.  The caller synchronises.
+// Grid cell of field record e of a tile (hf-cell halo).
+template <int PREC, int DIM>
+__device__ __forceinline__ long rec_cell(const UnitC<PREC> &U, const RunGeo &G, int e)
+{
+    const int Ly = G.T[1] + 2 * G.hf;
+    const int lx = e % G.fx, ly = (e / G.fx) % Ly, lz = e / G.fxy;
+    const int gx = wrap_near(G.lo[0] + lx - G.hf, U.n[0]);
+    const int gy = DIM >= 2 ? wrap_near(G.lo[1] + ly - G.hf, U.n[1]) : 0;
+    const int gz = DIM >= 3 ? wrap_near(G.lo[2] + lz - G.hf, U.n[2]) : 0;
+    return gx + (long)U.n[0] * (gy + (long)U.n[1] * gz);
+}
+
 template <int PREC, int DIM, int KIND>
-__device__ __forceinline__ void stage_unit(const UnitC<PREC> &U, const RunGeo &G, typename RealOf<PREC>::T *lds_f,
-                                           double *lds_d, int ndep)
+__device__ __forceinline__ void rec_load(const UnitC<PREC> &U, const RunGeo &G, int e,
+                                         double (&v)[FieldRec<PREC, KIND>::NC])
+{
+    const long gc = rec_cell<PREC, DIM>(U, G, e);
+#pragma unroll
+    for (int q = 0; q < FieldRec<PREC, KIND>::NC; ++q) v[q] = U.gf[q][gc];
+}
+
+// (conflict-free: consecutive threads write consecutive records)
+template <int PREC, int KIND>
+__device__ __forceinline__ void rec_store(const RunGeo &G, typename RealOf<PREC>::T *lds_f, int e,
+                                          const double (&v)[FieldRec<PREC, KIND>::NC])
 {
     using R = typename RealOf<PREC>::T;
     using FR = FieldRec<PREC, KIND>;
     constexpr int NC = FR::NC, FS = FR::FS;
-    const int Ly = G.T[1] + 2 * G.hf;
-    auto rec_cell = [&](int e) -> long {
-        int lx = e % G.fx;
-        int ly = (e / G.fx) % Ly;
-        int lz = e / G.fxy;
-        int gx = wrap_any(G.lo[0] + lx - G.hf, U.n[0]);
-        int gy = DIM >= 2 ? wrap_any(G.lo[1] + ly - G.hf, U.n[1]) : 0;
-        int gz = DIM >= 3 ? wrap_any(G.lo[2] + lz - G.hf, U.n[2]) : 0;
-        return gx + (long)U.n[0] * (gy + (long)U.n[1] * gz);
-    };
-    auto rec_load = [&](int e, double (&v)[NC]) {
-        const long gc = rec_cell(e);
+    if constexpr (FR::PLANES) {
+        float4 *p = reinterpret_cast<float4 *>(lds_f);
+        p[e] = make_float4((R)v[0], (R)v[1], (R)v[2], (R)v[3]);
+        reinterpret_cast<float2 *>(p + G.Lf)[e] = make_float2((R)v[4], (R)v[5]);
+    } else {
+        R w[FS];
 #pragma unroll
-        for (int q = 0; q < NC; ++q) v[q] = U.gf[q][gc];
-    };
-    // one 16-byte LDS store per 16 bytes of record (conflict-free:
-    // consecutive threads write consecutive records)
-    auto rec_store = [&](int e, const double (&v)[NC]) {
-        if constexpr (FR::PLANES) {
-            *reinterpret_cast<float4 *>(lds_f + FR::at(e, 0, G.Lf)) =
-                make_float4((R)v[0], (R)v[1], (R)v[2], 0.0f);
-            *reinterpret_cast<float4 *>(lds_f + FR::at(e, 3, G.Lf)) =
-                make_float4((R)v[3], (R)v[4], (R)v[5], 0.0f);
+        for (int q = 0; q < FS; ++q) w[q] = q < NC ? (R)v[q] : R(0);
+        if constexpr (PREC == PL_F32_OFFSET) {
+            *reinterpret_cast<float4 *>(lds_f + FS * e) = make_float4(w[0], w[1], w[2], w[3]);
         } else {
-            R w[FS];
 #pragma unroll
-            for (int q = 0; q < FS; ++q) w[q] = q < NC ? (R)v[q] : R(0);
-            if constexpr (PREC == PL_F32_OFFSET) {
-                *reinterpret_cast<float4 *>(lds_f + FS * e) = make_float4(w[0], w[1], w[2], w[3]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < FS / 2; ++k)
-                    *reinterpret_cast<double2 *>(lds_f + FS * e + 2 * k) = make_double2(w[2 * k], w[2 * k + 1]);
-            }
+            for (int k = 0; k < FS / 2; ++k)
+                *reinterpret_cast<double2 *>(lds_f + FS * e + 2 * k) = make_double2(w[2 * k], w[2 * k + 1]);
         }
-    };
+    }
+}
+
+// Stage the field records of a tile and clear its deposit tile (ndep values).
+// Float32 form: two-deep pipeline, a record's loads are issued before the
+// previous record is stored, and the first loads overlap the clearing.  The
+// caller synchronises.
+template <int PREC, int DIM, int KIND>
+__device__ __forceinline__ void stage_unit(const UnitC<PREC> &U, const RunGeo &G, typename RealOf<PREC>::T *lds_f,
+                                           double *lds_d, int ndep)
+{
+    constexpr int NC = FieldRec<PREC, KIND>::NC;
     if constexpr (PREC == PL_F32_OFFSET) {
         double cur[NC];
         int e = threadIdx.x;
-        if (e < G.Lf) rec_load(e, cur);
+        if (e < G.Lf) rec_load<PREC, DIM, KIND>(U, G, e, cur);
         for (int k = threadIdx.x; k < ndep; k += blockDim.x) lds_d[k] = 0.0;
         for (; e < G.Lf; e += blockDim.x) {
             double nxt[NC];
             const int en = e + (int)blockDim.x;
-            if (en < G.Lf) rec_load(en, nxt);
-            rec_store(e, cur);
+            if (en < G.Lf) rec_load<PREC, DIM, KIND>(U, G, en, nxt);
+            rec_store<PREC, KIND>(G, lds_f, e, cur);
 #pragma unroll
             for (int q = 0; q < NC; ++q) cur[q] = nxt[q];
         }
@@ -862,65 +983,68 @@ __device__ __forceinline__ void stage_unit(const UnitC<PREC> &U, const RunGeo &G
         // float64 records: one at a time (the pipeline's registers spill there)
         for (int e = threadIdx.x; e < G.Lf; e += blockDim.x) {
             double v[NC];
-            rec_load(e, v);
-            rec_store(e, v);
+            rec_load<PREC, DIM, KIND>(U, G, e, v);
+            rec_store<PREC, KIND>(G, lds_f, e, v);
         }
         for (int k = threadIdx.x; k < ndep; k += blockDim.x) lds_d[k] = 0.0;
     }
 }
 
-// Flush of a deposit tile: one float64 global atomic per touched cell and
-// channel.
+// Flush of a deposit tile, which it leaves cleared: one float64 global atomic
+// per touched cell and channel.  A cell's values are read before the previous
+// cell's atomics are issued.
 template <int PREC, int DIM, int CHS>
-__device__ __forceinline__ void flush_unit(const UnitC<PREC> &U, const RunGeo &G, const double *lds_d)
+__device__ __forceinline__ void flush_unit(const UnitC<PREC> &U, const RunGeo &G, double *lds_d)
 {
     const int Ly = G.T[1] + 4;
-    for (int e = threadIdx.x; e < G.Ld; e += blockDim.x) {
-        int lx = e % G.dx;
-        int ly = (e / G.dx) % Ly;
-        int lz = e / G.dxy;
-        int gx = wrap_any(G.lo[0] + lx - 2, U.n[0]);
-        int gy = DIM >= 2 ? wrap_any(G.lo[1] + ly - 2, U.n[1]) : 0;
-        int gz = DIM >= 3 ? wrap_any(G.lo[2] + lz - 2, U.n[2]) : 0;
-        long gc = gx + (long)U.n[0] * (gy + (long)U.n[1] * gz);
+    auto take = [&](int e, double (&v)[kMaxCh]) {
 #pragma unroll
         for (int ch = 0; ch < kMaxCh; ++ch) {
             const int so = ch_off<CHS>(U, ch, G.Ld);
-            if (so < 0) continue;
-            double val = lds_d[so + e];
-            if (val != 0.0) global_add(U.M[ch] + gc, val * U.inv_dv);
+            v[ch] = so >= 0 ? lds_d[so + e] : 0.0;
         }
+    };
+    double v[kMaxCh];
+    int e = threadIdx.x;
+    if (e < G.Ld) take(e, v);
+    for (; e < G.Ld; e += blockDim.x) {
+        double nv[kMaxCh];
+        const int en = e + (int)blockDim.x;
+        if (en < G.Ld) take(en, nv);
+        bool any = false;
+#pragma unroll
+        for (int ch = 0; ch < kMaxCh; ++ch) {
+            const int so = ch_off<CHS>(U, ch, G.Ld);
+            if (so >= 0) lds_d[so + e] = 0.0;
+            any = any || v[ch] != 0.0;
+        }
+        if (any) {
+            const int lx = e % G.dx, ly = (e / G.dx) % Ly, lz = e / G.dxy;
+            const int gx = wrap_near(G.lo[0] + lx - 2, U.n[0]);
+            const int gy = DIM >= 2 ? wrap_near(G.lo[1] + ly - 2, U.n[1]) : 0;
+            const int gz = DIM >= 3 ? wrap_near(G.lo[2] + lz - 2, U.n[2]) : 0;
+            const long gc = gx + (long)U.n[0] * (gy + (long)U.n[1] * gz);
+#pragma unroll
+            for (int ch = 0; ch < kMaxCh; ++ch) {
+                const int so = ch_off<CHS>(U, ch, G.Ld);
+                if (so >= 0) global_add(U.M[ch] + gc, v[ch] * U.inv_dv);
+            }
+        }
+#pragma unroll
+        for (int ch = 0; ch < kMaxCh; ++ch) v[ch] = nv[ch];
     }
 }
 
-// One work unit of the run kernel (a piece of tile t of item I): stage the
-// tile's field records (and clear its deposit tile), advance the piece's
-// runs, and flush the deposits; passive tracers are advanced one particle at
-// a time from the same field records.  The next unit is claimed into ctl[0]
-// before the flush (pre = true).
-template <int PREC, int SHAPE, int DIM, int KIND, int HF, int TS, int CHS>
-__device__ __forceinline__ void runs_unit(const ItemDesc &I, int t, int piece, int npieces, unsigned flags,
-                                          int lds_bytes, unsigned char *smem_raw, unsigned *counter, bool &pre,
-                                          int &err)
+// Geometry of tile t of an item, and a unit's LDS sections.
+template <int DIM, int HF, int TS>
+__device__ __forceinline__ void unit_geo(const ItemDesc &I, int t, unsigned flags, RunGeo &G)
 {
-    using R = typename RealOf<PREC>::T;
-    using FR = FieldRec<PREC, KIND>;
-    constexpr int NC = FR::NC, FS = FR::FS;
-    constexpr int KR = PREC == PL_F32_OFFSET ? 4 : 2;
-    int *ctl = reinterpret_cast<int *>(smem_raw + lds_bytes - 16);
-    const bool do_sums = flags & SF_SUMS;
-    RunGeo G;
     G.T[0] = TS ? ts_dim(TS, 0) : I.tile[0];
     G.T[1] = TS ? ts_dim(TS, 1) : I.tile[1];
     G.T[2] = TS ? ts_dim(TS, 2) : I.tile[2];
-    {
-        int tx = t % I.ntile[0];
-        int ty = (t / I.ntile[0]) % I.ntile[1];
-        int tz = t / (I.ntile[0] * I.ntile[1]);
-        G.lo[0] = tx * G.T[0];
-        G.lo[1] = ty * G.T[1];
-        G.lo[2] = tz * G.T[2];
-    }
+    G.lo[0] = (t % I.ntile[0]) * G.T[0];
+    G.lo[1] = ((t / I.ntile[0]) % I.ntile[1]) * G.T[1];
+    G.lo[2] = (t / (I.ntile[0] * I.ntile[1])) * G.T[2];
     G.hf = HF ? HF : ((flags & SF_FHALO2) ? 2 : 1);
     G.fx = G.T[0] + 2 * G.hf;
     G.fxy = G.fx * (G.T[1] + 2 * G.hf);
@@ -928,182 +1052,277 @@ __device__ __forceinline__ void runs_unit(const ItemDesc &I, int t, int piece, i
     G.dx = G.T[0] + 4;
     G.dxy = G.dx * (G.T[1] + 4);
     G.Ld = G.dxy * (DIM >= 3 ? G.T[2] + 4 : 1);
-    const int pbeg = min(max(I.tile_start[t], 0), I.np);
-    const int pend = min(max(I.tile_start[t + 1], pbeg), I.np);
-    const int nruns = min(max(I.runs[I.np + t], 0), pend - pbeg);
-    const int r_lo = (int)((long long)nruns * piece / npieces);
-    const int r_hi = (int)((long long)nruns * (piece + 1) / npieces);
-    if (r_hi <= r_lo) return;        // uniform: the whole block skips an empty piece
+}
 
-    UnitC<PREC> U;
-    load_unit<PREC>(I, U, G.Ld);
-    const int nslot = I.nslot;
+template <int PREC, int KIND>
+__device__ __forceinline__ void unit_shared(const RunGeo &G, int nslot, unsigned char *smem_raw, int lds_bytes,
+                                            unsigned flags, RunShared<PREC> &S)
+{
+    using R = typename RealOf<PREC>::T;
     size_t offs[6];
-    runs_lds_bytes<PREC, KIND>(G.Lf, G.Ld, nslot, G.hf, offs);
-    RunShared<PREC> S;
-    R *lds_f = reinterpret_cast<R *>(smem_raw + offs[0]);
-    S.lds_f = lds_f;
+    const int dq = runs_queue<PREC>((int)blockDim.x);
+    runs_lds_bytes<PREC, KIND>(G.Lf, G.Ld, nslot, G.hf, dq, offs);
+    S.narrow = PREC == PL_F32_OFFSET && (flags & SF_NARROW);
+    S.lds_f = reinterpret_cast<R *>(smem_raw + offs[0]);
     S.lds_d = reinterpret_cast<double *>(smem_raw + offs[1]);
     S.gq = reinterpret_cast<int *>(smem_raw + offs[2]);
     S.dq_c = reinterpret_cast<uint32_t *>(smem_raw + offs[3]);
     S.dq_d = reinterpret_cast<R *>(smem_raw + offs[4]);
-    S.dq_mu = S.dq_d + 3 * RunsQ<PREC>::DQ;
-    S.dq = RunsQ<PREC>::DQ;
-    S.ctl = ctl;
+    S.dq_mu = S.dq_d + 3 * dq;
+    S.dq = dq;
+    S.ctl = reinterpret_cast<int *>(smem_raw + lds_bytes - kRunsCtlBytes);
     S.sums = reinterpret_cast<double *>(smem_raw + offs[5]);
     S.smask = 0;
+}
 
-    stage_unit<PREC, DIM, KIND>(U, G, lds_f, S.lds_d, G.Ld * nslot);
-    {
-        if (threadIdx.x == 0) {
-            ctl[1] = 0;
-            ctl[2] = 0;
+__device__ __forceinline__ void run_entry(int e, int pbeg, int pend, int &rs, int &rl)
+{
+    rs = min(max(e >> 2, pbeg), pend - 1);
+    rl = min((e & 3) + 1, pend - rs);
+}
+
+// The runs [r_lo, r_hi) of a unit, one per thread at a time (r = r_lo + tid,
+// + blockDim, ...; entry: the first one's), each cut into batches of KR.  A
+// batch is loaded when it starts: with the next batch in flight the float32
+// kernel needed all its registers (1.38 ms on the 128^3 box with 2^24
+// particles against 1.32 before the units were pipelined).  A long piece is taken in segments of 4 * blockDim
+// runs with the LDS queues drained between segments when half full; every piece
+// ends with a drain.  Segment count, drain decisions and barriers are uniform
+// across the block.  The last wave (it has the fewest runs) calls last() when it
+// is through, before the block meets.  Pieces of one tile on
+// several CUs meet only in the global atomics of the flush.
+template <int PREC, int SHAPE, int DIM, int KIND, int CHS, int KR, class Ahead, class Last>
+__device__ __forceinline__ void unit_runs(const UnitC<PREC> &U, const RunGeo &G, const RunShared<PREC> &S,
+                                          gptr<const int32_t> runs, int pbeg, int pend, int r_lo, int r_hi, int entry,
+                                          bool do_sums, int &err, Ahead ahead, Last last)
+{
+    const int bd = (int)blockDim.x, seg = 4 * bd;
+    for (int s0 = r_lo; s0 < r_hi; s0 += seg) {
+        const int s1 = min(r_hi, s0 + seg);
+        int r = s0 + (int)threadIdx.x, b = 0, rs = 0, rl = 0;
+        if (r < s1) run_entry(s0 > r_lo ? runs[r] : entry, pbeg, pend, rs, rl);
+        while (r < s1) {
+            BatchRaw<PREC, DIM, KR> now;
+            fetch_batch<PREC, DIM, KR>(U, rs + b, min(KR, rl - b), now);
+            const int pi[KR] = {now.start};
+            run_batch<PREC, SHAPE, DIM, KIND, CHS, KR, true, false>(U, G, S, now, pi, do_sums, err, []() {});
+            b += KR;
+            if (b >= rl) {
+                r += bd;
+                b = 0;
+                if (r < s1) run_entry(runs[r], pbeg, pend, rs, rl);
+            }
         }
-        if (threadIdx.x < 8) S.sums[threadIdx.x] = 0.0;
+        const bool end = s1 >= r_hi;
+        if (end) ahead();
+        if (end && (int)threadIdx.x >= bd - 64) last();
         __syncthreads();
+        const int qg = S.ctl[RC_QP], qd = S.ctl[RC_QD];
+        if (end || 2 * qg > gq_cap(G.hf) || 2 * qd > S.dq) {
+            drain_deposits<PREC, SHAPE, DIM, CHS>(U, G, S, min(qd, S.dq));
+            const int ng = min(qg, gq_cap(G.hf));
+            if (ng > 0) {
+                for (int i = threadIdx.x; i < ng; i += blockDim.x)
+                    particle_single<PREC, SHAPE, DIM, KIND, CHS>(U, G, S, S.gq[i], do_sums, err);
+                // (rare: the loads again rather than their registers held through the gathers)
+                if (end) ahead();
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                S.ctl[RC_QP] = 0;
+                S.ctl[RC_QD] = 0;
+            }
+        }
+        if (!end) __syncthreads();      // all threads hold the same counts before anyone queues again
     }
+}
 
-    // this thread's runs r = r_lo + tid, + blockDim, ..., each cut into
-    // batches of KR; the next batch is fetched before the current one runs.
-    // A long piece is taken in segments of 4 * blockDim runs with the LDS
-    // queues drained between segments when half full; every piece ends
-    // with a drain.  Segment count, drain decisions and barriers are
-    // uniform across the block.  Pieces of one tile on several CUs meet
-    // only in the global atomics of the flush.
+// One work unit of the kernel that takes every species kind (a piece of tile t
+// of item I): stage the tile's field records (and clear its deposit tile),
+// advance the piece's runs, and flush the deposits; passive tracers are
+// advanced one particle at a time from the same field records.
+template <int PREC, int SHAPE, int DIM, int KIND, int HF, int TS, int CHS>
+__device__ __forceinline__ void runs_unit(const ItemDesc &I, int t, int pbeg, int pend, int r_lo, int r_hi,
+                                          unsigned flags, int lds_bytes, unsigned char *smem_raw, int &err)
+{
+    constexpr int KR = PREC == PL_F32_OFFSET ? 4 : 2;
+    const bool do_sums = flags & SF_SUMS;
+    RunGeo G;
+    unit_geo<DIM, HF, TS>(I, t, flags, G);
+    UnitC<PREC> U;
+    load_unit<PREC>(I, U, G.Ld);
+    RunShared<PREC> S;
+    unit_shared<PREC, KIND>(G, I.nslot, smem_raw, lds_bytes, flags, S);
+    stage_unit<PREC, DIM, KIND>(U, G, const_cast<typename RealOf<PREC>::T *>(S.lds_f), S.lds_d, G.Ld * I.nslot);
+    if (threadIdx.x == 0) {
+        S.ctl[RC_QP] = 0;
+        S.ctl[RC_QD] = 0;
+    }
+    if (threadIdx.x < 8) S.sums[threadIdx.x] = 0.0;
+    __syncthreads();
     const gptr<const int32_t> runs = (gptr<const int32_t>)(I.runs + pbeg);
-    auto run_span = [&](int r, int &rs, int &rl) {
-        const int e = runs[r];
-        rs = min(max(e >> 2, pbeg), pend - 1);
-        rl = min((e & 3) + 1, pend - rs);
-    };
     if constexpr (KIND == PL_TRACER) {
         // passive tracers deposit nothing: thread k advances the particles of
         // runs r_lo + k, + blockDim, ... on their own
         for (int r = r_lo + (int)threadIdx.x; r < r_hi; r += (int)blockDim.x) {
             int rs = 0, rl = 0;
-            run_span(r, rs, rl);
+            run_entry(runs[r], pbeg, pend, rs, rl);
             for (int q = 0; q < rl; ++q) tracer_particle<PREC, SHAPE, DIM>(U, G, S.lds_f, rs + q, err);
         }
     } else {
-        const int seg = 4 * (int)blockDim.x;
-        for (int s0 = r_lo; s0 < r_hi; s0 += seg) {
-            const int s1 = min(r_hi, s0 + seg);
-            int r = s0 + (int)threadIdx.x, b = 0, rs = 0, rl = 0;
-            bool have = r < s1;
-            BatchRaw<PREC, DIM, KR> cur;
-            if (have) {
-                run_span(r, rs, rl);
-                fetch_batch<PREC, DIM, KR>(U, rs, min(KR, rl), cur);
-            }
-            while (have) {
-                int nr = r, nb = b + KR, nrs = rs, nrl = rl;
-                if (nb >= rl) {
-                    nr = r + blockDim.x;
-                    nb = 0;
-                    if (nr < s1) run_span(nr, nrs, nrl);
-                }
-                const bool nhave = nr < s1;
-                BatchRaw<PREC, DIM, KR> nxt;
-                if (nhave) fetch_batch<PREC, DIM, KR>(U, nrs + nb, min(KR, nrl - nb), nxt);
-                const int pi[KR] = {cur.start};
-                run_batch<PREC, SHAPE, DIM, KIND, CHS, KR, true, false>(U, G, S, cur, pi, do_sums, err);
-                cur = nxt;
-                r = nr;
-                b = nb;
-                rs = nrs;
-                rl = nrl;
-                have = nhave;
-            }
-            __syncthreads();
-            const int qg = ctl[1], qd = ctl[2];
-            __syncthreads();          // all threads hold the same counts before anyone queues again
-            if (s1 >= r_hi || 2 * qg > gq_cap(G.hf) || 2 * qd > RunsQ<PREC>::DQ) {
-                const int ng = min(qg, gq_cap(G.hf));
-                for (int i = threadIdx.x; i < ng; i += blockDim.x)
-                    particle_single<PREC, SHAPE, DIM, KIND, CHS>(U, G, S, S.gq[i], do_sums, err);
-                const int nd = min(qd, RunsQ<PREC>::DQ);
-                for (int i = threadIdx.x; i < nd; i += blockDim.x) record_deposit<PREC, SHAPE, DIM, CHS>(U, G, S, i);
-                __syncthreads();
-                if (threadIdx.x == 0) {
-                    ctl[1] = 0;
-                    ctl[2] = 0;
-                }
-                __syncthreads();
-            }
-        }
-
-        // flush the deposit tile: one float64 global atomic per touched cell
-        // and channel.  The next unit is claimed first, so the claim's
-        // round trip overlaps the flush.
-        __syncthreads();
-        if (threadIdx.x == 0) ctl[0] = (int)atomicAdd(counter + (blockIdx.x + ctl[3]) % kQueues, 1u);
-        pre = true;
+        const int entry = r_lo + (int)threadIdx.x < r_hi ? runs[r_lo + (int)threadIdx.x] : 0;
+        unit_runs<PREC, SHAPE, DIM, KIND, CHS, KR>(U, G, S, runs, pbeg, pend, r_lo, r_hi, entry, do_sums, err, []() {}, []() {});
         if (do_sums && threadIdx.x < 8 && S.sums[threadIdx.x] != 0.0) global_add(I.psum + threadIdx.x, S.sums[threadIdx.x]);
         flush_unit<PREC, DIM, CHS>(U, G, S.lds_d);
     }
 }
 
-// Claim of the run kernels' next work unit.  The launch's unit slots are cut
-// into kQueues contiguous chunks (neighbouring tiles share a chunk), each with
-// its own counter; block b starts on chunk b % kQueues and moves to the next
-// chunk when its own is exhausted (qi chunks passed, mirrored in ctl[3] for
-// the claim issued before a flush).  Blocks are dispatched to the XCDs in
-// turn, so the blocks of one XCD mostly share a chunk and find its field
-// records in their L2; results do not depend on that placement.  The claim
-// goes into ctl[0] (or was issued before the last flush, pre): false when
-// every chunk is exhausted; otherwise the unit's item, tile and piece, with
-// t = -1 for an empty or skipped slot.  Item k of the launch owns slots
-// [unit_begin + k * kRunsSplit, + nunits + kRunsSplit); the sort lists an
-// item's units largest first as (tile, piece | npieces << 16).
+// Work units of a launch.  Item k has as many units as its sort listed, largest
+// first as (tile, piece | npieces << 16); the launch numbers the units of all
+// its items in order.  Every block adds the counts up for itself: entry k of
+// its unit table is the end of the units of the k-th group of ceil(nitems /
+// kRunsGroups) items.  An item whose tables do not cover its particles (tile
+// offsets from 0 to np, at least one unit when np > 0: never sorted, or its
+// count changed since) is latched and left alone.
+__device__ __forceinline__ int item_units(const ItemDesc &I, bool &stale)
+{
+    const int nu = min(max(I.runs[runs_count_at(I.np, I.ntiles)], 0), I.nunits > 0 ? I.nunits + kRunsSplit : 0);
+    stale = I.tile_start[0] != 0 || I.tile_start[I.ntiles] != I.np || (I.np > 0 && nu == 0);
+    return stale ? 0 : nu;
+}
+
+__device__ __forceinline__ void runs_units(const ItemDesc *__restrict__ items, int nitems, int *errflags, int *ctl)
+{
+    if (threadIdx.x < kRunsGroups) {
+        const int per = (nitems + kRunsGroups - 1) / kRunsGroups, k0 = (int)threadIdx.x * per;
+        int n = 0;
+        bool any = false;
+        for (int k = k0; k < min(nitems, k0 + per); ++k) {
+            bool stale;
+            n += item_units(items[k], stale);
+            any = any || stale;
+        }
+        if (any) atomicOr(errflags, (int)ERR_UNSORTED);
+        for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(n, off, 64);
+            if ((int)threadIdx.x >= off) n += y;
+        }
+        ctl[RC_ENDS + threadIdx.x] = n;
+    }
+}
+static_assert(kRunsGroups == 64, "the unit table is one wave's scan");
+
+// Claims.  The launch's units are cut into kQueues contiguous chunks
+// (neighbouring tiles share a chunk), each with its own counter; block b starts
+// on chunk b % kQueues and moves to the next chunk with units left when its own
+// is exhausted (qi chunks passed, mirrored in ctl[RC_QI]).  Blocks are
+// dispatched to the XCDs in turn, so the blocks of one XCD mostly share a chunk
+// and find its field records in their L2; results do not depend on that
+// placement.  With fewer units than blocks every unit is claimed in `sub` parts
+// of its runs (of at least kRunsMinSub), so a small box fills the chip too: 32^3
+// cells with 2.6e5 particles have 64 tiles for 256 CUs (67 us per launch whole,
+// 56 us in parts: their flushes add to the same cells at once).
+constexpr int kRunsMinSub = 128;
 __device__ __forceinline__ int queue_lo(int q, int total) { return (int)((long long)total * q / kQueues); }
 
-__device__ __forceinline__ bool runs_claim(const ItemDesc *__restrict__ items, int nitems, int total_units,
-                                           unsigned *counter, int *errflags, int *ctl, bool &pre, int &qi, int &iti,
-                                           int &t, int &piece, int &npieces)
+__device__ __forceinline__ int runs_sub(int total)
 {
-    __syncthreads();
-    if (!pre && threadIdx.x == 0 && qi < kQueues)
-        ctl[0] = (int)atomicAdd(counter + (blockIdx.x + qi) % kQueues, 1u);
-    __syncthreads();
-    pre = false;
-    t = -1;
-    if (qi >= kQueues) return false;
-    const int q = (int)((blockIdx.x + qi) % kQueues);
-    const int qlo = queue_lo(q, total_units), qhi = queue_lo(q + 1, total_units);
-    const int g = qlo + __builtin_amdgcn_readfirstlane(ctl[0]);
-    if (g >= qhi) {
-        // this chunk is exhausted: the next one
-        ++qi;
-        if (threadIdx.x == 0) ctl[3] = qi;
-        return true;                                          // uniform
-    }
-    iti = 0;
-    while (iti + 1 < nitems && items[iti + 1].unit_begin + (iti + 1) * kRunsSplit <= g) ++iti;
-    const ItemDesc &I = items[iti];
-    const int ubeg = I.unit_begin + iti * kRunsSplit;
-    const int ucap = I.nunits + kRunsSplit;
-    const int local = g - ubeg;
-    const int nu = min(max(I.runs[runs_count_at(I.np, I.ntiles)], 0), I.nunits > 0 ? ucap : 0);
-    // the sort's tables must cover the item's particles: tile offsets from
-    // 0 to np and at least one unit when np > 0; otherwise the item was
-    // never sorted (or its count changed since): latch it, leave it alone
-    const bool stale = I.tile_start[0] != 0 || I.tile_start[I.ntiles] != I.np || (I.np > 0 && nu == 0);
-    if (stale || local >= nu) {
-        // the rest of this item's slots in the chunk are empty: move the
-        // chunk's counter past them
-        if (threadIdx.x == 0) {
-            atomicMax(counter + q, (unsigned)(min(ubeg + ucap, qhi) - qlo));
-            if (stale) atomicOr(errflags, (int)ERR_UNSORTED);
+    return total > 0 && total < (int)gridDim.x ? (int)gridDim.x / total : 1;
+}
+
+// The next claim of the block (by one whole wave, uniformly): a part of a unit
+// in [0, parts), or -1 when every chunk is exhausted.  A chunk found exhausted
+// costs one round trip; the counters of the others are then read together.
+__device__ __forceinline__ int runs_take(int parts, unsigned *counter, int &qi)
+{
+    const int lane = (int)threadIdx.x & 63, home = (int)(blockIdx.x % kQueues);
+    while (qi < kQueues) {
+        const int q = (home + qi) % kQueues, qlo = queue_lo(q, parts), qhi = queue_lo(q + 1, parts);
+        if (qhi > qlo) {
+            int n = 0;
+            if (lane == 0) n = (int)atomicAdd(counter + q, 1u);
+            const int g = qlo + __builtin_amdgcn_readfirstlane(n);
+            if (g < qhi) return g;
         }
-        return true;                                          // uniform
+        // lane k: whether the chunk after k passed ones has units left
+        const int p = (home + lane) % kQueues;
+        unsigned seen = ~0u;
+        if (lane < kQueues) seen = __hip_atomic_load(counter + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool left = lane < kQueues && lane > qi && seen < (unsigned)(queue_lo(p + 1, parts) - queue_lo(p, parts));
+        const uint64_t m = __ballot(left);
+        qi = m ? (int)__builtin_ctzll(m) : kQueues;
     }
+    return -1;
+}
+
+// The runs of claim g (one whole wave, uniformly): item, tile, particles and
+// runs of one unit's part; false when it has none (or the unit list is damaged).
+__device__ __forceinline__ bool runs_lookup(const ItemDesc *__restrict__ items, int nitems, const int *ctl, int g, int sub,
+                                            int *u)
+{
+    int s = 0;
+    if (sub > 1) {
+        s = g % sub;
+        g /= sub;
+    }
+    const int lane = (int)threadIdx.x & 63, per = (nitems + kRunsGroups - 1) / kRunsGroups;
+    const int end = ctl[RC_ENDS + lane];
+    const int grp = min((int)__popcll(__ballot(end <= g)), kRunsGroups - 1);
+    int local = g - (grp > 0 ? __builtin_amdgcn_readlane(end, grp - 1) : 0), k = grp * per;
+    const int kend = min(nitems, k + per);
+    for (; k < kend - 1; ++k) {
+        bool stale;
+        const int n = item_units(items[k], stale);
+        if (local < n) break;
+        local -= n;
+    }
+    if (k >= kend) return false;
+    const ItemDesc &I = items[k];
     const int32_t *unit = I.runs + runs_units_at(I.np, I.ntiles) + 2 * local;
-    const int tt = unit[0];
-    piece = unit[1] & 0xffff;
-    npieces = unit[1] >> 16;
-    if ((unsigned)tt >= (unsigned)I.ntiles || npieces < 1 || piece >= npieces) return true;      // uniform
-    t = tt;
-    return true;
+    const int t = __builtin_amdgcn_readfirstlane(unit[0]), w = __builtin_amdgcn_readfirstlane(unit[1]);
+    const int piece = w & 0xffff, npieces = w >> 16;
+    if ((unsigned)t >= (unsigned)I.ntiles || npieces < 1 || piece >= npieces) return false;
+    const int beg = I.tile_start[t], last = I.tile_start[t + 1], cnt = I.runs[I.np + t];
+    const int pbeg = min(max(__builtin_amdgcn_readfirstlane(beg), 0), I.np);
+    const int pend = min(max(__builtin_amdgcn_readfirstlane(last), pbeg), I.np);
+    const int nruns = min(max(__builtin_amdgcn_readfirstlane(cnt), 0), pend - pbeg);
+    int lo = 0, hi = nruns;
+    if (npieces > 1) {
+        lo = (int)((long long)nruns * piece / npieces);
+        hi = (int)((long long)nruns * (piece + 1) / npieces);
+    }
+    if (sub > 1) {
+        // parts of at least kRunsMinSub runs, the last ones empty
+        const int n = hi - lo, parts = max(1, min(sub, n / kRunsMinSub));
+        if (s >= parts) return false;
+        hi = lo + (int)((long long)n * (s + 1) / parts);
+        lo = lo + (int)((long long)n * s / parts);
+    }
+    u[RU_ITEM] = k;
+    u[RU_TILE] = t;
+    u[RU_PBEG] = pbeg;
+    u[RU_PEND] = pend;
+    u[RU_RLO] = lo;
+    u[RU_RHI] = hi;
+    return hi > lo;
+}
+
+// The next unit with runs, claimed and looked up by one whole wave into a
+// unit's control words (item -1: none left).
+__device__ __forceinline__ void runs_next(const ItemDesc *__restrict__ items, int nitems, unsigned *counter, int *ctl,
+                                          int *unit)
+{
+    const int total = __builtin_amdgcn_readfirstlane(ctl[RC_ENDS + kRunsGroups - 1]), sub = runs_sub(total);
+    int qi = __builtin_amdgcn_readfirstlane(ctl[RC_QI]);
+    for (;;) {
+        const int g = runs_take(total * sub, counter, qi);
+        if (g < 0) {
+            unit[RU_ITEM] = -1;
+            break;
+        }
+        if (runs_lookup(items, nitems, ctl, g, sub, unit)) break;
+    }
+    ctl[RC_QI] = qi;
 }
 
 // The last block to finish resets the chunk counters for the next launch.
@@ -1137,17 +1356,114 @@ template <int PREC, int SHAPE, int DIM, int KIND, int HF, int TS, int CHS, int N
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_runs(const ItemDesc *__restrict__ items, int nitems, int total_units,
                                              unsigned *counter, int *errflags, unsigned flags, int lds_bytes)
 {
+    using R = typename RealOf<PREC>::T;
+    constexpr int KR = PREC == PL_F32_OFFSET ? 4 : 2;
+    constexpr int NC = FieldRec<PREC, KIND>::NC;
+    // records of the next unit that a thread loads ahead of the flush
+    constexpr int NPRE = 2;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    int *ctl = reinterpret_cast<int *>(smem_raw + lds_bytes - 16);
+    int *ctl = reinterpret_cast<int *>(smem_raw + lds_bytes - kRunsCtlBytes);
+    const bool do_sums = flags & SF_SUMS;
     int err = 0;
-    bool pre = false;                      // uniform: ctl[0] already holds the next claim
-    int qi = 0;                            // uniform: chunks passed
-    if (threadIdx.x == 0) ctl[3] = 0;
-    int iti = 0, t = -1, piece = 0, npieces = 1;
-    while (runs_claim(items, nitems, total_units, counter, errflags, ctl, pre, qi, iti, t, piece, npieces)) {
-        if (t < 0) continue;                                  // uniform
-        runs_unit<PREC, SHAPE, DIM, KIND, HF, TS, CHS>(items[iti], t, piece, npieces, flags, lds_bytes, smem_raw,
-                                                      counter, pre, err);
+    if (threadIdx.x == 0) {
+        ctl[RC_QP] = 0;
+        ctl[RC_QD] = 0;
+        ctl[RC_QI] = 0;
+    }
+    runs_units(items, nitems, errflags, ctl);
+    __syncthreads();
+    if (threadIdx.x < 64) runs_next(items, nitems, counter, ctl, ctl + RC_UNIT);
+    __syncthreads();
+    // Unit by unit, two known ahead (one lane looks the second up while the
+    // others work).  The loads of the next unit's fields go out before this
+    // unit's flush and come back before its atomics, and the LDS has them right
+    // after it.  What it measured, share of the waves' time on the 128^3 box
+    // with 2^24 particles (float32, rho J F): staging 9.4 to 3 %, claims 4.4 to 0
+    // %, the queue's drain and its wait 7.0 to 5 %, flush 10.6 % as before (bound
+    // by the round trips of its device-scope atomics); with the smaller records
+    // and no batch prefetch 1.38 to 1.15 ms per launch.
+    struct Ref {
+        int iti, t, pbeg, pend, r_lo, r_hi;
+    };
+    auto known = [&](int slot) -> Ref {
+        const int *w = ctl + RC_UNIT + RU_WORDS * slot;
+        auto word = [&](int k) -> int { return __builtin_amdgcn_readfirstlane(w[k]); };
+        return Ref{word(RU_ITEM), word(RU_TILE), word(RU_PBEG), word(RU_PEND), word(RU_RLO), word(RU_RHI)};
+    };
+    Ref cur = known(0);
+    if (cur.iti >= 0) {
+        RunGeo G;
+        UnitC<PREC> U;
+        RunShared<PREC> S;
+        const int tid = (int)threadIdx.x, bd = (int)blockDim.x;
+        unit_geo<DIM, HF, TS>(items[cur.iti], cur.t, flags, G);
+        load_unit<PREC>(items[cur.iti], U, G.Ld);
+        unit_shared<PREC, KIND>(G, items[cur.iti].nslot, smem_raw, lds_bytes, flags, S);
+        stage_unit<PREC, DIM, KIND>(U, G, const_cast<R *>(S.lds_f), S.lds_d, G.Ld * items[cur.iti].nslot);
+        if (tid < 8) S.sums[tid] = 0.0;
+        if (tid >= bd - 64) runs_next(items, nitems, counter, ctl, ctl + RC_UNIT + RU_WORDS);
+        auto first_entry = [&](const Ref &u) -> int {
+            return u.iti >= 0 && u.r_lo + tid < u.r_hi
+                       ? ((gptr<const int32_t>)(items[u.iti].runs + u.pbeg))[u.r_lo + tid] : 0;
+        };
+        int entry = first_entry(cur);
+        __syncthreads();
+        Ref nxt = known(1);
+        for (int slot = 0;; slot ^= 1) {
+            const gptr<const int32_t> runs = (gptr<const int32_t>)(items[cur.iti].runs + cur.pbeg);
+            const int entry_n = first_entry(nxt);
+            RunGeo Gn = G;
+            double pre[NPRE][NC];
+            auto ahead = [&]() {
+                if (nxt.iti < 0) return;                         // uniform
+                const ItemDesc &In = items[nxt.iti];
+                UnitC<PREC> V;           // (what the field loads need of it)
+                for (int a = 0; a < 3; ++a) {
+                    V.n[a] = In.n[a];
+                    V.gf[a] = (gptr<const double>)(KIND == PL_LORENTZ ? In.E[a] : In.vg[a]);
+                    V.gf[3 + a] = (gptr<const double>)(KIND == PL_LORENTZ ? In.B[a] : nullptr);
+                }
+                unit_geo<DIM, HF, TS>(In, nxt.t, flags, Gn);
+#pragma unroll
+                for (int k = 0; k < NPRE; ++k)
+                    if (tid + k * bd < Gn.Lf) rec_load<PREC, DIM, KIND>(V, Gn, tid + k * bd, pre[k]);
+            };
+            unit_runs<PREC, SHAPE, DIM, KIND, CHS, KR>(
+                U, G, S, runs, cur.pbeg, cur.pend, cur.r_lo, cur.r_hi, entry, do_sums, err, ahead, [&]() {
+                    runs_next(items, nitems, counter, ctl, ctl + RC_UNIT + RU_WORDS * slot);
+                });
+            if (do_sums && tid < 8) {
+                const double v = S.sums[tid];
+                S.sums[tid] = 0.0;
+                if (v != 0.0) global_add(items[cur.iti].psum + tid, v);
+            }
+            flush_unit<PREC, DIM, CHS>(U, G, S.lds_d);
+            if (nxt.iti < 0) break;                              // uniform
+            if (nxt.iti != cur.iti) {
+                load_unit<PREC>(items[nxt.iti], U, Gn.Ld);
+                if (TS == 0) {
+                    // another item's tile may lay the sections out otherwise
+                    __syncthreads();
+                    unit_shared<PREC, KIND>(Gn, items[nxt.iti].nslot, smem_raw, lds_bytes, flags, S);
+                    for (int k = tid; k < Gn.Ld * items[nxt.iti].nslot; k += bd) S.lds_d[k] = 0.0;
+                    if (tid < 8) S.sums[tid] = 0.0;
+                }
+                    }
+            G = Gn;
+            R *lds_f = const_cast<R *>(S.lds_f);
+#pragma unroll
+            for (int k = 0; k < NPRE; ++k)
+                if (tid + k * bd < G.Lf) rec_store<PREC, KIND>(G, lds_f, tid + k * bd, pre[k]);
+            for (int e = tid + NPRE * bd; e < G.Lf; e += bd) {
+                double v[NC];
+                rec_load<PREC, DIM, KIND>(U, G, e, v);
+                rec_store<PREC, KIND>(G, lds_f, e, v);
+            }
+            cur = nxt;
+            entry = entry_n;
+            nxt = known(slot);
+            __syncthreads();
+        }
     }
     runs_latch(err, errflags);
     release_queues(counter);
@@ -1162,25 +1478,25 @@ __global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2,
                                              unsigned *counter, int *errflags, unsigned flags, int lds_bytes)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    int *ctl = reinterpret_cast<int *>(smem_raw + lds_bytes - 16);
+    int *ctl = reinterpret_cast<int *>(smem_raw + lds_bytes - kRunsCtlBytes);
     int err = 0;
-    bool pre = false;
-    int qi = 0;
-    if (threadIdx.x == 0) ctl[3] = 0;
-    int iti = 0, t = -1, piece = 0, npieces = 1;
-    while (runs_claim(items, nitems, total_units, counter, errflags, ctl, pre, qi, iti, t, piece, npieces)) {
-        if (t < 0) continue;                                  // uniform
-        const ItemDesc &I = items[iti];
+    if (threadIdx.x == 0) ctl[RC_QI] = 0;
+    runs_units(items, nitems, errflags, ctl);
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x < 64) runs_next(items, nitems, counter, ctl, ctl + RC_UNIT);
+        __syncthreads();
+        auto word = [&](int k) -> int { return __builtin_amdgcn_readfirstlane(ctl[RC_UNIT + k]); };
+        if (word(RU_ITEM) < 0) break;                         // uniform
+        const ItemDesc &I = items[word(RU_ITEM)];
+        const int t = word(RU_TILE), pbeg = word(RU_PBEG), pend = word(RU_PEND), lo = word(RU_RLO), hi = word(RU_RHI);
         const int kind = __builtin_amdgcn_readfirstlane(I.kind);
         if (kind == PL_LORENTZ)
-            runs_unit<PREC, SHAPE, DIM, PL_LORENTZ, HF, TS, CHL>(I, t, piece, npieces, flags, lds_bytes, smem_raw,
-                                                                 counter, pre, err);
+            runs_unit<PREC, SHAPE, DIM, PL_LORENTZ, HF, TS, CHL>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err);
         else if (kind == PL_DUST)
-            runs_unit<PREC, SHAPE, DIM, PL_DUST, HF, TS, CHD>(I, t, piece, npieces, flags, lds_bytes, smem_raw,
-                                                              counter, pre, err);
+            runs_unit<PREC, SHAPE, DIM, PL_DUST, HF, TS, CHD>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err);
         else
-            runs_unit<PREC, SHAPE, DIM, PL_TRACER, HF, TS, 0>(I, t, piece, npieces, flags, lds_bytes, smem_raw,
-                                                              counter, pre, err);
+            runs_unit<PREC, SHAPE, DIM, PL_TRACER, HF, TS, 0>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err);
     }
     runs_latch(err, errflags);
     release_queues(counter);
@@ -1201,12 +1517,12 @@ static StepKernel pick_runs(int shape, int dim, int kind, int hf, int ts, int ch
 #define PL_RF(HF_, TS_) PL_R(PL_TSC, 3, PL_LORENTZ, HF_, TS_, 1) PL_R(PL_TSC, 3, PL_DUST, HF_, TS_, 2)
     PL_RG(PL_TSC, 3) PL_RG(PL_TSC, 2) PL_RG(PL_CIC, 3) PL_RG(PL_CIC, 2)
     PL_RF(1, 1) PL_RF(2, 1) PL_RF(1, 2) PL_RF(2, 2)
-    // every charged channel (on 8^3 tiles only a one-cell field halo leaves the LDS for it)
     PL_RN(PL_TSC, 2, PL_LORENTZ, 0, 0, 0, kRunsSmall) PL_RN(PL_TSC, 2, PL_DUST, 0, 0, 0, kRunsSmall)
     PL_RN(PL_CIC, 2, PL_LORENTZ, 0, 0, 0, kRunsSmall) PL_RN(PL_CIC, 2, PL_DUST, 0, 0, 0, kRunsSmall)
     PL_RN(PL_TSC, 2, PL_LORENTZ, 2, 3, 1, kRunsSmall) PL_RN(PL_TSC, 2, PL_LORENTZ, 2, 3, 3, kRunsSmall)
     PL_RN(PL_TSC, 2, PL_DUST, 2, 3, 2, kRunsSmall)
-    PL_R(PL_TSC, 3, PL_LORENTZ, 1, 1, 3) PL_R(PL_TSC, 3, PL_LORENTZ, 1, 2, 3) PL_R(PL_TSC, 3, PL_LORENTZ, 2, 2, 3)
+    PL_R(PL_TSC, 3, PL_LORENTZ, 1, 1, 3) PL_R(PL_TSC, 3, PL_LORENTZ, 2, 1, 3) PL_R(PL_TSC, 3, PL_LORENTZ, 1, 2, 3)
+    PL_R(PL_TSC, 3, PL_LORENTZ, 2, 2, 3)
 #undef PL_RF
 #undef PL_RG
 #undef PL_R
@@ -1222,21 +1538,40 @@ StepKernel pick_runs_mix(int shape, int dim, int hf, int ts, int chl, int chd)
         return k_runs_mix<PREC, S, D, HF_, TS_, CL, CD>;
     PL_M(PL_TSC, 3, 0, 0, 0, 0) PL_M(PL_TSC, 2, 0, 0, 0, 0) PL_M(PL_CIC, 3, 0, 0, 0, 0) PL_M(PL_CIC, 2, 0, 0, 0, 0)
     PL_M(PL_TSC, 3, 1, 1, 1, 2) PL_M(PL_TSC, 3, 2, 1, 1, 2) PL_M(PL_TSC, 3, 1, 2, 1, 2) PL_M(PL_TSC, 3, 2, 2, 1, 2)
-    PL_M(PL_TSC, 3, 1, 1, 3, 2) PL_M(PL_TSC, 3, 1, 2, 3, 2) PL_M(PL_TSC, 3, 2, 2, 3, 2)
+    PL_M(PL_TSC, 3, 1, 1, 3, 2) PL_M(PL_TSC, 3, 2, 1, 3, 2) PL_M(PL_TSC, 3, 1, 2, 3, 2) PL_M(PL_TSC, 3, 2, 2, 3, 2)
 #undef PL_M
     return nullptr;
 }
 
 template <int PREC>
-static size_t runs_item_lds(const Ctx *c, const ItemDesc &it, int hf)
+static size_t runs_item_lds(const Ctx *c, const ItemDesc &it, int hf, int nt)
 {
-    const int d3 = c->d.ndim >= 3;
+    const int d3 = c->d.ndim >= 3, dq = runs_queue<PREC>(nt);
     const int Lf = (it.tile[0] + 2 * hf) * (it.tile[1] + 2 * hf) * (d3 ? it.tile[2] + 2 * hf : 1);
     const int Ld = (it.tile[0] + 4) * (it.tile[1] + 4) * (d3 ? it.tile[2] + 4 : 1);
     size_t offs[6];
-    if (it.kind == PL_LORENTZ) return runs_lds_bytes<PREC, PL_LORENTZ>(Lf, Ld, it.nslot, hf, offs);
-    if (it.kind == PL_DUST) return runs_lds_bytes<PREC, PL_DUST>(Lf, Ld, it.nslot, hf, offs);
-    return runs_lds_bytes<PREC, PL_TRACER>(Lf, Ld, 0, hf, offs);
+    if (it.kind == PL_LORENTZ) return runs_lds_bytes<PREC, PL_LORENTZ>(Lf, Ld, it.nslot, hf, dq, offs);
+    if (it.kind == PL_DUST) return runs_lds_bytes<PREC, PL_DUST>(Lf, Ld, it.nslot, hf, dq, offs);
+    return runs_lds_bytes<PREC, PL_TRACER>(Lf, Ld, 0, hf, dq, offs);
+}
+
+// Which particles join their batch's float32 deposit sums decides those sums'
+// last bits: particles up to one cell outside the tile do where 32-byte field
+// records with a two-cell halo and queues of 256 fit the LDS beside the deposit
+// tile, else particles inside the tile only.  (The records take 24 bytes; the
+// rule stays, so the grids do not depend on how much the LDS holds besides.)
+template <int PREC>
+static bool runs_wide_sums(const Ctx *c, const ItemDesc *host, int nitems)
+{
+    const int d3 = c->d.ndim >= 3;
+    for (int i = 0; i < nitems; ++i) {
+        const int *T = host[i].tile, ns = host[i].kind == PL_TRACER ? 0 : host[i].nslot;
+        const size_t Lf = (size_t)(T[0] + 4) * (T[1] + 4) * (d3 ? T[2] + 4 : 1);
+        const size_t b = runs_section(Lf * (host[i].kind == PL_LORENTZ ? 32 : 16)) + runs_section(Lf * ns * 8) + 256 +
+                         1024 + 1024 * (size_t)(3 + ns) + 80;
+        if (b > (size_t)c->lds_max) return false;
+    }
+    return true;
 }
 
 // Launch configuration of the run kernel for the items of one launch.
@@ -1253,8 +1588,8 @@ bool runs_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, RunsPlan &pl
     // allows them: charged rho J F or all eight, dust rho F.  (With run-time
     // shapes the LDS offsets are registers and the kernel spills: 5.3e6
     // charged particles on 96^3 and eight 32^3 boxes, eight channels, 980 us
-    // against 806 us fixed; float64 on 96^3, 7.1e6 particles: 1105 us
-    // against 940 us.)
+    // against 613 us fixed; float64 on 96^3, 7.1e6 particles: 1105 us
+    // against 799 us, both with the changes of k_runs.)
     const bool d2 = c->d.ndim == 2;
     if (c->d.shape == PL_TSC && !(d2 && pl.mixed)) {
         auto set_of = [&](const ItemDesc &it, int want) {
@@ -1282,23 +1617,25 @@ bool runs_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, RunsPlan &pl
             pl.chd = 2;
         }
     }
+    auto bytes = [&](int hf, int nt) {
+        size_t lds = 0;
+        for (int i = 0; i < nitems; ++i) lds = std::max(lds, runs_item_lds<PREC>(c, host[i], hf, nt));
+        return lds;
+    };
+    // 2D tiles small enough for two blocks on a CU: a unit of an 8 x 8 tile has
+    // fewer runs than a large block has threads, and a large block's staging,
+    // runs and flush wait on each other (512^2 cells, 16 particles per cell: 285
+    // us per launch with one large block of run-time shape, 190 us with two of
+    // 256 threads; with four of 128 or eight of 64 threads a launch of the same
+    // kernel took 1.1 and 1.4 times as long)
+    if (d2 && !pl.mixed && 2 * bytes(2, kRunsSmall) <= (size_t)c->lds_max) pl.nt = kRunsSmall;
+    else if (d2) pl.ts = pl.chl = pl.chd = 0;
     // LDS of the launch: a two-cell field halo when it fits, else one cell
     for (int hf = 2; hf >= 1; --hf) {
-        size_t lds = 0;
-        for (int i = 0; i < nitems; ++i) lds = std::max(lds, runs_item_lds<PREC>(c, host[i], hf));
-        if (lds <= (size_t)c->lds_max) {
-            pl.hf = hf;
-            pl.lds = lds;
-            // 2D tiles whose LDS lets two blocks share a CU: a unit of an 8 x 8
-            // tile has fewer runs than a large block has threads, and its
-            // staging, runs and flush wait on each other (512^2 cells, 16
-            // particles per cell: 285 us per launch with one large block of
-            // run-time shape, 235 us with two small ones of fixed shape; four
-            // at half the registers spill: 313 us)
-            if (d2 && !pl.mixed && 2 * lds <= (size_t)c->lds_max) pl.nt = kRunsSmall;
-            else if (d2) pl.ts = pl.chl = pl.chd = 0;
-            return true;
-        }
+        pl.hf = hf;
+        pl.lds = bytes(hf, pl.nt);
+        pl.narrow = PREC == PL_F32_OFFSET && hf == 2 && !runs_wide_sums<PREC>(c, host, nitems);
+        if (pl.lds <= (size_t)c->lds_max) return true;
     }
     return false;
 }
@@ -1311,6 +1648,7 @@ hipError_t launch_runs_impl(Ctx *c, const ItemDesc *table, const ItemDesc *host,
     RunsPlan pl;
     if (!runs_plan_impl<PREC>(c, host, nitems, pl)) return hipErrorInvalidConfiguration;
     if (pl.hf == 2) sf |= SF_FHALO2;
+    if (pl.narrow) sf |= SF_NARROW;
     StepKernel k;
     int chs = 0;
     if (pl.mixed) {
@@ -1326,7 +1664,7 @@ hipError_t launch_runs_impl(Ctx *c, const ItemDesc *table, const ItemDesc *host,
     const int rb = pl.nt;
     // every item has kRunsSplit units beyond its tiles for the pieces of crowded tiles
     const int units = total_units + nitems * kRunsSplit;
-    int grid = std::min(units, resident_blocks(c, k, rb, pl.lds));
+    const int grid = std::min(units, resident_blocks(c, k, rb, pl.lds));
     hipLaunchKernelGGL(k, dim3(grid), dim3(rb), pl.lds, c->stream, table, nitems, units, counter, c->errflags, sf,
                        (int)pl.lds);
     c->stats[0]++;

@@ -43,6 +43,7 @@ enum StepFlag : unsigned {
     SF_SUMS = 4u,       // particle-side conservation sums
     SF_RUNS = 8u,       // tiled: each thread takes a contiguous run of the tile's particles
     SF_FHALO2 = 16u,    // run-based: the LDS field tile carries a two-cell halo
+    SF_NARROW = 32u,    // run-based: only particles inside the tile join their batch's deposit sums
 };
 
 // Everything a kernel needs to know about one item of a call.  Built on the
@@ -166,7 +167,7 @@ struct Ctx {
 struct RunsPlan {
     int hf = 0, ts = 0, chl = 0, chd = 0, nt = 0;
     size_t lds = 0;
-    bool mixed = false;
+    bool mixed = false, narrow = false;
 };
 bool runs_plan(const Ctx *c, const ItemDesc *host, int nitems, RunsPlan &pl);
 
