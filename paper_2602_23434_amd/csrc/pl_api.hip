@@ -122,10 +122,7 @@ void free_ctx(Ctx *c)
     (void)hipFree(c->counters);
     (void)hipFree(c->errflags);
     (void)hipFree(c->sums);
-    for (int k = 0; k < 2; ++k) {
-        (void)hipFree(c->keys[k]);
-        (void)hipFree(c->idx[k]);
-    }
+    (void)hipFree(c->slab);
     (void)hipFree(c->hist);
     (void)hipFree(c->hist_scan);
     (void)hipFree(c->cell_start);
@@ -549,9 +546,19 @@ pl_status pl_part_init(pl_ctx **out, const pl_init_desc *d)
               hipMalloc(&c->hist, (size_t)c->hist_cap * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&c->hist_scan, (size_t)c->hist_cap * sizeof(uint32_t)) == hipSuccess &&
               hipHostMalloc(&c->pinned, Ctx::kRing * mi * sizeof(ItemDesc), hipHostMallocDefault) == hipSuccess;
-    for (int k = 0; ok && k < 2; ++k)
-        ok = hipMalloc(&c->keys[k], np * sizeof(uint32_t)) == hipSuccess &&
-             hipMalloc(&c->idx[k], np * sizeof(uint32_t)) == hipSuccess;
+    // keys and indices in one allocation, which also holds the spectral update's
+    // 64-byte fluid records of every cell where there is a particle per cell or
+    // more (with four or more it needs nothing beyond the keys)
+    const size_t npa = (np + 63) & ~(size_t)63;
+    size_t slab = 4 * npa * sizeof(uint32_t);
+    if (ok && max_cells <= (int64_t)np) slab = std::max(slab, (size_t)max_cells * 64);
+    ok = ok && hipMalloc(&c->slab, slab) == hipSuccess;
+    for (int k = 0; ok && k < 2; ++k) {
+        c->keys[k] = static_cast<uint32_t *>(c->slab) + (size_t)k * npa;
+        c->idx[k] = static_cast<uint32_t *>(c->slab) + (size_t)(2 + k) * npa;
+    }
+    c->records = static_cast<double *>(c->slab);
+    c->record_cells = (int64_t)(slab / 64);
     if (ok && d->key_mode == PL_KEY_TILE_RANK)
         ok = hipMalloc(&c->cell_start, (size_t)max_cells * sizeof(int32_t)) == hipSuccess;
     if (ok && d->algo == PL_ALGO_PLAIN) {

@@ -158,6 +158,10 @@ struct Ctx {
     // p.fp arrays whose particles a sort has reordered since a gather_push
     // last wrote them: a deposit of F from them is refused
     std::vector<const void *> fp_stale;
+
+    void *slab = nullptr;            // the keys and indices, one allocation
+    double *records = nullptr;       // fluid records of the spectral update (the slab, between sorts)
+    int64_t record_cells = 0;        // cells it holds
 };
 
 // Launch configuration of the run kernel for one launch's items: field halo,
