@@ -10,6 +10,12 @@
 // waves take consecutive sub-ranges.  The final index list moves every SoA
 // array into the alternate buffer set, and a boundary pass writes the
 // first-particle offset of every tile.
+//
+// Several items of a call are sorted together where the scratch holds their
+// particles (SortGroup): item i's keys start after the keys of the items before
+// it, so one sort of the concatenated particles leaves every item in its own
+// range, in its own stable order.  A sort's launches cost about 5 us each
+// whatever they do, and a call over eleven items took 220 of them.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -22,90 +28,157 @@ namespace pl {
 
 constexpr int kSortWaves = 8;
 constexpr int kSortThreads = kSortWaves * 64;
-constexpr int kPerWave = 1024;                       // elements per wave per block
-constexpr int kPerBlock = kSortWaves * kPerWave;     // elements per block
+// Elements per thread of a block: 16, or 4 where 16 would leave most CUs without
+// a block (262107 particles: 32 blocks or 128).
+constexpr int kPerThread = 16, kPerThreadSmall = 4;
+constexpr int kSmallSort = 1 << 19;
+constexpr int kPerBlock = kSortThreads * kPerThread;
+// Digit counts of one pass over up to np elements (the smaller blocks' at most).
+constexpr int64_t kSortHist(int64_t np)
+{
+    const int64_t small = np < kSmallSort ? np : kSmallSort, s = kSortThreads * kPerThreadSmall;
+    const int64_t a = (np + kPerBlock - 1) / kPerBlock, b = (small + s - 1) / s;
+    return ((a > b ? a : b) << kMaxDigitBits) + 1024;
+}
+__host__ inline int sort_per(int np) { return np > kSmallSort ? kPerThread : kPerThreadSmall; }
+__host__ inline int sort_blocks(int np) { return (np + kSortThreads * sort_per(np) - 1) / (kSortThreads * sort_per(np)); }
 constexpr int kScanBlocks = 512;
 
-// Digit counts of the 64 keys from e0 (those below end) added to cnt: the
-// first lane of every run of equal digits adds the run's length.  All lanes
-// of the wave take part.
-__device__ __forceinline__ void count_runs(const uint32_t *keys, int e0, int end, int shift, uint32_t mask,
-                                           uint32_t *cnt)
+// Digit count of one key per lane (v: the lane has one, the lanes with one
+// come first, the first nv of the lanes) added to cnt: the first lane of every run of equal
+// digits adds the run's length.  All lanes of the wave take part.
+__device__ __forceinline__ void count_runs(uint32_t key, bool v, int nv, int shift, uint32_t mask, uint32_t *cnt)
 {
     const int lane = threadIdx.x & 63;
-    const int e = e0 + lane;
-    const bool v = e < end;
-    const uint32_t d = v ? (keys[e] >> shift) & mask : ~0u;
+    const uint32_t d = v ? (key >> shift) & mask : ~0u;
     const uint32_t prev = __shfl_up(d, 1, 64);
     const bool head = v && (lane == 0 || prev != d);
     const uint64_t hm = __ballot(head);
     if (head) {
         const uint64_t later = hm & ~((2ull << lane) - 1ull);     // heads after this lane
-        const int stop = later ? __builtin_ctzll(later) : min(64, end - e0);
+        const int stop = later ? __builtin_ctzll(later) : min(64, nv);
         atomicAdd(&cnt[d], (uint32_t)(stop - lane));
     }
 }
 
-__global__ void k_keys(SortArgs a, uint32_t *keys)
+// Items sorted together: their particles one after another (item i's at
+// [base[i], base[i + 1])) and their keys (item i's from kbase[i]).  tbase: tiles
+// before item i.  Passed to the kernels by value.
+struct SortItem {
+    int n[3], tile[3];
+    int np, ntiles;
+    const uint32_t *cell;            // F32_OFFSET
+    const double *x[3];              // F64
+    int32_t *tile_start;
+    int32_t *runs;
+};
+constexpr int kGroup = 8;
+struct SortGroup {
+    int count, total, prec, ndim, key_mode;
+    int base[kGroup + 1], tbase[kGroup + 1];
+    uint32_t kbase[kGroup];
+    SortItem it[kGroup];
+};
+static_assert(sizeof(SortGroup) <= 3072, "kernel arguments");
+
+// Key of particle p of an item.
+__device__ __forceinline__ uint32_t sort_key(const SortGroup &g, const SortItem &a, int p)
 {
     const int tx = a.tile[0], ty = a.tile[1], tz = a.tile[2];
     const int ntx = (a.n[0] + tx - 1) / tx, nty = (a.n[1] + ty - 1) / ty;     // (the plain algorithm's may not divide)
     const int per_tile = tx * ty * tz;
     const bool p2 = ((tx & (tx - 1)) | (ty & (ty - 1)) | (tz & (tz - 1))) == 0;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < a.np; p += gridDim.x * blockDim.x) {
-        int c[3] = {0, 0, 0};
-        if (a.prec == PL_F32_OFFSET) {
-            unpack_cell(a.cell[p], c[0], c[1], c[2]);
-            for (int d = 0; d < 3; ++d)
-                if (c[d] >= a.n[d]) c[d] %= a.n[d];
-        } else {
-            for (int d = 0; d < a.ndim; ++d) {
-                double v = a.x[d][p];
-                double nn = (double)a.n[d];
-                if (!(v >= 0.0 && v < nn)) {
-                    if (!isfinite(v)) v = 0.0;
-                    v = v - nn * floor(v / nn);
-                    if (v >= nn || v < 0.0) v = 0.0;
-                }
-                c[d] = (int)floor(v);
+    int c[3] = {0, 0, 0};
+    if (g.prec == PL_F32_OFFSET) {
+        unpack_cell(a.cell[p], c[0], c[1], c[2]);
+        for (int d = 0; d < 3; ++d)
+            if (c[d] >= a.n[d]) c[d] %= a.n[d];
+    } else {
+        for (int d = 0; d < g.ndim; ++d) {
+            double v = a.x[d][p];
+            double nn = (double)a.n[d];
+            if (!(v >= 0.0 && v < nn)) {
+                if (!isfinite(v)) v = 0.0;
+                v = v - nn * floor(v / nn);
+                if (v >= nn || v < 0.0) v = 0.0;
             }
+            c[d] = (int)floor(v);
         }
-        // power-of-two tile sides (the usual case) divide by shifts
-        int q[3], r[3];
-        const int td[3] = {tx, ty, tz};
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            if (p2) {
-                const int lg = __builtin_ctz((unsigned)td[d]);
-                q[d] = c[d] >> lg;
-                r[d] = c[d] & (td[d] - 1);
-            } else {
-                q[d] = c[d] / td[d];
-                r[d] = c[d] % td[d];
-            }
-        }
-        int t = q[0] + ntx * (q[1] + nty * q[2]);
-        uint32_t key = (uint32_t)t;
-        if (a.key_mode == PL_KEY_TILE_CELL || a.key_mode == PL_KEY_TILE_RUN) {
-            int yy = r[1];
-            // run order: rows taken as 0, 2, 4, 6, 1, 3, 5, 7 within every group
-            // of eight (0, 2, 1, 3 within groups of four), so that the lanes
-            // served together by one LDS access hold rows of one parity and
-            // their records and deposit cells fall on distinct banks
-            if (a.key_mode == PL_KEY_TILE_RUN && (ty & 7) == 0)
-                yy = (yy & ~7) | ((yy & 1) << 2) | ((yy >> 1) & 3);
-            else if (a.key_mode == PL_KEY_TILE_RUN && (ty & 3) == 0)
-                yy = (yy & ~3) | ((yy & 1) << 1) | ((yy >> 1) & 1);
-            int loc = r[0] + tx * (yy + ty * r[2]);
-            key = (uint32_t)t * (uint32_t)per_tile + (uint32_t)loc;
-        }
-        keys[p] = key;
     }
+    // power-of-two tile sides (the usual case) divide by shifts
+    int q[3], r[3];
+    const int td[3] = {tx, ty, tz};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        if (p2) {
+            const int lg = __builtin_ctz((unsigned)td[d]);
+            q[d] = c[d] >> lg;
+            r[d] = c[d] & (td[d] - 1);
+        } else {
+            q[d] = c[d] / td[d];
+            r[d] = c[d] % td[d];
+        }
+    }
+    int t = q[0] + ntx * (q[1] + nty * q[2]);
+    uint32_t key = (uint32_t)t;
+    if (g.key_mode == PL_KEY_TILE_CELL || g.key_mode == PL_KEY_TILE_RUN) {
+        int yy = r[1];
+        // run order: rows taken as 0, 2, 4, 6, 1, 3, 5, 7 within every group
+        // of eight (0, 2, 1, 3 within groups of four), so that the lanes
+        // served together by one LDS access hold rows of one parity and
+        // their records and deposit cells fall on distinct banks
+        if (g.key_mode == PL_KEY_TILE_RUN && (ty & 7) == 0)
+            yy = (yy & ~7) | ((yy & 1) << 2) | ((yy >> 1) & 3);
+        else if (g.key_mode == PL_KEY_TILE_RUN && (ty & 3) == 0)
+            yy = (yy & ~3) | ((yy & 1) << 1) | ((yy >> 1) & 1);
+        int loc = r[0] + tx * (yy + ty * r[2]);
+        key = (uint32_t)t * (uint32_t)per_tile + (uint32_t)loc;
+    }
+    return key;
+}
+
+// Keys of every particle, and the digit histogram of the first pass (low
+// dbits bits) of each block's keys, stored digit-major: hist[d *
+// nblocks + b].
+template <int PT>
+__global__ __launch_bounds__(kSortThreads) void k_keys(SortGroup g, uint32_t *keys, int dbits, int nblocks, uint32_t *hist)
+{
+    constexpr int kBlock = PT * kSortThreads;
+    __shared__ uint32_t h[1 << kMaxDigitBits];
+    const int nd = 1 << dbits;
+    for (int d = threadIdx.x; d < nd; d += blockDim.x) h[d] = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int beg = blockIdx.x * kBlock, end = min(g.total, beg + kBlock);
+    constexpr int PER = 4;                            // a thread's keys in flight
+    for (int b0 = beg; b0 < end; b0 += PER * kSortThreads) {
+        uint32_t k[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) k[q] = 0;
+        for (int i = 0; i < g.count; ++i) {           // uniform
+            if (g.base[i] >= b0 + PER * kSortThreads || g.base[i + 1] <= b0) continue;
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const int e = b0 + q * kSortThreads + (int)threadIdx.x;
+                if (e < end && e >= g.base[i] && e < g.base[i + 1])
+                    k[q] = g.kbase[i] + sort_key(g, g.it[i], e - g.base[i]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int e = b0 + q * kSortThreads + (int)threadIdx.x;
+            if (e < end) keys[e] = k[q];
+            if (e - lane < end) count_runs(k[q], e < end, end - (e - lane), 0, (uint32_t)nd - 1u, h);     // uniform per wave
+        }
+    }
+    __syncthreads();
+    for (int d = threadIdx.x; d < nd; d += blockDim.x) hist[(size_t)d * nblocks + blockIdx.x] = h[d];
 }
 
 // Per-block digit histogram of dbits-bit digits, stored digit-major:
 // hist[d * nblocks + b].  Equal digits in consecutive lanes (the keys are
 // mostly in order after the first sort) count with one LDS atomic per run.
+template <int PT>
 __global__ __launch_bounds__(kSortThreads) void k_hist(const uint32_t *keys, int np, int shift, int dbits,
                                                        int nblocks, uint32_t *hist)
 {
@@ -115,10 +188,20 @@ __global__ __launch_bounds__(kSortThreads) void k_hist(const uint32_t *keys, int
     for (int d = threadIdx.x; d < nd; d += blockDim.x) h[d] = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    const int beg = blockIdx.x * kPerBlock;
-    const int end = min(np, beg + kPerBlock);
-    for (int e0 = beg + (int)threadIdx.x - lane; e0 < end; e0 += blockDim.x)       // uniform per wave
-        count_runs(keys, e0, end, shift, mask, h);
+    const int beg = blockIdx.x * (PT * kSortThreads);
+    const int end = min(np, beg + PT * kSortThreads);
+    constexpr int PER = PT;                           // a thread's keys, all in flight
+    uint32_t k[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = beg + q * kSortThreads + (int)threadIdx.x;
+        k[q] = e < end ? keys[e] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e0 = beg + q * kSortThreads + (int)threadIdx.x - lane;
+        if (e0 < end) count_runs(k[q], e0 + lane < end, end - e0, shift, mask, h);     // uniform per wave
+    }
     __syncthreads();
     for (int d = threadIdx.x; d < nd; d += blockDim.x) hist[(size_t)d * nblocks + blockIdx.x] = h[d];
 }
@@ -192,38 +275,75 @@ __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t *in, long m, 
 
 // Stable scatter of one radix pass of dbits-bit digits (per-wave digit
 // cursors in dynamic LDS: kSortWaves << dbits words).  idx_in == nullptr
-// means identity (first pass).
+// means identity (first pass).  A wave holds its keys and indices in registers:
+// one read of each, all of them in flight (the keys were read twice, 64 at a
+// time: 179 to 132 us per pass over 2^24 pairs).  offs: the scanned histogram, or (raw) the histogram
+// itself, which few enough blocks sum up for themselves.
+template <int PT>
 __global__ __launch_bounds__(kSortThreads) void k_scatter(const uint32_t *keys_in, const uint32_t *idx_in,
                                                           uint32_t *keys_out, uint32_t *idx_out, int np,
-                                                          int shift, int dbits, int nblocks, const uint32_t *offs)
+                                                          int shift, int dbits, int nblocks, const uint32_t *offs,
+                                                          bool raw)
 {
     extern __shared__ uint32_t wcs[];
+    __shared__ uint32_t sh[kSortWaves + 1];
+    constexpr int PER = PT, kPerWave = 64 * PT;
     const int nd = 1 << dbits;
     const uint32_t mask = (uint32_t)nd - 1u;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     uint32_t *wc = wcs + wv * nd;                     // this wave's cursors
-    for (int e = threadIdx.x; e < kSortWaves * nd; e += blockDim.x) wcs[e] = 0;
-    __syncthreads();
-    const int bbeg = blockIdx.x * kPerBlock;
-    const int wbeg = bbeg + wv * kPerWave;
+    const int wbeg = (int)blockIdx.x * (PT * kSortThreads) + wv * kPerWave;
     const int wend = min(np, wbeg + kPerWave);
-    for (int e0 = wbeg; e0 < wend; e0 += 64) count_runs(keys_in, e0, wend, shift, mask, wc);
+    uint32_t kr[PER], ir[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int e = wbeg + 64 * i + lane;
+        kr[i] = e < wend ? keys_in[e] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int e = wbeg + 64 * i + lane;
+        ir[i] = idx_in ? (e < wend ? idx_in[e] : 0u) : (uint32_t)e;
+    }
+    for (int e = threadIdx.x; e < kSortWaves * nd; e += blockDim.x) wcs[e] = 0;
+    // first position of digit d of this block, thread d
+    uint32_t first = 0;
+    if (raw) {
+        uint32_t all = 0;
+        if ((int)threadIdx.x < nd)
+#pragma unroll 8
+            for (int b = 0; b < nblocks; ++b) {
+                const uint32_t v = offs[(size_t)threadIdx.x * nblocks + b];
+                first += b < (int)blockIdx.x ? v : 0u;
+                all += v;
+            }
+        uint32_t total;
+        first += block_exclusive_scan(all, sh, total);
+    } else if ((int)threadIdx.x < nd) {
+        first = offs[(size_t)threadIdx.x * nblocks + blockIdx.x];
+    }
     __syncthreads();
-    for (int d = threadIdx.x; d < nd; d += blockDim.x) {
-        uint32_t run = offs[(size_t)d * nblocks + blockIdx.x];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int e0 = wbeg + 64 * i;
+        if (e0 < wend) count_runs(kr[i], e0 + lane < wend, wend - e0, shift, mask, wc);      // uniform per wave
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < nd) {
+        uint32_t run = first;
         for (int w = 0; w < kSortWaves; ++w) {
-            uint32_t t = wcs[w * nd + d];
-            wcs[w * nd + d] = run;
+            uint32_t t = wcs[w * nd + threadIdx.x];
+            wcs[w * nd + threadIdx.x] = run;
             run += t;
         }
     }
     __syncthreads();
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int base = wbeg; base < wend; base += 64) {
-        int e = base + lane;
-        bool valid = e < wend;
-        uint32_t k = valid ? keys_in[e] : 0u;
-        uint32_t id = valid ? (idx_in ? idx_in[e] : (uint32_t)e) : 0u;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (wbeg + 64 * i >= wend) break;             // uniform per wave
+        const bool valid = wbeg + 64 * i + lane < wend;
+        const uint32_t k = kr[i];
         uint32_t d = (k >> shift) & mask;
         uint64_t peers = __ballot(valid);
         for (int b = 0; b < dbits; ++b) {
@@ -234,7 +354,7 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const uint32_t *keys_i
             uint32_t rank = (uint32_t)__popcll(peers & lt);
             uint32_t dst = wc[d] + rank;
             keys_out[dst] = k;
-            idx_out[dst] = id;
+            idx_out[dst] = ir[i];
         }
         // make every lane's read of wc[d] happen before the update
         __builtin_amdgcn_wave_barrier();
@@ -253,48 +373,70 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const uint32_t *keys_i
 // permutation is read once, and all of a position's loads are in flight
 // before its stores.  With perm2 the source of position r is
 // perm2[perm[r]] (run order: new position -> sorted position -> source).
+// Positions and sources count from the group's first particle; items share a
+// launch where they have the same arrays.  With run tables the first blocks list
+// the work units, which nothing else in the launch waits for.
 struct PermArrays {
-    const void *src[SortArgs::kMaxArrays];
-    void *dst[SortArgs::kMaxArrays];
+    int first[kGroup + 1];   // positions of the launch's items, counted from the group's first particle
+    const void *src[kGroup][SortArgs::kMaxArrays];
+    void *dst[kGroup][SortArgs::kMaxArrays];
     int wide;                // bit k: array k has 8-byte elements
-    int n;
+    int n, count;
 };
+struct UnitLists {
+    int count;
+    int32_t *runs[kGroup];
+    int np[kGroup], ntiles[kGroup];
+};
+constexpr int kPermThreads = 256;
+__device__ __forceinline__ void unit_list(int32_t *runs, int np, int ntiles);
 
-__global__ void k_permute_all(const uint32_t *__restrict__ perm, const uint32_t *__restrict__ perm2, int np,
-                              PermArrays pa)
+__global__ __launch_bounds__(kPermThreads) void k_permute_all(const uint32_t *__restrict__ perm,
+                                                              const uint32_t *__restrict__ perm2, PermArrays pa,
+                                                              UnitLists ul)
 {
+    if ((int)blockIdx.x < ul.count) {                // uniform
+        unit_list(ul.runs[blockIdx.x], ul.np[blockIdx.x], ul.ntiles[blockIdx.x]);
+        return;
+    }
     // two positions per iteration, every load of both issued before any store
-    const int stride = gridDim.x * blockDim.x;
-    for (int r0 = blockIdx.x * blockDim.x + threadIdx.x; r0 < np; r0 += 2 * stride) {
-        const int r1 = r0 + stride;
-        const bool two = r1 < np;
-        uint32_t q0 = perm[r0], q1 = two ? perm[r1] : q0;
-        if (perm2) {
-            q0 = perm2[q0];
-            q1 = perm2[q1];
-        }
-        unsigned long long v0[SortArgs::kMaxArrays], v1[SortArgs::kMaxArrays];
+    const int stride = ((int)gridDim.x - ul.count) * kPermThreads;
+    const int b0 = ((int)blockIdx.x - ul.count) * kPermThreads + (int)threadIdx.x;
+    for (int it = 0; it < pa.count; ++it) {
+        const int base = pa.first[it], end = pa.first[it + 1];
+        for (int r0 = base + b0; r0 < end; r0 += 2 * stride) {
+            const int r1 = r0 + stride;
+            const bool two = r1 < end;
+            uint32_t q0 = perm[r0], q1 = two ? perm[r1] : q0;
+            if (perm2) {
+                q0 = perm2[q0];
+                q1 = perm2[q1];
+            }
+            q0 -= (uint32_t)base;
+            q1 -= (uint32_t)base;
+            unsigned long long v0[SortArgs::kMaxArrays], v1[SortArgs::kMaxArrays];
 #pragma unroll
-        for (int k = 0; k < SortArgs::kMaxArrays; ++k) {
-            if (k < pa.n) {
-                if ((pa.wide >> k) & 1) {
-                    v0[k] = ((const unsigned long long *)pa.src[k])[q0];
-                    v1[k] = ((const unsigned long long *)pa.src[k])[q1];
-                } else {
-                    v0[k] = ((const uint32_t *)pa.src[k])[q0];
-                    v1[k] = ((const uint32_t *)pa.src[k])[q1];
+            for (int k = 0; k < SortArgs::kMaxArrays; ++k) {
+                if (k < pa.n) {
+                    if ((pa.wide >> k) & 1) {
+                        v0[k] = ((const unsigned long long *)pa.src[it][k])[q0];
+                        v1[k] = ((const unsigned long long *)pa.src[it][k])[q1];
+                    } else {
+                        v0[k] = ((const uint32_t *)pa.src[it][k])[q0];
+                        v1[k] = ((const uint32_t *)pa.src[it][k])[q1];
+                    }
                 }
             }
-        }
 #pragma unroll
-        for (int k = 0; k < SortArgs::kMaxArrays; ++k) {
-            if (k < pa.n) {
-                if ((pa.wide >> k) & 1) {
-                    ((unsigned long long *)pa.dst[k])[r0] = v0[k];
-                    if (two) ((unsigned long long *)pa.dst[k])[r1] = v1[k];
-                } else {
-                    ((uint32_t *)pa.dst[k])[r0] = (uint32_t)v0[k];
-                    if (two) ((uint32_t *)pa.dst[k])[r1] = (uint32_t)v1[k];
+            for (int k = 0; k < SortArgs::kMaxArrays; ++k) {
+                if (k < pa.n) {
+                    if ((pa.wide >> k) & 1) {
+                        ((unsigned long long *)pa.dst[it][k])[r0 - base] = v0[k];
+                        if (two) ((unsigned long long *)pa.dst[it][k])[r1 - base] = v1[k];
+                    } else {
+                        ((uint32_t *)pa.dst[it][k])[r0 - base] = (uint32_t)v0[k];
+                        if (two) ((uint32_t *)pa.dst[it][k])[r1 - base] = (uint32_t)v1[k];
+                    }
                 }
             }
         }
@@ -303,13 +445,13 @@ __global__ void k_permute_all(const uint32_t *__restrict__ perm, const uint32_t 
 
 // Spectral rows (nb float64 per particle, particle-major): destination row r
 // takes source row perm[r] (perm2[perm[r]] with perm2); one wave per row.
-__global__ __launch_bounds__(256) void k_permute_rows(const uint32_t *perm, const uint32_t *perm2, int np, int nb,
+__global__ __launch_bounds__(256) void k_permute_rows(const uint32_t *perm, const uint32_t *perm2, int base, int np, int nb,
                                                       const double *src0, double *dst0, const double *src1,
                                                       double *dst1)
 {
     const int lane = threadIdx.x & 63;
     for (int r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; r < np; r += (gridDim.x * blockDim.x) >> 6) {
-        const uint32_t q = perm2 ? perm2[perm[r]] : perm[r];
+        const uint32_t q = (perm2 ? perm2[perm[base + r]] : perm[base + r]) - (uint32_t)base;
         const long s = (long)q * nb, d = (long)r * nb;
         for (int i = lane; i < nb; i += 64) {
             dst0[d + i] = src0[s + i];
@@ -318,34 +460,69 @@ __global__ __launch_bounds__(256) void k_permute_rows(const uint32_t *perm, cons
     }
 }
 
-static void permute_arrays(Ctx *c, const SortArgs &a, const uint32_t *perm, const uint32_t *perm2, int grid)
+// Every array of the items args[0 .. g.count) moved by the group's
+// permutation, and (lists) their work units listed.
+static void permute_arrays(Ctx *c, const SortGroup &g, const SortArgs *args, const uint32_t *perm, const uint32_t *perm2,
+                           bool lists)
 {
-    if (a.nb > 0) {
-        const int g = std::max(1, std::min((a.np + 3) / 4, 64 * c->num_cu));
-        hipLaunchKernelGGL(k_permute_rows, dim3(g), dim3(256), 0, c->stream, perm, perm2, a.np, a.nb, a.rsrc[0],
-                           a.rdst[0], a.rsrc[1], a.rdst[1]);
+    for (int i = 0; i < g.count; ++i) {
+        const SortArgs &a = args[i];
+        if (a.nb <= 0) continue;
+        const int grid = std::max(1, std::min((a.np + 3) / 4, 64 * c->num_cu));
+        hipLaunchKernelGGL(k_permute_rows, dim3(grid), dim3(256), 0, c->stream, perm, perm2, g.base[i], a.np, a.nb,
+                           a.rsrc[0], a.rdst[0], a.rsrc[1], a.rdst[1]);
         c->stats[0]++;
     }
-    PermArrays pa;
-    memset(&pa, 0, sizeof(pa));
-    pa.n = a.narrays;
-    for (int k = 0; k < a.narrays; ++k) {
-        pa.src[k] = a.src[k];
-        pa.dst[k] = a.dst[k];
-        if (a.esize[k] == 8) pa.wide |= 1 << k;
+    for (int i0 = 0, i1 = 0; i0 < g.count; i0 = i1) {
+        PermArrays pa;
+        UnitLists ul;
+        memset(&pa, 0, sizeof(pa));
+        memset(&ul, 0, sizeof(ul));
+        pa.n = args[i0].narrays;
+        for (int k = 0; k < pa.n; ++k)
+            if (args[i0].esize[k] == 8) pa.wide |= 1 << k;
+        for (i1 = i0; i1 < g.count; ++i1) {
+            const SortArgs &a = args[i1];
+            int wide = 0;
+            for (int k = 0; k < a.narrays; ++k)
+                if (a.esize[k] == 8) wide |= 1 << k;
+            if (a.narrays != pa.n || wide != pa.wide) break;
+            const int m = i1 - i0;
+            pa.first[m] = g.base[i1];
+            pa.first[m + 1] = g.base[i1 + 1];
+            for (int k = 0; k < a.narrays; ++k) {
+                pa.src[m][k] = a.src[k];
+                pa.dst[m][k] = a.dst[k];
+            }
+            if (lists) {
+                ul.runs[ul.count] = a.runs;
+                ul.np[ul.count] = a.np;
+                ul.ntiles[ul.count++] = a.ntiles;
+            }
+        }
+        pa.count = i1 - i0;
+        const int np = g.base[i1] - g.base[i0];
+        const int grid = std::min((np + kPermThreads - 1) / kPermThreads, 16 * c->num_cu) + ul.count;
+        hipLaunchKernelGGL(k_permute_all, dim3(grid), dim3(kPermThreads), 0, c->stream, perm, perm2, pa, ul);
+        c->stats[0]++;
     }
-    hipLaunchKernelGGL(k_permute_all, dim3(grid), dim3(256), 0, c->stream, perm, perm2, a.np, pa);
-    c->stats[0]++;
 }
 
-__global__ void k_tile_start(const uint32_t *keys, int np, int shift, int per_tile, int ntiles, int32_t *ts)
+// First particle of every tile of every item (offsets within the item).
+__global__ void k_tile_start(SortGroup g, const uint32_t *keys, int shift, int key_mode)
 {
-    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < np; r += gridDim.x * blockDim.x) {
-        int t = (int)((keys[r] >> shift) / (uint32_t)per_tile);
-        int prev = r > 0 ? (int)((keys[r - 1] >> shift) / (uint32_t)per_tile) : -1;
-        for (int q = prev + 1; q <= t; ++q) ts[q] = r;
-        if (r == np - 1)
-            for (int q = t + 1; q <= ntiles; ++q) ts[q] = np;
+    for (int i = 0; i < g.count; ++i) {
+        const SortItem &a = g.it[i];
+        const uint32_t per = key_mode == PL_KEY_TILE || shift > 0 ? 1u : (uint32_t)(a.tile[0] * a.tile[1] * a.tile[2]);
+        const uint32_t kb = g.kbase[i];
+        const uint32_t *k = keys + g.base[i];
+        for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < a.np; q += gridDim.x * blockDim.x) {
+            const int t = (int)(((k[q] - kb) >> shift) / per);
+            const int prev = q > 0 ? (int)(((k[q - 1] - kb) >> shift) / per) : -1;
+            for (int m = prev + 1; m <= t; ++m) a.tile_start[m] = q;
+            if (q == a.np - 1)
+                for (int m = t + 1; m <= a.ntiles; ++m) a.tile_start[m] = a.np;
+        }
     }
 }
 
@@ -389,10 +566,20 @@ __global__ void k_rank_keys(uint32_t *keys, int np, const int32_t *cs, int per_t
 constexpr int kRunsBuildThreads = 256;
 constexpr int kRunsDense = 8;
 static_assert(kRunLen == 4, "the crowded rounds' ballot prefix sums take run shortfalls of two bits");
-__global__ __launch_bounds__(kRunsBuildThreads) void k_runs_build(const uint32_t *keys, int np, int per_tile,
-                                                                  int ntiles, const int32_t *ts, int32_t *runs,
-                                                                  uint32_t *perm_out)
+__global__ __launch_bounds__(kRunsBuildThreads) void k_runs_build(SortGroup g, const uint32_t *all_keys,
+                                                                  uint32_t *all_perm)
 {
+    // this block's item (its tiles are the blocks from tbase), keys and permutation
+    int im = 0;
+    while (im + 1 < g.count && (int)blockIdx.x >= g.tbase[im + 1]) ++im;
+    const SortItem &a = g.it[im];
+    const int np = a.np, per_tile = a.tile[0] * a.tile[1] * a.tile[2];
+    const int32_t *ts = a.tile_start;
+    int32_t *runs = a.runs;
+    const uint32_t *keys = all_keys + g.base[im];
+    uint32_t *perm_out = all_perm ? all_perm + g.base[im] : nullptr;
+    const uint32_t pbase = (uint32_t)g.base[im];
+
     __shared__ int cnt[kRunsMaxTileCells];
     __shared__ int first[kRunsMaxTileCells];
     __shared__ int4 crowd[kRunsMaxTileCells];
@@ -401,7 +588,8 @@ __global__ __launch_bounds__(kRunsBuildThreads) void k_runs_build(const uint32_t
     __shared__ int s_max;
     const int cpt = (per_tile + kRunsBuildThreads - 1) / kRunsBuildThreads;   // cells per thread
     const int c0 = threadIdx.x * cpt, c1 = min(per_tile, c0 + cpt);
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    {
+        const int t = (int)blockIdx.x - g.tbase[im];
         const int beg = ts[t], end = ts[t + 1];
         for (int c = threadIdx.x; c < per_tile; c += blockDim.x) cnt[c] = 0;
         if (threadIdx.x == 0) s_max = 0;
@@ -410,7 +598,7 @@ __global__ __launch_bounds__(kRunsBuildThreads) void k_runs_build(const uint32_t
         // (the keys are sorted: no atomics, crowded cells included).  Each
         // thread takes four consecutive keys per 16-byte load and issues the
         // loads of KB such groups before using any.
-        const uint32_t kb = (uint32_t)t * (uint32_t)per_tile;
+        const uint32_t kb = g.kbase[im] + (uint32_t)t * (uint32_t)per_tile;
         {
             typedef uint32_t U4 __attribute__((ext_vector_type(4), aligned(4)));
             constexpr int KB = 8;
@@ -484,7 +672,7 @@ __global__ __launch_bounds__(kRunsBuildThreads) void k_runs_build(const uint32_t
                     const int dst = perm_out ? beg + lbase + lpos : src;
                     runs[beg + base + pos] = (dst << 2) | (len - 1);
                     if (perm_out)
-                        for (int i = 0; i < len; ++i) perm_out[dst + i] = (uint32_t)(src + i);
+                        for (int i = 0; i < len; ++i) perm_out[dst + i] = pbase + (uint32_t)(src + i);
                     ++pos;
                     lpos += len;
                 }
@@ -551,7 +739,7 @@ __global__ __launch_bounds__(kRunsBuildThreads) void k_runs_build(const uint32_t
                         const int dst = perm_out ? beg + wl0 + ppos + lpre : src;
                         runs[beg + wb + pos] = (dst << 2) | (len - 1);
                         if (perm_out)
-                            for (int i = 0; i < len; ++i) perm_out[dst + i] = (uint32_t)(src + i);
+                            for (int i = 0; i < len; ++i) perm_out[dst + i] = pbase + (uint32_t)(src + i);
                     }
                     rpos += __popcll(am);
                     ppos += kRunLen * __popcll(am) - __popcll(d0) - 2 * __popcll(d1);
@@ -573,7 +761,7 @@ __global__ __launch_bounds__(kRunsBuildThreads) void k_runs_build(const uint32_t
     }
 }
 
-// Work units of the run-based kernel (one block).  With P = max(ceil(total
+// Work units of the run-based kernel (by one block).  With P = max(ceil(total
 // runs / kRunsSplit), kRunsMinPiece), a tile of c runs becomes ceil(c / P)
 // pieces (an empty tile none), so at most ntiles + kRunsSplit units exist.
 // Tiles cut into pieces or holding more than twice the mean run count go
@@ -584,11 +772,10 @@ __global__ __launch_bounds__(kRunsBuildThreads) void k_runs_build(const uint32_t
 // its CU, and splitting keeps one tile from outweighing a CU's share of the
 // step.  Every loop that contains a block scan has the same trip count in all
 // threads.
-constexpr int kOrderThreads = 1024;
 constexpr int kRankMax = 1024;
-__global__ __launch_bounds__(kOrderThreads) void k_unit_list(int32_t *runs, int np, int ntiles)
+__device__ __forceinline__ void unit_list(int32_t *runs, int np, int ntiles)
 {
-    __shared__ uint32_t sh[kOrderThreads / 64 + 1];
+    __shared__ uint32_t sh[kPermThreads / 64 + 1];
     __shared__ int rk_tile[kRankMax];
     __shared__ int rk_cnt[kRankMax];
     __shared__ int rk_k[kRankMax];
@@ -645,12 +832,15 @@ __global__ __launch_bounds__(kOrderThreads) void k_unit_list(int32_t *runs, int 
         by_rank[rank] = i;
     }
     __syncthreads();
-    uint32_t nranked;
-    {
-        const int i = threadIdx.x < nh ? by_rank[threadIdx.x] : 0;
-        const uint32_t k = threadIdx.x < nh ? (uint32_t)rk_k[i] : 0u;
-        const uint32_t at = block_exclusive_scan(k, sh, nranked);
-        if (threadIdx.x < nh) emit(at, rk_tile[i], (int)k);
+    uint32_t nranked = 0;
+    for (int r0 = 0; r0 < nh; r0 += blockDim.x) {
+        const int r = r0 + (int)threadIdx.x;
+        const int i = r < nh ? by_rank[r] : 0;
+        const uint32_t k = r < nh ? (uint32_t)rk_k[i] : 0u;
+        uint32_t tot;
+        const uint32_t at = nranked + block_exclusive_scan(k, sh, tot);
+        if (r < nh) emit(at, rk_tile[i], (int)k);
+        nranked += tot;
     }
     // every other non-empty tile in index order
     uint32_t hb = 0;
@@ -671,10 +861,15 @@ __global__ __launch_bounds__(kOrderThreads) void k_unit_list(int32_t *runs, int 
     if (threadIdx.x == 0) runs[runs_count_at(np, ntiles)] = (int32_t)min(lb, cap);
 }
 
+// (an item without particles)
+__global__ __launch_bounds__(kPermThreads) void k_unit_list(int32_t *runs, int np, int ntiles) { unit_list(runs, np, ntiles); }
+
 __global__ void k_fill_i32(int32_t *p, int n, int v)
 {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = v;
 }
+
+int64_t sort_hist_entries(int64_t np) { return kSortHist(np); }
 
 static int bits_for(uint64_t count)
 {
@@ -688,32 +883,88 @@ static int bits_for(uint64_t count)
 // Digits of kMaxDigitBits bits, the last pass taking only the bits left.
 // (Wider digits, 11 bits in two passes for 21-bit keys, were slower: the
 // per-block digit tables cost more than the pass they save.)
-static int radix_passes(Ctx *c, int np, int src, bool identity, int bits)
+// first_hist: the first pass's histogram is in c->hist already.  With few
+// blocks the scatter sums the histogram up itself instead of three scan
+// launches.
+constexpr int kRawBlocks = 128;
+static int radix_passes(Ctx *c, int np, int src, bool identity, int bits, bool first_hist)
 {
     hipStream_t s = c->stream;
-    const int nblocks = (np + kPerBlock - 1) / kPerBlock;
+    const int nblocks = sort_blocks(np);
+    const bool big = sort_per(np) == kPerThread;
+    const bool raw = nblocks <= kRawBlocks;
     bits = std::max(bits, 1);
     const int width = kMaxDigitBits;
     const int npass = (bits + width - 1) / width;
     for (int pass = 0; pass < npass; ++pass) {
         const int shift = width * pass;
         const int dbits = std::min(width, bits - shift);
-        const long m = (long)nblocks << dbits;
-        const long seg = (m + kScanBlocks - 1) / kScanBlocks;
-        const int nparts = (int)((m + seg - 1) / seg);
-        uint32_t *part = c->hist_scan + m;
-        hipLaunchKernelGGL(k_hist, dim3(nblocks), dim3(kSortThreads), 0, s, c->keys[src], np, shift, dbits, nblocks,
-                           c->hist);
-        hipLaunchKernelGGL(k_scan_reduce, dim3(nparts), dim3(256), 0, s, c->hist, m, seg, part);
-        hipLaunchKernelGGL(k_scan_parts, dim3(1), dim3(kScanBlocks), 0, s, part, nparts);
-        hipLaunchKernelGGL(k_scan_apply, dim3(nparts), dim3(256), 0, s, c->hist, m, seg, part, c->hist_scan);
-        hipLaunchKernelGGL(k_scatter, dim3(nblocks), dim3(kSortThreads), (size_t)(kSortWaves << dbits) * 4, s,
+        if (pass > 0 || !first_hist) {
+            hipLaunchKernelGGL(big ? k_hist<kPerThread> : k_hist<kPerThreadSmall>, dim3(nblocks), dim3(kSortThreads), 0, s, c->keys[src], np, shift, dbits, nblocks,
+                               c->hist);
+            c->stats[0]++;
+        }
+        if (!raw) {
+            const long m = (long)nblocks << dbits;
+            const long seg = (m + kScanBlocks - 1) / kScanBlocks;
+            const int nparts = (int)((m + seg - 1) / seg);
+            uint32_t *part = c->hist_scan + m;
+            hipLaunchKernelGGL(k_scan_reduce, dim3(nparts), dim3(256), 0, s, c->hist, m, seg, part);
+            hipLaunchKernelGGL(k_scan_parts, dim3(1), dim3(kScanBlocks), 0, s, part, nparts);
+            hipLaunchKernelGGL(k_scan_apply, dim3(nparts), dim3(256), 0, s, c->hist, m, seg, part, c->hist_scan);
+            c->stats[0] += 3;
+        }
+        hipLaunchKernelGGL(big ? k_scatter<kPerThread> : k_scatter<kPerThreadSmall>, dim3(nblocks), dim3(kSortThreads), (size_t)(kSortWaves << dbits) * 4, s,
                            c->keys[src], (identity && pass == 0) ? (const uint32_t *)nullptr : c->idx[src],
-                           c->keys[1 - src], c->idx[1 - src], np, shift, dbits, nblocks, c->hist_scan);
-        c->stats[0] += 5;
+                           c->keys[1 - src], c->idx[1 - src], np, shift, dbits, nblocks, raw ? c->hist : c->hist_scan,
+                           raw);
+        c->stats[0]++;
         src = 1 - src;
     }
     return src;
+}
+
+// Keys of a group's particles by `key_mode`, sorted: the buffer index that holds
+// them and their sources.
+static int sort_keys(Ctx *c, const SortGroup &g, uint64_t keys)
+{
+    const int bits = std::max(bits_for(keys), 1), nblocks = sort_blocks(g.total);
+    hipLaunchKernelGGL(sort_per(g.total) == kPerThread ? k_keys<kPerThread> : k_keys<kPerThreadSmall>, dim3(nblocks), dim3(kSortThreads), 0, c->stream, g, c->keys[0],
+                       std::min(kMaxDigitBits, bits), nblocks, c->hist);
+    c->stats[0]++;
+    return radix_passes(c, g.total, 0, true, bits, true);
+}
+
+// The group of the items args[0 .. count), each with particles; the number of
+// distinct keys.
+static uint64_t make_group(const SortArgs *args, int count, int key_mode, SortGroup &g)
+{
+    memset(&g, 0, sizeof(g));
+    g.count = count;
+    g.prec = args[0].prec;
+    g.ndim = args[0].ndim;
+    g.key_mode = key_mode;
+    uint64_t keys = 0;
+    for (int i = 0; i < count; ++i) {
+        const SortArgs &a = args[i];
+        SortItem &s = g.it[i];
+        for (int k = 0; k < 3; ++k) {
+            s.n[k] = a.n[k];
+            s.tile[k] = a.tile[k];
+            s.x[k] = a.x[k];
+        }
+        s.np = a.np;
+        s.ntiles = a.ntiles;
+        s.cell = a.cell;
+        s.tile_start = a.tile_start;
+        s.runs = a.runs;
+        g.kbase[i] = (uint32_t)keys;
+        g.base[i + 1] = g.base[i] + a.np;
+        g.tbase[i + 1] = g.tbase[i] + a.ntiles;
+        keys += (uint64_t)a.ntiles * (key_mode == PL_KEY_TILE ? 1 : a.tile[0] * a.tile[1] * a.tile[2]);
+    }
+    g.total = g.base[count];
+    return keys;
 }
 
 int bins_buffer(int ntiles)
@@ -737,80 +988,100 @@ hipError_t launch_bins(Ctx *c, const ItemDesc &it)
     a.np = it.np;
     a.ntiles = it.ntiles;
     a.cell = it.cell;
-    const int grid_e = std::min((a.np + 255) / 256, 16 * c->num_cu);
-    hipLaunchKernelGGL(k_keys, dim3(grid_e), dim3(256), 0, c->stream, a, c->keys[0]);
-    const int src = radix_passes(c, a.np, 0, true, bits_for((uint64_t)a.ntiles));
-    hipLaunchKernelGGL(k_tile_start, dim3(grid_e), dim3(256), 0, c->stream, c->keys[src], a.np, 0, 1, a.ntiles,
-                       it.tile_start);
-    c->stats[0] += 2;
+    a.tile_start = it.tile_start;
+    SortGroup g;
+    const uint64_t keys = make_group(&a, 1, PL_KEY_TILE, g);
+    const int src = sort_keys(c, g, keys);
+    hipLaunchKernelGGL(k_tile_start, dim3(std::min((a.np + 255) / 256, 16 * c->num_cu)), dim3(256), 0, c->stream, g,
+                       c->keys[src], 0, (int)PL_KEY_TILE);
+    c->stats[0]++;
     return hipGetLastError();
 }
 
-hipError_t launch_sort(Ctx *c, const SortArgs &a)
+static hipError_t sort_empty(Ctx *c, const SortArgs &a)
+{
+    const int grid = std::max(1, (a.ntiles + 256) / 256);
+    hipLaunchKernelGGL(k_fill_i32, dim3(grid), dim3(256), 0, c->stream, a.tile_start, a.ntiles + 1, 0);
+    c->stats[0]++;
+    if (a.runs) {
+        hipLaunchKernelGGL(k_fill_i32, dim3(grid), dim3(256), 0, c->stream, a.runs, a.ntiles, 0);
+        hipLaunchKernelGGL(k_unit_list, dim3(1), dim3(kPermThreads), 0, c->stream, a.runs, 0, a.ntiles);
+        c->stats[0] += 2;
+    }
+    return hipGetLastError();
+}
+
+static hipError_t sort_group(Ctx *c, const SortArgs *args, int count)
 {
     hipStream_t s = c->stream;
-    if (a.np == 0) {
-        hipLaunchKernelGGL(k_fill_i32, dim3(std::max(1, (a.ntiles + 256) / 256)), dim3(256), 0, s, a.tile_start,
-                           a.ntiles + 1, 0);
-        c->stats[0]++;
-        if (a.runs) {
-            hipLaunchKernelGGL(k_fill_i32, dim3(std::max(1, (a.ntiles + 256) / 256)), dim3(256), 0, s, a.runs,
-                               a.ntiles, 0);
-            hipLaunchKernelGGL(k_unit_list, dim3(1), dim3(kOrderThreads), 0, s, a.runs, 0, a.ntiles);
-            c->stats[0] += 2;
-        }
-        return hipGetLastError();
-    }
-    const int per_tile_cells = a.tile[0] * a.tile[1] * a.tile[2];
-    const int grid_e = std::min((a.np + 255) / 256, 16 * c->num_cu);
-    int src, shift = 0, div = 1;
-    if (a.key_mode == PL_KEY_TILE_RANK) {
-        // phase 1: stable sort by (tile, cell); phase 2: stable sort by
-        // (tile, rank in cell, cell) on top of it
-        SortArgs b = a;
-        b.key_mode = PL_KEY_TILE_CELL;
-        hipLaunchKernelGGL(k_keys, dim3(grid_e), dim3(256), 0, s, b, c->keys[0]);
-        src = radix_passes(c, a.np, 0, true, bits_for((uint64_t)a.ntiles * per_tile_cells));
+    const int mode = args[0].key_mode;
+    SortGroup g;
+    const int grid_of = 16 * c->num_cu;
+    int src, shift = 0;
+    if (mode == PL_KEY_TILE_RANK) {
+        // (one item) phase 1: stable sort by (tile, cell); phase 2: stable sort
+        // by (tile, rank in cell, cell) on top of it
+        const SortArgs &a = args[0];
+        const int per_tile_cells = a.tile[0] * a.tile[1] * a.tile[2], grid_e = std::min((a.np + 255) / 256, grid_of);
+        src = sort_keys(c, g, make_group(args, 1, PL_KEY_TILE_CELL, g));
         const int cb = bits_for((uint64_t)per_tile_cells), tb = bits_for((uint64_t)a.ntiles);
         const int rb = std::min(10, 32 - tb - cb);
         hipLaunchKernelGGL(k_cell_start, dim3(grid_e), dim3(256), 0, s, c->keys[src], a.np, c->cell_start);
         hipLaunchKernelGGL(k_rank_keys, dim3(grid_e), dim3(256), 0, s, c->keys[src], a.np, c->cell_start,
                            per_tile_cells, cb, rb);
-        src = radix_passes(c, a.np, src, false, tb + rb + cb);
+        c->stats[0] += 2;
+        src = radix_passes(c, a.np, src, false, tb + rb + cb, false);
         shift = rb + cb;
-        c->stats[0] += 3;
     } else {
-        hipLaunchKernelGGL(k_keys, dim3(grid_e), dim3(256), 0, s, a, c->keys[0]);
-        div = a.key_mode == PL_KEY_TILE ? 1 : per_tile_cells;
-        src = radix_passes(c, a.np, 0, true, bits_for((uint64_t)a.ntiles * div));
+        const uint64_t keys = make_group(args, count, mode, g);
+        src = sort_keys(c, g, keys);
+    }
+    const bool runs = args[0].runs != nullptr, order = mode == PL_KEY_TILE_RUN;
+    if (order && !runs) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_tile_start, dim3(std::min((g.total + 255) / 256, grid_of)), dim3(256), 0, s, g, c->keys[src], shift,
+                       mode);
+    c->stats[0]++;
+    if (runs) {
+        // one block per tile: a crowded tile's rounds do not hold up others
+        hipLaunchKernelGGL(k_runs_build, dim3(std::max(g.tbase[g.count], 1)), dim3(kRunsBuildThreads), 0, s, g, c->keys[src],
+                           order ? c->idx[1 - src] : nullptr);
         c->stats[0]++;
     }
-    if (a.key_mode == PL_KEY_TILE_RUN) {
-        // run order: tile offsets and the run table from the tile+cell order,
-        // then every array moved straight into run order
-        if (!a.runs) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_tile_start, dim3(grid_e), dim3(256), 0, s, c->keys[src], a.np, 0, div, a.ntiles,
-                           a.tile_start);
-        // one block per tile: a crowded tile's rounds do not hold up others
-        hipLaunchKernelGGL(k_runs_build, dim3(std::max(a.ntiles, 1)), dim3(kRunsBuildThreads), 0, s,
-                           c->keys[src], a.np, per_tile_cells, a.ntiles, a.tile_start, a.runs, c->idx[1 - src]);
-        permute_arrays(c, a, c->idx[1 - src], c->idx[src], grid_e);
-        hipLaunchKernelGGL(k_unit_list, dim3(1), dim3(kOrderThreads), 0, s, a.runs, a.np, a.ntiles);
-        c->stats[0] += 3;
-        return hipGetLastError();
-    }
-    permute_arrays(c, a, c->idx[src], nullptr, grid_e);
-    hipLaunchKernelGGL(k_tile_start, dim3(grid_e), dim3(256), 0, s, c->keys[src], a.np, shift, div, a.ntiles,
-                       a.tile_start);
-    c->stats[0]++;
-    if (a.runs) {
-        // keys are tile * cells_per_tile + cell in tile (PL_KEY_TILE_CELL)
-        hipLaunchKernelGGL(k_runs_build, dim3(std::max(a.ntiles, 1)), dim3(kRunsBuildThreads), 0, s,
-                           c->keys[src], a.np, per_tile_cells, a.ntiles, a.tile_start, a.runs, nullptr);
-        hipLaunchKernelGGL(k_unit_list, dim3(1), dim3(kOrderThreads), 0, s, a.runs, a.np, a.ntiles);
-        c->stats[0] += 2;
-    }
+    // run order: every array moved from its place before the sort straight there
+    if (order) permute_arrays(c, g, args, c->idx[1 - src], c->idx[src], true);
+    else permute_arrays(c, g, args, c->idx[src], nullptr, runs);
     return hipGetLastError();
+}
+
+hipError_t launch_sort(Ctx *c, const SortArgs *args, int count, int64_t cap)
+{
+    for (int i0 = 0, i1 = 0; i0 < count; i0 = i1) {
+        i1 = i0 + 1;
+        if (args[i0].np == 0) {
+            const hipError_t e = sort_empty(c, args[i0]);
+            if (e != hipSuccess) return e;
+            continue;
+        }
+        // the items that follow join while the scratch holds their particles, the
+        // keys fit 32 bits and the digits' passes stay as many
+        auto keys_of = [&](const SortArgs &a) -> uint64_t {
+            return (uint64_t)a.ntiles * (a.key_mode == PL_KEY_TILE ? 1 : a.tile[0] * a.tile[1] * a.tile[2]);
+        };
+        int64_t np = args[i0].np;
+        uint64_t keys = keys_of(args[i0]), most = keys;
+        auto passes = [](uint64_t k) { return (std::max(bits_for(k), 1) + kMaxDigitBits - 1) / kMaxDigitBits; };
+        while (args[i0].key_mode != PL_KEY_TILE_RANK && i1 < count && i1 - i0 < kGroup && args[i1].np > 0) {
+            const uint64_t k = keys_of(args[i1]);
+            if (np + args[i1].np > cap || keys + k > (1ull << 32) || passes(keys + k) > passes(std::max(most, k)) + 1) break;
+            np += args[i1].np;
+            keys += k;
+            most = std::max(most, k);
+            ++i1;
+        }
+        const hipError_t e = sort_group(c, args + i0, i1 - i0);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
@@ -821,7 +1092,7 @@ hipError_t launch_sort(Ctx *c, const SortArgs &a)
 // ---------------------------------------------------------------------------
 
 constexpr int64_t kNaNp = PL_NOALLOC_MAX_NP;
-constexpr int64_t kNaHist = (((kNaNp + kPerBlock - 1) / kPerBlock) << kMaxDigitBits) + 1024;
+constexpr int64_t kNaHist = kSortHist(kNaNp);
 constexpr size_t kNaBytes = (size_t)(4 * kNaNp + 2 * kNaHist) * sizeof(uint32_t);
 
 static __device__ __align__(256) unsigned char scratch[kNaBytes];
@@ -831,9 +1102,10 @@ static std::mutex na_mu;
 static void *na_ptr[kNaDevices];       // device address of `scratch` on each device
 static int na_cu[kNaDevices];
 
-hipError_t launch_sort_noalloc(Ctx *c, const SortArgs &a)
+hipError_t launch_sort_noalloc(Ctx *c, const SortArgs *a, int count)
 {
-    if (a.np > kNaNp) return hipErrorInvalidValue;
+    for (int i = 0; i < count; ++i)
+        if (a[i].np > kNaNp) return hipErrorInvalidValue;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -867,7 +1139,7 @@ hipError_t launch_sort_noalloc(Ctx *c, const SortArgs &a)
     c->hist_scan = w + 4 * kNaNp + kNaHist;
     c->hist_cap = kNaHist;
     c->cell_start = nullptr;           // PL_KEY_TILE_RANK is refused before this point
-    return launch_sort(c, a);
+    return launch_sort(c, a, count, kNaNp);
 }
 
 }  // namespace pl

@@ -385,8 +385,7 @@ pl_status run_call(Ctx *c, pl_item *items, int nitems, double dt, uint32_t flags
     if (st != PL_OK) return st;
 
     auto enqueue = [&](const ItemDesc *table) -> pl_status {
-        for (const SortArgs &a : sargs)
-            if (launch_sort(c, a) != hipSuccess) return PL_EHIP;
+        if (!sargs.empty() && launch_sort(c, sargs.data(), (int)sargs.size(), c->max_np) != hipSuccess) return PL_EHIP;
         return enqueue_step(c, table, host, total, flags, push, deposit);
     };
     // host bookkeeping once the launches are queued: the sort flipped the sets,
@@ -537,8 +536,7 @@ pl_status pl_part_init(pl_ctx **out, const pl_init_desc *d)
 
     const size_t mi = (size_t)d->max_items;
     const size_t np = (size_t)std::max<int64_t>(d->max_np, 1);
-    const size_t nblocks = (np + 8191) / 8192;
-    c->hist_cap = (int64_t)((nblocks << kMaxDigitBits) + 1024);    // digit-major counts of one radix pass
+    c->hist_cap = sort_hist_entries((int64_t)np);                  // digit-major counts of one radix pass
     bool ok = hipMalloc(&c->table, mi * sizeof(ItemDesc)) == hipSuccess &&
               hipMalloc(&c->counters, kCounterSlots * sizeof(unsigned)) == hipSuccess &&
               hipMalloc(&c->errflags, 4 * sizeof(int)) == hipSuccess &&
@@ -678,8 +676,8 @@ pl_status pl_part_sort(pl_ctx *ctx, pl_item *items, int nitems)
         pl_status st = sort_args(c, items[i], args[i]);
         if (st != PL_OK) return st;
     }
+    if (launch_sort(c, args.data(), nitems, c->max_np) != hipSuccess) return PL_EHIP;
     for (int i = 0; i < nitems; ++i) {
-        if (launch_sort(c, args[i]) != hipSuccess) return PL_EHIP;
         items[i].p.cur = 1 - items[i].p.cur;
         c->stats[3]++;
         const void *fp = items[i].p.fp[0];
@@ -807,12 +805,10 @@ pl_status pl_sort_noalloc(const pl_init_desc *d, pl_item *items, int nitems)
             st = sort_args(&c, items[i], a[i - i0]);
             if (st != PL_OK) return st;
         }
-        for (int i = i0; i < i1; ++i) {
-            hipError_t e = launch_sort_noalloc(&c, a[i - i0]);
-            if (e == hipErrorInvalidDevice) return PL_EUNSUPPORTED;
-            if (e != hipSuccess) return PL_EHIP;
-            items[i].p.cur = 1 - items[i].p.cur;
-        }
+        hipError_t e = launch_sort_noalloc(&c, a, i1 - i0);
+        if (e == hipErrorInvalidDevice) return PL_EUNSUPPORTED;
+        if (e != hipSuccess) return PL_EHIP;
+        for (int i = i0; i < i1; ++i) items[i].p.cur = 1 - items[i].p.cur;
     }
     return PL_OK;
 }

@@ -236,7 +236,10 @@ struct SortArgs {
     const double *rsrc[2];
     double *rdst[2];
 };
-hipError_t launch_sort(Ctx *c, const SortArgs &a);
+// Items one after another, several together where `cap` particles of scratch
+// hold them.
+hipError_t launch_sort(Ctx *c, const SortArgs *a, int count, int64_t cap);
+int64_t sort_hist_entries(int64_t np);         // digit counts that its passes need
 // Indices of an item's particles by tile (stable) into the item's idx, offsets
 // of the tiles into its tile_start; idx_buffer: which of the context's index
 // buffers the passes leave them in.
@@ -244,6 +247,6 @@ int bins_buffer(int ntiles);
 hipError_t launch_bins(Ctx *c, const ItemDesc &it);
 // The same sort with its scratch in the library's fixed device array (set up
 // on the first call on each device); c supplies the stream only.
-hipError_t launch_sort_noalloc(Ctx *c, const SortArgs &a);
+hipError_t launch_sort_noalloc(Ctx *c, const SortArgs *a, int count);
 
 }  // namespace pl
