@@ -42,7 +42,7 @@ namespace pl {
 
 enum LocalMode { LM_FUSED = 0, LM_PUSH = 1, LM_DEP = 2 };
 
-constexpr int kLocalThreads = 512;
+constexpr int kLocalThreads = 512, kLocalSmall = 256;
 constexpr int kLocalRounds = 5;        // rounds of runs counted together (11 bits each in 64)
 constexpr int kLocalMaxCells = 2047;   // cells of a tile and its ring: fits 11 bits
 constexpr int kLocalMaxCap = 8192;     // particles of a chunk: 13 bits of a run entry, 2 bits of length
@@ -265,7 +265,7 @@ __device__ __forceinline__ void fetch_indexed(const UnitC<PREC> &U, const int pi
 }
 
 // One chunk of a tile.
-template <int PREC, int SHAPE, int DIM, int KIND, int MODE, int TS, int CHS>
+template <int PREC, int SHAPE, int DIM, int KIND, int MODE, int TS, int CHS, int NT>
 __device__ __forceinline__ void local_unit(const ItemDesc &I, int t, int pbeg, int pend, int cap, unsigned flags,
                                            int ctl_at, unsigned char *smem, unsigned *counter, bool &pre, int &err)
 {
@@ -350,7 +350,7 @@ __device__ __forceinline__ void local_unit(const ItemDesc &I, int t, int pbeg, i
         __syncthreads();
         // this thread's cells: particles before them, runs before them in each
         // of the first rounds, and further runs
-        constexpr int CPT = (kLocalMaxCells + kLocalThreads - 1) / kLocalThreads;
+        constexpr int CPT = (kLocalMaxCells + NT - 1) / NT;
         const int cpt = (E + bd - 1) / bd, c0 = (int)threadIdx.x * cpt;
         unsigned n[CPT];
         unsigned tot = 0, rest = 0;
@@ -485,8 +485,8 @@ __device__ __forceinline__ void local_unit(const ItemDesc &I, int t, int pbeg, i
     if constexpr (GROUP) flush_unit<PREC, DIM, CHS>(U, G, S.lds_d);
 }
 
-template <int PREC, int SHAPE, int DIM, int KIND, int MODE, int TS, int CHS>
-__global__ __launch_bounds__(kLocalThreads) __attribute__((amdgpu_waves_per_eu(MODE == LM_PUSH ? 4 : 2, MODE == LM_PUSH ? 8 : 2)))
+template <int PREC, int SHAPE, int DIM, int KIND, int MODE, int TS, int CHS, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MODE == LM_PUSH ? 4 : 2, MODE == LM_PUSH ? 8 : 2)))
 void k_local(const ItemDesc *__restrict__ items, int nitems, int total_units, unsigned *counter, int *errflags,
              unsigned flags, int cap, int ctl_at)
 {
@@ -516,7 +516,7 @@ void k_local(const ItemDesc *__restrict__ items, int nitems, int total_units, un
         if (j < 0 || j >= nch) continue;                      // uniform: an empty slot
         const int pbeg = beg + (int)((long long)(end - beg) * j / nch);
         const int pend = beg + (int)((long long)(end - beg) * (j + 1) / nch);
-        local_unit<PREC, SHAPE, DIM, KIND, MODE, TS, CHS>(I, t, pbeg, pend, cap, flags, ctl_at, smem_raw, counter, pre,
+        local_unit<PREC, SHAPE, DIM, KIND, MODE, TS, CHS, NT>(I, t, pbeg, pend, cap, flags, ctl_at, smem_raw, counter, pre,
                                                                   err);
     }
     runs_latch(err, errflags);
@@ -530,12 +530,14 @@ void k_local(const ItemDesc *__restrict__ items, int nitems, int total_units, un
 using LocalKernel = void (*)(const ItemDesc *, int, int, unsigned *, int *, unsigned, int, int);
 
 template <int PREC>
-static LocalKernel pick_local(int shape, int dim, int kind, int mode, int ts, int chs)
+static LocalKernel pick_local(int shape, int dim, int kind, int mode, int ts, int chs, int nt)
 {
-#define PL_L(S, D, K, M, TS_, CHS_) \
-    if (shape == S && dim == D && kind == K && mode == M && ts == TS_ && chs == CHS_) \
-        return k_local<PREC, S, D, K, M, TS_, CHS_>;
-#define PL_LM(S, D, K) PL_L(S, D, K, LM_FUSED, 0, 0) PL_L(S, D, K, LM_PUSH, 0, 0) PL_L(S, D, K, LM_DEP, 0, 0)
+#define PL_LN(S, D, K, M, TS_, CHS_, NT_) \
+    if (shape == S && dim == D && kind == K && mode == M && ts == TS_ && chs == CHS_ && nt == NT_) \
+        return k_local<PREC, S, D, K, M, TS_, CHS_, NT_>;
+#define PL_L(S, D, K, M, TS_, CHS_) PL_LN(S, D, K, M, TS_, CHS_, kLocalThreads)
+#define PL_LM(S, D, K) PL_L(S, D, K, LM_FUSED, 0, 0) PL_L(S, D, K, LM_PUSH, 0, 0) PL_L(S, D, K, LM_DEP, 0, 0) \
+    PL_LN(S, D, K, LM_FUSED, 0, 0, kLocalSmall) PL_LN(S, D, K, LM_DEP, 0, 0, kLocalSmall)
 #define PL_LG(S, D) PL_LM(S, D, PL_LORENTZ) PL_LM(S, D, PL_DUST) PL_L(S, D, PL_TRACER, LM_PUSH, 0, 0)
     PL_LG(PL_TSC, 3) PL_LG(PL_TSC, 2) PL_LG(PL_CIC, 3) PL_LG(PL_CIC, 2)
 #define PL_LT(TS_) \
@@ -544,10 +546,15 @@ static LocalKernel pick_local(int shape, int dim, int kind, int mode, int ts, in
     PL_L(PL_TSC, 3, PL_DUST, LM_DEP, TS_, 2) PL_L(PL_TSC, 3, PL_LORENTZ, LM_PUSH, TS_, 0) \
     PL_L(PL_TSC, 3, PL_DUST, LM_PUSH, TS_, 0) PL_L(PL_TSC, 3, PL_TRACER, LM_PUSH, TS_, 0)
     PL_LT(1) PL_LT(2)
+#define PL_LS(K, M, CHS_) PL_LN(PL_TSC, 3, K, M, 4, CHS_, kLocalSmall)
+    PL_LS(PL_LORENTZ, LM_FUSED, 1) PL_LS(PL_LORENTZ, LM_FUSED, 3) PL_LS(PL_LORENTZ, LM_DEP, 1)
+    PL_LS(PL_DUST, LM_FUSED, 2) PL_LS(PL_DUST, LM_DEP, 2)
+#undef PL_LS
 #undef PL_LT
 #undef PL_LG
 #undef PL_LM
 #undef PL_L
+#undef PL_LN
     return nullptr;
 }
 
@@ -567,16 +574,20 @@ static LocalLds local_item_lds(const Ctx *c, const ItemDesc &it, int mode, int h
 // Launch configuration for the items of one species kind: field halo,
 // particles per chunk, LDS bytes.  False when a tile has too many cells or its
 // LDS does not fit with chunks of at least kLocalMinCap particles.
-// A chunk of fewer than two particles per thread does not pay for its grouping
-// (4096 particles in 32 tiles: 266 us for ten steps against 251 us of the
-// one-particle-per-thread kernel).
+// Fewer particles per tile than threads do not pay for the grouping (4096
+// particles in 32 tiles: 266 us for ten steps against 251 us of the
+// one-particle-per-thread kernel); up to kLocalSmallPerTile a block of 256
+// threads holds enough of a tile's runs, and the phases of two blocks on a CU
+// overlap (float64 by tile key, 8 x 4 x 4 tiles of 768 particles: eight
+// steps and the sort 5.89 ms with 512 threads, 4.16 ms with 256).
 constexpr int kLocalMinCap = 1024;
-constexpr int kLocalMinPerTile = 512;
+constexpr int kLocalSmallPerTile = 2048;
 
 template <int PREC>
 bool local_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, bool push, bool deposit, LocalPlan &pl)
 {
     pl = LocalPlan{};
+    pl.nt = kLocalThreads;
     if (nitems < 1) return false;
     const int kind = host[0].kind;
     const bool dep = deposit && kind != PL_TRACER;
@@ -601,16 +612,26 @@ bool local_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, bool push, 
         pl.lds = bytes(pl.hf, pl.cap);
         return pl.lds <= (size_t)c->lds_max;
     }
-    // few particles per tile: one per thread and no grouping costs less
     int64_t np = 0, nt = 0;
     for (int i = 0; i < nitems; ++i) {
         np += host[i].np;
         nt += host[i].ntiles;
     }
-    if (!host[0].idx && np < kLocalMinPerTile * nt) return false;
+    pl.hf = 1;
+    // tiles of few particles whose LDS lets two blocks share a CU: smaller blocks
+    if (np < kLocalSmallPerTile * nt) {
+        pl.nt = kLocalSmall;
+        for (pl.cap = 2048; pl.cap >= kLocalMinCap; pl.cap -= 256) {
+            pl.lds = bytes(1, pl.cap);
+            if (2 * pl.lds <= (size_t)c->lds_max) break;
+        }
+        if (pl.cap < kLocalMinCap) pl.nt = kLocalThreads;
+    }
+    // few particles per thread: no grouping costs less
+    if (!host[0].idx && np < pl.nt * nt) return false;
+    if (pl.nt == kLocalSmall) return true;
     // chunks: what the LDS holds, and no more than leave each CU one
     const int64_t share = (np / c->num_cu + 255) / 256 * 256;
-    pl.hf = 1;
     pl.cap = (int)std::min<int64_t>(kLocalMaxCap, std::max<int64_t>(kLocalMinCap, share));
     for (; pl.cap >= kLocalMinCap; pl.cap -= 256) {
         pl.lds = bytes(1, pl.cap);
@@ -628,7 +649,8 @@ hipError_t launch_local_impl(Ctx *c, const ItemDesc *table, const ItemDesc *host
     if (units <= 0) return hipSuccess;
     const int kind = host[0].kind;
     if (c->d.shape == PL_TSC && c->d.ndim == 3) {
-        for (int cand = 1; cand <= 2 && ts == 0; ++cand) {
+        for (int cand : {1, 2, 4}) {
+            if (ts || (cand == 4) != (pl.nt == kLocalSmall)) continue;
             bool all = true;
             for (int i = 0; i < nitems; ++i)
                 for (int a = 0; a < 3; ++a) all = all && host[i].tile[a] == ts_dim(cand, a);
@@ -645,12 +667,12 @@ hipError_t launch_local_impl(Ctx *c, const ItemDesc *table, const ItemDesc *host
             if (!chs) ts = 0;
         }
     }
-    LocalKernel k = pick_local<PREC>(c->d.shape, c->d.ndim, kind, pl.mode, ts, chs);
+    LocalKernel k = pick_local<PREC>(c->d.shape, c->d.ndim, kind, pl.mode, ts, chs, pl.nt);
     if (!k) return hipErrorInvalidValue;
     if (pl.hf == 2) sf |= SF_FHALO2;
     // every item's control words sit at one place: the end of the launch's LDS
-    const int grid = std::min(units, resident_blocks(c, (StepKernel)k, kLocalThreads, pl.lds));
-    hipLaunchKernelGGL(k, dim3(grid), dim3(kLocalThreads), pl.lds, c->stream, table, nitems, units, counter,
+    const int grid = std::min(units, resident_blocks(c, (StepKernel)k, pl.nt, pl.lds));
+    hipLaunchKernelGGL(k, dim3(grid), dim3(pl.nt), pl.lds, c->stream, table, nitems, units, counter,
                        c->errflags, sf, pl.cap, (int)pl.lds - 64);
     c->stats[0]++;
     return hipGetLastError();

@@ -135,10 +135,11 @@ __host__ __device__ constexpr int chs_slot(int CHS, int ch)
                     : CHS == 2 ? (ch == 0 ? 0 : (ch >= 4 && ch <= 6 ? ch - 3 : -1)) : CHS == 3 ? ch : -1;
 }
 
-// Compile-time tile shapes (TS): 0 runtime, 1 = 8x8x8, 2 = 8x8x4, 3 = 8x8 (2D).
+// Compile-time tile shapes (TS): 0 runtime, 1 = 8x8x8, 2 = 8x8x4, 3 = 8x8 (2D),
+// 4 = 8x4x4.
 __host__ __device__ constexpr int ts_dim(int TS, int a)
 {
-    return TS == 1 ? 8 : TS == 2 ? (a < 2 ? 8 : 4) : TS == 3 ? (a < 2 ? 8 : 1) : 0;
+    return TS == 1 ? 8 : TS == 2 ? (a < 2 ? 8 : 4) : TS == 3 ? (a < 2 ? 8 : 1) : TS == 4 ? (a < 1 ? 8 : 4) : 0;
 }
 
 // Tile geometry of one work unit in the LDS (one-cell halo on every side).

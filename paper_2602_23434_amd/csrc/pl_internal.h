@@ -176,9 +176,10 @@ struct RunsPlan {
 bool runs_plan(const Ctx *c, const ItemDesc *host, int nitems, RunsPlan &pl);
 
 // Launch configuration of a self-grouping tile kernel (k_local_impl.h) for
-// items of one species kind: mode, field halo, particles per chunk, LDS bytes.
+// items of one species kind: mode, field halo, particles per chunk, threads per
+// block, LDS bytes.
 struct LocalPlan {
-    int mode = 0, hf = 1, cap = 0;
+    int mode = 0, hf = 1, cap = 0, nt = 0;
     size_t lds = 0;
 };
 bool local_plan(const Ctx *c, const ItemDesc *host, int nitems, bool push, bool deposit, LocalPlan &pl);
