@@ -475,8 +475,8 @@ __device__ __forceinline__ void local_unit(const ItemDesc &I, int t, int pbeg, i
     }
     __syncthreads();
     // the next unit is claimed before the flush, whose atomics hide the round trip
-    if (threadIdx.x == 0) ctl[0] = (int)atomicAdd(counter, 1u);
-    pre = true;
+    pre = counter != nullptr;
+    if (pre && threadIdx.x == 0) ctl[0] = (int)atomicAdd(counter, 1u);
     if (KIND != PL_TRACER && do_sums && threadIdx.x < 8) {
         double sum = 0.0;
         for (int k = 0; k < kLocalSums; ++k) sum += S.sums[threadIdx.x * kLocalSums + k];
@@ -494,12 +494,19 @@ void k_local(const ItemDesc *__restrict__ items, int nitems, int total_units, un
     int *ctl = reinterpret_cast<int *>(smem_raw + ctl_at);
     int err = 0;
     bool pre = false;                      // uniform: ctl[0] already holds the next claim
-    for (;;) {
-        __syncthreads();
-        if (!pre && threadIdx.x == 0) ctl[0] = (int)atomicAdd(counter, 1u);
-        __syncthreads();
-        pre = false;
-        const int g = __builtin_amdgcn_readfirstlane(ctl[0]);
+    // a block for every unit: no claims (see claim_unit)
+    const bool direct = (int)gridDim.x >= total_units;
+    for (int turn = 0;; ++turn) {
+        int g = (int)blockIdx.x;
+        if (direct) {
+            if (turn > 0) break;                              // uniform
+        } else {
+            __syncthreads();
+            if (!pre && threadIdx.x == 0) ctl[0] = (int)atomicAdd(counter, 1u);
+            __syncthreads();
+            pre = false;
+            g = __builtin_amdgcn_readfirstlane(ctl[0]);
+        }
         if (g >= total_units) break;                          // uniform
         const ItemDesc &I = items[find_item(items, nitems, g)];
         const int32_t *ts = I.tile_start;
@@ -516,11 +523,12 @@ void k_local(const ItemDesc *__restrict__ items, int nitems, int total_units, un
         if (j < 0 || j >= nch) continue;                      // uniform: an empty slot
         const int pbeg = beg + (int)((long long)(end - beg) * j / nch);
         const int pend = beg + (int)((long long)(end - beg) * (j + 1) / nch);
-        local_unit<PREC, SHAPE, DIM, KIND, MODE, TS, CHS, NT>(I, t, pbeg, pend, cap, flags, ctl_at, smem_raw, counter, pre,
+        local_unit<PREC, SHAPE, DIM, KIND, MODE, TS, CHS, NT>(I, t, pbeg, pend, cap, flags, ctl_at, smem_raw,
+                                                                  direct ? nullptr : counter, pre,
                                                                   err);
     }
     runs_latch(err, errflags);
-    release_counter(counter);
+    release_counter(counter, total_units);
 }
 
 // ---------------------------------------------------------------------------

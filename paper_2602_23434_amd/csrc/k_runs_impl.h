@@ -1219,10 +1219,11 @@ static_assert(kRunsGroups == 64, "the unit table is one wave's scan");
 // dispatched to the XCDs in turn, so the blocks of one XCD mostly share a chunk
 // and find its field records in their L2; results do not depend on that
 // placement.  With fewer units than blocks every unit is claimed in `sub` parts
-// of its runs (of at least kRunsMinSub), so a small box fills the chip too: 32^3
-// cells with 2.6e5 particles have 64 tiles for 256 CUs (67 us per launch whole,
-// 56 us in parts: their flushes add to the same cells at once).
-constexpr int kRunsMinSub = 128;
+// of its runs (of at least kRunsMinSub), so a small box fills the chip too.
+// Every part flushes a whole tile, and a launch's atomics are bound at about
+// 5e10/s: 32^3 cells with 2.6e5 particles (64 tiles for 256 CUs) took 67 us per
+// launch whole, 56 us in four parts of 300 runs, 54.5 us in two.
+constexpr int kRunsMinSub = 512;
 __device__ __forceinline__ int queue_lo(int q, int total) { return (int)((long long)total * q / kQueues); }
 
 __device__ __forceinline__ int runs_sub(int total)
@@ -1315,7 +1316,14 @@ __device__ __forceinline__ void runs_next(const ItemDesc *__restrict__ items, in
     const int total = __builtin_amdgcn_readfirstlane(ctl[RC_ENDS + kRunsGroups - 1]), sub = runs_sub(total);
     int qi = __builtin_amdgcn_readfirstlane(ctl[RC_QI]);
     for (;;) {
-        const int g = runs_take(total * sub, counter, qi);
+        int g = -1;
+        if (total * sub <= (int)gridDim.x) {
+            // a block for every part: block b takes part b (see claim_unit)
+            if (qi == 0 && (int)blockIdx.x < total * sub) g = (int)blockIdx.x;
+            qi = kQueues;
+        } else {
+            g = runs_take(total * sub, counter, qi);
+        }
         if (g < 0) {
             unit[RU_ITEM] = -1;
             break;
@@ -1325,9 +1333,12 @@ __device__ __forceinline__ void runs_next(const ItemDesc *__restrict__ items, in
     ctl[RC_QI] = qi;
 }
 
-// The last block to finish resets the chunk counters for the next launch.
-__device__ __forceinline__ void release_queues(unsigned *counter)
+// The last block to finish resets the chunk counters for the next launch (a
+// launch with a block for every part claimed nothing).
+__device__ __forceinline__ void release_queues(unsigned *counter, const int *ctl)
 {
+    const int total = ctl[RC_ENDS + kRunsGroups - 1];
+    if (total * runs_sub(total) <= (int)gridDim.x) return;            // uniform
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();
@@ -1466,7 +1477,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         }
     }
     runs_latch(err, errflags);
-    release_queues(counter);
+    release_queues(counter, ctl);
 }
 
 // One persistent launch over the items of every species kind of a call: each
@@ -1499,7 +1510,7 @@ __global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2,
             runs_unit<PREC, SHAPE, DIM, PL_TRACER, HF, TS, 0>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err);
     }
     runs_latch(err, errflags);
-    release_queues(counter);
+    release_queues(counter, ctl);
 }
 
 // ---------------------------------------------------------------------------

@@ -31,10 +31,13 @@ template <int DIM> struct Stencil {
     static constexpr int SZ = DIM >= 3 ? 3 : 1;
 };
 
-// Work-unit claim shared by every persistent kernel: returns a wave-uniform
-// unit index, or -1 when the work is exhausted.
-__device__ __forceinline__ int claim_unit(unsigned *counter, int total, int *s_slot)
+// Work-unit claim: returns a wave-uniform unit index, or -1 when the work is
+// exhausted.  A launch with a block for every unit needs no counter (two round
+// trips of about a microsecond each in a launch that may take fifteen): block b
+// takes unit b.  turn: the block's claims so far.
+__device__ __forceinline__ int claim_unit(unsigned *counter, int total, int *s_slot, int &turn)
 {
+    if ((int)gridDim.x >= total) return turn++ == 0 && (int)blockIdx.x < total ? (int)blockIdx.x : -1;
     __syncthreads();
     if (threadIdx.x == 0) *s_slot = (int)atomicAdd(counter, 1u);
     __syncthreads();
@@ -43,8 +46,9 @@ __device__ __forceinline__ int claim_unit(unsigned *counter, int total, int *s_s
 }
 
 // The last block to finish resets the counter pair for the next launch.
-__device__ __forceinline__ void release_counter(unsigned *counter)
+__device__ __forceinline__ void release_counter(unsigned *counter, int total)
 {
+    if ((int)gridDim.x >= total) return;
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();
@@ -310,10 +314,10 @@ __global__ __launch_bounds__(512, (TILED && PREC == PL_F32_OFFSET && KIND != PL_
     const bool do_push = flags & SF_PUSH;
     const bool do_dep = flags & SF_DEPOSIT;
     const bool do_sums = flags & SF_SUMS;
-    int err = 0;
+    int err = 0, turn = 0;
 
     for (;;) {
-        int g = claim_unit(counter, total_units, s_unit);
+        int g = claim_unit(counter, total_units, s_unit, turn);
         if (g < 0) break;
         const int iti = find_item(items, nitems, g);
         const ItemDesc &I = items[iti];
@@ -576,7 +580,7 @@ __global__ __launch_bounds__(512, (TILED && PREC == PL_F32_OFFSET && KIND != PL_
         for (int off = 32; off > 0; off >>= 1) e |= __shfl_xor(e, off, 64);
         if ((threadIdx.x & 63) == 0) atomicOr(errflags, e);
     }
-    release_counter(counter);
+    release_counter(counter, total_units);
 }
 
 // ---------------------------------------------------------------------------
