@@ -2,6 +2,8 @@
 // pack / unpack kernels.
 #include <hip/hip_runtime.h>
 
+#include <string.h>
+
 #include <algorithm>
 #include <vector>
 
@@ -159,6 +161,60 @@ __global__ void k_zero_items(const ItemDesc *items)
     double *p = it.M[ch];
     const long n = (long)it.n[0] * it.n[1] * it.n[2];
     for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) p[i] = 0.0;
+}
+
+// The same for a call of a few items, whose descriptors come as arguments and
+// are written to the call's table: one launch instead of a copy from pinned
+// memory, an event and a launch.  zero = false: the table only.  A step of a
+// 32 x 32 box with 4096 particles took 23.9 us from call to call with the copy
+// and 18.8 us with this kernel (10 eager steps and a sort: 239 and 188 us).  More
+// items than fit 4 KB of arguments take the ring.
+template <int N> struct TableArgs {
+    ItemDesc d[N];
+};
+static_assert(sizeof(TableArgs<kTableArgs>) + 32 <= 4096, "kernel arguments");
+
+template <int N>
+__global__ void k_zero_table(TableArgs<N> t, int n, bool zero, ItemDesc *table)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        const int words = n * (int)(sizeof(ItemDesc) / 4);
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(&t);
+        for (int i = threadIdx.x; i < words; i += blockDim.x) reinterpret_cast<uint32_t *>(table)[i] = src[i];
+    }
+    if (!zero) return;
+    const ItemDesc &it = t.d[blockIdx.y / kMaxCh];
+    const int ch = blockIdx.y % kMaxCh;
+    if (it.kind == PL_TRACER || it.slot[ch] < 0) return;
+    double *p = it.M[ch];
+    const long cells = (long)it.n[0] * it.n[1] * it.n[2];
+    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < cells; i += (long)gridDim.x * blockDim.x) p[i] = 0.0;
+}
+
+template <int N>
+hipError_t launch_table_n(Ctx *c, const std::vector<ItemDesc> &host, bool zero, ItemDesc *table)
+{
+    TableArgs<N> t;
+    memset(&t, 0, sizeof(t));
+    long cells = 0;
+    for (size_t i = 0; i < host.size(); ++i) {
+        t.d[i] = host[i];
+        if (host[i].kind != PL_TRACER && host[i].nslot > 0)
+            cells = std::max(cells, (long)host[i].n[0] * host[i].n[1] * host[i].n[2]);
+    }
+    zero = zero && cells > 0;
+    const int channels = zero ? (int)host.size() * kMaxCh : 1;
+    const long per = std::min<long>((cells + 255) / 256, (8L * c->num_cu + channels - 1) / channels * 4);
+    const int gx = zero ? (int)std::max<long>(1, per) : 1;
+    hipLaunchKernelGGL(k_zero_table<N>, dim3(gx, channels), dim3(256), 0, c->stream, t, (int)host.size(), zero, table);
+    if (zero) c->stats[0]++;
+    return hipGetLastError();
+}
+
+hipError_t launch_table(Ctx *c, const std::vector<ItemDesc> &host, bool zero, ItemDesc *table)
+{
+    if (host.empty() || host.size() > (size_t)kTableArgs) return hipErrorInvalidValue;
+    return host.size() == 1 ? launch_table_n<1>(c, host, zero, table) : launch_table_n<kTableArgs>(c, host, zero, table);
 }
 
 hipError_t launch_zero(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc> &host)

@@ -320,9 +320,11 @@ pl_status build_table(Ctx *c, const pl_item *items, int nitems, double dt, Mode 
     return PL_OK;
 }
 
-// Stage the table through the pinned ring and queue its upload.
-pl_status upload_table(Ctx *c, const std::vector<ItemDesc> &host, ItemDesc *dst)
+// Queue the table of a call: as kernel arguments for a few items (with zero also
+// their moments' zeroing), else staged through the pinned ring.
+pl_status upload_table(Ctx *c, const std::vector<ItemDesc> &host, ItemDesc *dst, bool zero = false)
 {
+    if (host.size() <= (size_t)kTableArgs) return launch_table(c, host, zero, dst) == hipSuccess ? PL_OK : PL_EHIP;
     int slot = c->ring_pos;
     c->ring_pos = (c->ring_pos + 1) % Ctx::kRing;
     PL_TRY_HIP(hipEventSynchronize(c->ring_ev[slot]));
@@ -333,10 +335,17 @@ pl_status upload_table(Ctx *c, const std::vector<ItemDesc> &host, ItemDesc *dst)
     return PL_OK;
 }
 
-pl_status enqueue_step(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc> &host, int total_units,
-                       uint32_t flags, bool push, bool deposit)
+// upload: the table is not in device memory yet.
+pl_status enqueue_step(Ctx *c, ItemDesc *table, const std::vector<ItemDesc> &host, int total_units,
+                       uint32_t flags, bool push, bool deposit, bool upload)
 {
-    if (deposit && (flags & PL_ZERO_FIRST)) PL_TRY_HIP(launch_zero(c, table, host));
+    bool zero = deposit && (flags & PL_ZERO_FIRST);
+    if (upload) {
+        const pl_status st = upload_table(c, host, table, zero);
+        if (st != PL_OK) return st;
+        if (host.size() <= (size_t)kTableArgs) zero = false;          // done with the table
+    }
+    if (zero) PL_TRY_HIP(launch_zero(c, table, host));
     if (flags & PL_SUMS) PL_TRY_HIP(launch_zero_sums(c, c->sums, 16 * c->d.max_items));
     hipError_t e = launch_step(c, table, host, (int)host.size(), total_units, flags, deposit, push);
     if (e == hipErrorInvalidConfiguration) return PL_EUNSUPPORTED;
@@ -384,9 +393,9 @@ pl_status run_call(Ctx *c, pl_item *items, int nitems, double dt, uint32_t flags
     pl_status st = build_table(c, step_items, nitems, dt, mode, deposit, host, total);
     if (st != PL_OK) return st;
 
-    auto enqueue = [&](const ItemDesc *table) -> pl_status {
+    auto enqueue = [&](ItemDesc *table, bool upload) -> pl_status {
         if (!sargs.empty() && launch_sort(c, sargs.data(), (int)sargs.size(), c->max_np) != hipSuccess) return PL_EHIP;
-        return enqueue_step(c, table, host, total, flags, push, deposit);
+        return enqueue_step(c, table, host, total, flags, push, deposit, upload);
     };
     // host bookkeeping once the launches are queued: the sort flipped the sets,
     // and this step rewrites p.fp in the items' (new) order
@@ -405,9 +414,7 @@ pl_status run_call(Ctx *c, pl_item *items, int nitems, double dt, uint32_t flags
     };
 
     if (!(flags & PL_GRAPH)) {
-        st = upload_table(c, host, c->table);
-        if (st != PL_OK) return st;
-        st = enqueue(c->table);
+        st = enqueue(c->table, true);
         return st == PL_OK ? done() : st;
     }
 
@@ -438,7 +445,7 @@ pl_status run_call(Ctx *c, pl_item *items, int nitems, double dt, uint32_t flags
     PL_TRY_HIP(hipStreamSynchronize(c->stream));
     PL_TRY_HIP(hipMemcpy(slot->table, host.data(), host.size() * sizeof(ItemDesc), hipMemcpyHostToDevice));
     PL_TRY_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    pl_status est = enqueue(slot->table);
+    pl_status est = enqueue(slot->table, false);
     hipGraph_t graph = nullptr;
     hipError_t ce = hipStreamEndCapture(c->stream, &graph);
     if (est != PL_OK) {

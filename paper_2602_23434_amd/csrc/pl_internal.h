@@ -198,6 +198,10 @@ bool plain_bins(const Ctx *c, ItemDesc &it, bool push, bool deposit);
 hipError_t launch_step(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc> &host, int nitems,
                        int total_units, unsigned flags, bool deposit, bool push);
 hipError_t launch_zero(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc> &host);
+// The table of a call of up to kTableArgs items, written by a kernel that also
+// zeroes their moments (zero).
+constexpr int kTableArgs = 4;
+hipError_t launch_table(Ctx *c, const std::vector<ItemDesc> &host, bool zero, ItemDesc *table);
 hipError_t launch_zero_sums(Ctx *c, double *sums, int n);
 hipError_t launch_grid_sums(Ctx *c, const ItemDesc &it, double *out8);
 hipError_t launch_pack(Ctx *c, const ItemDesc &it, int prec, int ndim, const double *x[3], const double *u[3]);
