@@ -85,7 +85,9 @@ typedef int pl_status;
 #define PL_DUST    1       /* dust grain, drag towards the gas velocity */
 #define PL_TRACER  2       /* passive tracer of the gas velocity (Eq. 1) */
 
-#define PL_ALGO_PLAIN 0    /* one thread per particle, fields and deposits straight from/to HBM */
+#define PL_ALGO_PLAIN 0    /* particles in any order, no sort: one thread per particle, fields and
+                              deposits straight from/to HBM, or, from a few hundred particles on,
+                              binned by tile inside the call and advanced tile by tile in LDS */
 #define PL_ALGO_TILED 1    /* per-tile LDS field stage and LDS deposit (needs pl_part_sort) */
 #define PL_ALGO_RUNS  2    /* per-tile LDS kernel in which each thread advances a run of up to
                               four particles of one cell in register batches (four float32 or two
@@ -93,8 +95,8 @@ typedef int pl_status;
                               LDS field tile, and the batch's deposits into a stencil point are
                               summed in registers before one LDS atomic per channel (3D/2D,
                               TSC/CIC; charged, dust and, from the same field tile, tracer
-                              species; push-only and deposit-only calls run the PL_ALGO_TILED
-                              kernel).
+                              species; push-only and deposit-only calls need the tile offsets
+                              only, as PL_ALGO_TILED does).
                               Needs pl_part_sort with PL_KEY_TILE_CELL or PL_KEY_TILE_RUN,
                               which writes p.runs */
 
@@ -435,7 +437,7 @@ pl_status pl_part_set_stream(pl_ctx *ctx, void *stream);
 /* Diagnostics, counted since pl_part_init; writes min(n, PL_NSTATS) entries:
  * out[0] kernel launches, out[1] graph replays, out[2] graph recordings,
  * out[3] sorts, out[4] launches of the run-based kernel, out[5] PL_ALGO_RUNS
- * launch groups that took the tiled kernel because the run-based kernel's
+ * launch groups that took a PL_ALGO_TILED kernel because the run-based kernel's
  * LDS footprint exceeds the device's, out[6] launches of a run-based kernel
  * compiled for a fixed tile shape and channel set, out[7] the variant of the
  * last run-based launch: ts | chs << 4 | hf << 8 | mixed << 12, with mixed = 1

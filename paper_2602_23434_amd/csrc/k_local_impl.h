@@ -26,14 +26,17 @@
 // scattered access to the particles' arrays.  Measured on MI355X against the
 // one-particle-per-thread kernel on the same inputs:
 //  * plain float64 step, 2^24 particles in random order on 128^3 cells, rho J
-//    F: 136.1 ms (3.2e9 global atomics at 2.4e10/s) to 6.8 ms, of which the
-//    binning is 0.8 ms;
+//    F: 136.1 ms (3.2e9 global atomics at 2.4e10/s) to 6.1 ms, of which the
+//    binning is 0.6 ms;
 //  * deposit call on run order (float32, 7.1e6 particles, 8^3 tiles, rho J F):
-//    1995 us (four lanes of one cell on one LDS address) to 480 us; push call
-//    431 us to 263 us;
+//    1995 us (four lanes of one cell on one LDS address) to 460 us; push call
+//    431 us to 242 us;
 //  * tiled fused step by tile key (float32, 1.9e6 particles, 8 channels): 578
-//    us to 289 us;
-//  * plain push of 1e6 float64 tracers in random order: 677 us to 270 us.
+//    us to 269 us;
+//  * plain push of 1e6 float64 tracers in random order: 677 us to 245 us (165 us
+//    and the binning);
+//  * push of few particles per tile (72 tracers per 8^3 tile): 62 us per launch;
+//    blocks of 256 threads 67 us, with a one-cell field halo 77 us.
 #pragma once
 
 #include "k_runs_impl.h"

@@ -11,8 +11,8 @@
 // thread advances its run in register batches of KR particles that share one
 // cell:
 //  * each batch particle interpolates its fields from the 27 (9 in 2D)
-//    records of its own cell's stencil in the LDS field tile (one or two
-//    16-byte reads per record in float32, three in float64);
+//    records of its own cell's stencil in the LDS field tile (24 bytes per
+//    charged record in float32, 48 in float64);
 //  * after the push, the batch's deposits are summed per stencil point and
 //    channel before one float64 LDS atomic, cutting LDS atomics by the run
 //    length;

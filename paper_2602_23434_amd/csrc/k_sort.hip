@@ -2,14 +2,15 @@
 //
 // key(p) = tile of the particle's cell, or tile * cells_per_tile + cell in
 // tile, or (rank-interleaved) tile, rank of the particle among the particles
-// of its cell, cell in tile.  The permutation is the stable one (ties keep their order), built by
-// least-significant-digit radix sort on (key, source index) pairs with 8-bit
-// digits: per pass a digit histogram per block, an exclusive scan in
-// digit-major order, and a scatter in which every wave ranks its 64 elements
-// by digit with ballots (so equal digits keep their order) and the block's
-// waves take consecutive sub-ranges.  The final index list moves every SoA
-// array into the alternate buffer set, and a boundary pass writes the
-// first-particle offset of every tile.
+// of its cell, cell in tile.  The permutation is the stable one (ties keep
+// their order), built by least-significant-digit radix sort on (key, source
+// index) pairs with 8-bit digits: per pass a digit histogram per block, an
+// exclusive scan in digit-major order (of few blocks: by the scatter itself),
+// and a scatter in which every wave ranks its 64 elements by digit with ballots
+// (so equal digits keep their order) and the block's waves take consecutive
+// sub-ranges.  The final index list moves every SoA array into the alternate
+// buffer set, and a boundary pass writes the first-particle offset of every
+// tile.
 //
 // Several items of a call are sorted together where the scratch holds their
 // particles (SortGroup): item i's keys start after the keys of the items before

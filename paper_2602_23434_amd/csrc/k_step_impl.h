@@ -1,7 +1,11 @@
 // Gather -> push -> deposit kernels for gfx950 (template; instantiated per
 // precision in k_step_f32.hip and k_step_f64.hip).
 //
-// One templated body serves both algorithms:
+// One particle per thread.  It takes the calls that the tile kernels which group
+// their particles by cell do not: plain calls of too few particles to bin, and
+// tiles whose LDS footprint or particle count does not pay for the grouping
+// (the rules stand with group_route and plain_bins).  One templated body serves
+// both algorithms:
 //  * PLAIN: one thread per particle; fields are read from HBM/L2 at the 27
 //    (TSC) stencil cells and every deposit is a float64 global atomic.
 //  * TILED: one work unit per (item, cell tile).  The block stages the tile's
@@ -12,8 +16,9 @@
 //    stencil leaves the LDS tile (it drifted since the sort) takes the plain
 //    route for that gather or deposit, so results never depend on the sort.
 // Work units of all items of a call are claimed from one atomic counter by a
-// persistent grid sized to the chip's resident capacity; items are ordered
-// largest first on the host.
+// persistent grid sized to the chip's resident capacity (or are the blocks'
+// indices where that holds them all); items are ordered largest first on the
+// host.
 #pragma once
 
 #include <hip/hip_runtime.h>
