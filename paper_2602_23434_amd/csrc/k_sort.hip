@@ -24,6 +24,7 @@
 #include <mutex>
 
 #include "pl_device.h"
+#include "sort_groups.h"
 
 namespace pl {
 
@@ -73,7 +74,6 @@ struct SortItem {
     int32_t *tile_start;
     int32_t *runs;
 };
-constexpr int kGroup = 8;
 struct SortGroup {
     int count, total, prec, ndim, key_mode;
     int base[kGroup + 1], tbase[kGroup + 1];
@@ -872,13 +872,6 @@ __global__ void k_fill_i32(int32_t *p, int n, int v)
 
 int64_t sort_hist_entries(int64_t np) { return kSortHist(np); }
 
-static int bits_for(uint64_t count)
-{
-    int b = 0;
-    while (b < 32 && ((uint64_t)1 << b) < count) ++b;
-    return b;
-}
-
 // LSD radix passes over the low `bits` bits of keys[src] with indices idx[src]
 // (identity when `identity`); returns the buffer index holding the result.
 // Digits of kMaxDigitBits bits, the last pass taking only the bits left.
@@ -1063,20 +1056,19 @@ hipError_t launch_sort(Ctx *c, const SortArgs *args, int count, int64_t cap)
             if (e != hipSuccess) return e;
             continue;
         }
-        // the items that follow join while the scratch holds their particles, the
-        // keys fit 32 bits and the digits' passes stay as many
+        // the items that follow join while the rules of sort_groups.h let them
         auto keys_of = [&](const SortArgs &a) -> uint64_t {
             return (uint64_t)a.ntiles * (a.key_mode == PL_KEY_TILE ? 1 : a.tile[0] * a.tile[1] * a.tile[2]);
         };
-        int64_t np = args[i0].np;
-        uint64_t keys = keys_of(args[i0]), most = keys;
-        auto passes = [](uint64_t k) { return (std::max(bits_for(k), 1) + kMaxDigitBits - 1) / kMaxDigitBits; };
+        GroupSize size;
+        size.np = args[i0].np;
+        size.keys = size.most = keys_of(args[i0]);
         while (args[i0].key_mode != PL_KEY_TILE_RANK && i1 < count && i1 - i0 < kGroup && args[i1].np > 0) {
             const uint64_t k = keys_of(args[i1]);
-            if (np + args[i1].np > cap || keys + k > (1ull << 32) || passes(keys + k) > passes(std::max(most, k)) + 1) break;
-            np += args[i1].np;
-            keys += k;
-            most = std::max(most, k);
+            if (!group_takes(size, args[i1].np, k, cap)) break;
+            size.np += args[i1].np;
+            size.keys += k;
+            size.most = std::max(size.most, k);
             ++i1;
         }
         const hipError_t e = sort_group(c, args + i0, i1 - i0);
