@@ -1047,6 +1047,28 @@ static hipError_t sort_group(Ctx *c, const SortArgs *args, int count)
     return hipGetLastError();
 }
 
+// What the sort of an item reads and writes in the caller's memory.
+static int sort_memory(const SortArgs &a, GroupMemory::Range *r)
+{
+    static_assert(2 * SortArgs::kMaxArrays + 6 <= GroupMemory::kPerItem, "ranges of an item");
+    int n = 0;
+    auto add = [&](const void *p, size_t bytes, bool write) {
+        const uintptr_t b = (uintptr_t)p;
+        r[n++] = GroupMemory::Range{b, b + bytes, 0, write};
+    };
+    for (int k = 0; k < a.narrays; ++k) {
+        add(a.src[k], (size_t)a.np * a.esize[k], false);
+        add(a.dst[k], (size_t)a.np * a.esize[k], true);
+    }
+    for (int k = 0; k < 2 && a.nb > 0; ++k) {
+        add(a.rsrc[k], (size_t)a.np * a.nb * sizeof(double), false);
+        add(a.rdst[k], (size_t)a.np * a.nb * sizeof(double), true);
+    }
+    add(a.tile_start, ((size_t)a.ntiles + 1) * sizeof(int32_t), true);
+    if (a.runs) add(a.runs, (size_t)PL_RUNS_LEN(a.np, a.ntiles) * sizeof(int32_t), true);
+    return n;
+}
+
 hipError_t launch_sort(Ctx *c, const SortArgs *args, int count, int64_t cap)
 {
     for (int i0 = 0, i1 = 0; i0 < count; i0 = i1) {
@@ -1063,9 +1085,15 @@ hipError_t launch_sort(Ctx *c, const SortArgs *args, int count, int64_t cap)
         GroupSize size;
         size.np = args[i0].np;
         size.keys = size.most = keys_of(args[i0]);
+        GroupMemory mem;
+        GroupMemory::Range r[GroupMemory::kPerItem];
+        const int first = sort_memory(args[i0], r);
+        mem.add(i0, r, first);
         while (args[i0].key_mode != PL_KEY_TILE_RANK && i1 < count && i1 - i0 < kGroup && args[i1].np > 0) {
             const uint64_t k = keys_of(args[i1]);
             if (!group_takes(size, args[i1].np, k, cap)) break;
+            const int nr = sort_memory(args[i1], r);
+            if (!mem.add(i1, r, nr)) break;
             size.np += args[i1].np;
             size.keys += k;
             size.most = std::max(size.most, k);

@@ -41,4 +41,43 @@ inline bool group_takes(const GroupSize &g, int64_t np, uint64_t keys, int64_t c
     return g.np + np <= cap && g.keys + keys <= 0xffffffffull && sort_passes(g.keys + keys) <= sort_passes(most) + 1;
 }
 
+// Memory that the items of a group read and write.  Sorted one after another,
+// an item may write what an earlier one has read (a spare set of arrays handed
+// from item to item) or written; in one launch it may not.
+struct GroupMemory {
+    static constexpr int kPerItem = 32;
+    struct Range {
+        uintptr_t beg, end;
+        int item;
+        bool write;
+    };
+    Range all[kGroup * kPerItem];        // by address
+    int n = 0;
+
+    // Add an item's ranges (at most kPerItem); false, and nothing added, when a
+    // byte that it writes is used by another item of the group, or it uses one
+    // that another writes.
+    bool add(int item, const Range *mine, int count)
+    {
+        const int before = n;
+        for (int k = 0; k < count; ++k) {
+            if (mine[k].end <= mine[k].beg) continue;
+            int at = n++;
+            for (; at > 0 && all[at - 1].beg > mine[k].beg; --at) all[at] = all[at - 1];
+            all[at] = mine[k];
+            all[at].item = item;
+        }
+        bool clash = false;
+        for (int a = 0; a < n && !clash; ++a)
+            for (int b = a + 1; b < n && all[b].beg < all[a].end && !clash; ++b)
+                clash = all[a].item != all[b].item && (all[a].write || all[b].write);
+        if (!clash) return true;
+        int kept = 0;
+        for (int k = 0; k < n; ++k)
+            if (all[k].item != item) all[kept++] = all[k];
+        n = before;
+        return false;
+    }
+};
+
 }  // namespace pl

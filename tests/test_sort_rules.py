@@ -19,6 +19,23 @@ extern "C" int takes(int64_t gnp, uint64_t gkeys, uint64_t gmost, int64_t np, ui
     g.most = gmost;
     return pl::group_takes(g, np, keys, cap);
 }
+// ranges: (item, begin, end, write) of items in turn, n of them; the items that join the first one's group
+extern "C" int joined(const int64_t *r, int n)
+{
+    static pl::GroupMemory m;
+    m.n = 0;
+    int items = 0;
+    for (int k = 0; k < n;) {
+        pl::GroupMemory::Range mine[pl::GroupMemory::kPerItem];
+        int c = 0;
+        const int64_t it = r[4 * k];
+        for (; k < n && r[4 * k] == it; ++k)
+            mine[c++] = pl::GroupMemory::Range{(uintptr_t)r[4 * k + 1], (uintptr_t)r[4 * k + 2], 0, r[4 * k + 3] != 0};
+        if (!m.add((int)it, mine, c)) break;
+        ++items;
+    }
+    return items;
+}
 """
 
 
@@ -30,6 +47,7 @@ def rules(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + CSRC, str(src), "-o", str(so)], check=True)
     L = C.CDLL(str(so))
     L.takes.argtypes = [C.c_int64, C.c_uint64, C.c_uint64, C.c_int64, C.c_uint64, C.c_int64]
+    L.joined.argtypes = [C.POINTER(C.c_int64), C.c_int]
     return L
 
 
@@ -51,3 +69,24 @@ def test_keys_up_to_the_sentinel_join(rules):
     assert rules.takes(10, 2 ** 31, 2 ** 31, 10, 2 ** 31 - 1, 100)
     assert not rules.takes(10, 2 ** 31, 2 ** 31, 10, 2 ** 31, 100)
     assert not rules.takes(10, 2 ** 31, 2 ** 31, 91, 1, 100)      # the scratch's particles
+
+
+def _joined(rules, ranges):
+    flat = [int(v) for r in ranges for v in r]
+    return rules.joined((C.c_int64 * len(flat))(*flat), len(ranges))
+
+
+@pytest.mark.parametrize("name,ranges,want", [
+    # (item, begin, end, write): each item reads its set and writes its other one
+    ("own sets", [(0, 0, 10, 0), (0, 20, 30, 1), (1, 10, 20, 0), (1, 30, 40, 1)], 2),
+    ("a read-only array of both", [(0, 0, 10, 0), (0, 20, 30, 1), (1, 0, 10, 0), (1, 30, 40, 1)], 2),
+    ("the second writes what the first has read", [(0, 0, 10, 0), (0, 20, 30, 1), (1, 10, 20, 0), (1, 0, 10, 1)], 1),
+    ("the second reads what the first writes", [(0, 0, 10, 0), (0, 20, 30, 1), (1, 29, 39, 0), (1, 40, 50, 1)], 1),
+    ("one table for both", [(0, 0, 10, 0), (0, 20, 30, 1), (1, 10, 20, 0), (1, 30, 40, 1), (1, 25, 26, 1)], 1),
+    ("an array inside another's", [(0, 0, 100, 1), (1, 200, 210, 0), (1, 50, 60, 0)], 1),
+    ("a long range before a short one", [(0, 0, 100, 0), (1, 10, 20, 0), (2, 90, 95, 1)], 2),
+    ("its own arrays in any order", [(0, 0, 10, 1), (0, 5, 8, 0), (1, 10, 12, 1)], 2),
+    ("empty ranges", [(0, 5, 5, 1), (0, 6, 8, 1), (1, 5, 6, 1), (1, 7, 7, 1)], 2),
+])
+def test_items_that_share_memory_are_sorted_one_after_another(rules, name, ranges, want):
+    assert _joined(rules, ranges) == want
