@@ -29,6 +29,7 @@
 #pragma once
 
 #include "k_step_impl.h"
+#include "unit_chunks.h"
 
 namespace pl {
 
@@ -826,6 +827,7 @@ template <int PREC> __host__ __device__ constexpr int runs_queue(int threads)
 // the two next units (item or -1, tile, particles, runs).
 enum RunsCtl { RC_QP = 1, RC_QD = 2, RC_QI = 3, RC_UNIT = 4 };
 enum RunsUnit { RU_ITEM = 0, RU_TILE, RU_PBEG, RU_PEND, RU_RLO, RU_RHI, RU_WORDS };
+constexpr int RU_NONE = -1, RU_LATER = -2, RU_HEAVY = 1 << 30;     // RU_ITEM: no unit left, not claimed yet, a heavy unit
 constexpr int kRunsGroups = 64;        // entries of the launch's unit table
 constexpr int kRunsCtlBytes = 64 + 4 * kRunsGroups;
 enum { RC_ENDS = 16 };                 // unit table: first word
@@ -1212,19 +1214,24 @@ __device__ __forceinline__ void runs_units(const ItemDesc *__restrict__ items, i
 }
 static_assert(kRunsGroups == 64, "the unit table is one wave's scan");
 
-// Claims.  The launch's units are cut into kQueues contiguous chunks
-// (neighbouring tiles share a chunk), each with its own counter; block b starts
-// on chunk b % kQueues and moves to the next chunk with units left when its own
-// is exhausted (qi chunks passed, mirrored in ctl[RC_QI]).  Blocks are
-// dispatched to the XCDs in turn, so the blocks of one XCD mostly share a chunk
-// and find its field records in their L2; results do not depend on that
-// placement.  With fewer units than blocks every unit is claimed in `sub` parts
-// of its runs (of at least kRunsMinSub), so a small box fills the chip too.
+// Claims.  The parts of the launch's units are dealt to kQueues chunks, kDeal
+// consecutive ones at a time (neighbouring tiles share a chunk), each chunk with
+// its own counter; block b starts on chunk b % kQueues and moves to the next
+// chunk with parts left when its own is exhausted (qi chunks passed, mirrored in
+// ctl[RC_QI]).  Blocks are dispatched to the XCDs in turn, so the blocks of one
+// XCD mostly share a chunk and find its field records in their L2; results do
+// not depend on that placement.  The dealing spreads an item's crowded tiles,
+// which its list has first, over the chunks: in eight contiguous ones the blocks
+// of the first had all of them, one after another.  Measured per pass of 8
+// steps and a sort, contiguous and dealt in 64, 16 and 4: clumped 64^3 float64
+// 2414, 2034, 1840 and 1862 us, clumped 128^3 float32 11.04, 8.95, 9.11 and 9.13 ms; even
+// 128^3 float32 10.75, 10.62, 10.62 and 10.71 ms, eleven items at once 15.0,
+// 15.2, 14.9 and 14.8 ms.  With fewer units than blocks every unit is claimed in
+// `sub` parts of its runs (of at least kRunsMinSub), so a small box fills the chip too.
 // Every part flushes a whole tile, and a launch's atomics are bound at about
 // 5e10/s: 32^3 cells with 2.6e5 particles (64 tiles for 256 CUs) took 67 us per
 // launch whole, 56 us in four parts of 300 runs, 54.5 us in two.
 constexpr int kRunsMinSub = 512;
-__device__ __forceinline__ int queue_lo(int q, int total) { return (int)((long long)total * q / kQueues); }
 
 __device__ __forceinline__ int runs_sub(int total)
 {
@@ -1238,26 +1245,29 @@ __device__ __forceinline__ int runs_take(int parts, unsigned *counter, int &qi)
 {
     const int lane = (int)threadIdx.x & 63, home = (int)(blockIdx.x % kQueues);
     while (qi < kQueues) {
-        const int q = (home + qi) % kQueues, qlo = queue_lo(q, parts), qhi = queue_lo(q + 1, parts);
-        if (qhi > qlo) {
+        const int q = (home + qi) % kQueues, size = chunk_size(q, parts);
+        if (size > 0) {
             int n = 0;
             if (lane == 0) n = (int)atomicAdd(counter + q, 1u);
-            const int g = qlo + __builtin_amdgcn_readfirstlane(n);
-            if (g < qhi) return g;
+            n = __builtin_amdgcn_readfirstlane(n);
+            if (n < size) return chunk_part(q, n);
         }
         // lane k: whether the chunk after k passed ones has units left
         const int p = (home + lane) % kQueues;
         unsigned seen = ~0u;
         if (lane < kQueues) seen = __hip_atomic_load(counter + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool left = lane < kQueues && lane > qi && seen < (unsigned)(queue_lo(p + 1, parts) - queue_lo(p, parts));
+        const bool left = lane < kQueues && lane > qi && seen < (unsigned)chunk_size(p, parts);
         const uint64_t m = __ballot(left);
         qi = m ? (int)__builtin_ctzll(m) : kQueues;
     }
     return -1;
 }
 
-// The runs of claim g (one whole wave, uniformly): item, tile, particles and
-// runs of one unit's part; false when it has none (or the unit list is damaged).
+// The runs of claim g (one whole wave, uniformly): item (with RU_HEAVY where
+// the part has more than kHeavy times the particles of the item's mean unit),
+// tile, particles and runs of one unit's part; false when it has none (or the
+// unit list is damaged).
+constexpr float kHeavy = 1.5f;
 __device__ __forceinline__ bool runs_lookup(const ItemDesc *__restrict__ items, int nitems, const int *ctl, int g, int sub,
                                             int *u)
 {
@@ -1280,6 +1290,7 @@ __device__ __forceinline__ bool runs_lookup(const ItemDesc *__restrict__ items, 
     if (k >= kend) return false;
     const ItemDesc &I = items[k];
     const int32_t *unit = I.runs + runs_units_at(I.np, I.ntiles) + 2 * local;
+    const int nu = __builtin_amdgcn_readfirstlane(I.runs[runs_count_at(I.np, I.ntiles)]);
     const int t = __builtin_amdgcn_readfirstlane(unit[0]), w = __builtin_amdgcn_readfirstlane(unit[1]);
     const int piece = w & 0xffff, npieces = w >> 16;
     if ((unsigned)t >= (unsigned)I.ntiles || npieces < 1 || piece >= npieces) return false;
@@ -1292,6 +1303,7 @@ __device__ __forceinline__ bool runs_lookup(const ItemDesc *__restrict__ items, 
         lo = (int)((long long)nruns * piece / npieces);
         hi = (int)((long long)nruns * (piece + 1) / npieces);
     }
+    const bool heavy = (float)(pend - pbeg) * (float)nu > kHeavy * (float)I.np * (float)npieces;
     if (sub > 1) {
         // parts of at least kRunsMinSub runs, the last ones empty
         const int n = hi - lo, parts = max(1, min(sub, n / kRunsMinSub));
@@ -1299,7 +1311,7 @@ __device__ __forceinline__ bool runs_lookup(const ItemDesc *__restrict__ items, 
         hi = lo + (int)((long long)n * (s + 1) / parts);
         lo = lo + (int)((long long)n * s / parts);
     }
-    u[RU_ITEM] = k;
+    u[RU_ITEM] = k | (heavy ? RU_HEAVY : 0);
     u[RU_TILE] = t;
     u[RU_PBEG] = pbeg;
     u[RU_PEND] = pend;
@@ -1309,12 +1321,13 @@ __device__ __forceinline__ bool runs_lookup(const ItemDesc *__restrict__ items, 
 }
 
 // The next unit with runs, claimed and looked up by one whole wave into a
-// unit's control words (item -1: none left).
-__device__ __forceinline__ void runs_next(const ItemDesc *__restrict__ items, int nitems, unsigned *counter, int *ctl,
+// unit's control words (item -1: none left); whether it is a heavy one.
+__device__ __forceinline__ bool runs_next(const ItemDesc *__restrict__ items, int nitems, unsigned *counter, int *ctl,
                                           int *unit)
 {
     const int total = __builtin_amdgcn_readfirstlane(ctl[RC_ENDS + kRunsGroups - 1]), sub = runs_sub(total);
     int qi = __builtin_amdgcn_readfirstlane(ctl[RC_QI]);
+    bool heavy = false;
     for (;;) {
         int g = -1;
         if (total * sub <= (int)gridDim.x) {
@@ -1325,12 +1338,16 @@ __device__ __forceinline__ void runs_next(const ItemDesc *__restrict__ items, in
             g = runs_take(total * sub, counter, qi);
         }
         if (g < 0) {
-            unit[RU_ITEM] = -1;
+            unit[RU_ITEM] = RU_NONE;
             break;
         }
-        if (runs_lookup(items, nitems, ctl, g, sub, unit)) break;
+        if (runs_lookup(items, nitems, ctl, g, sub, unit)) {
+            heavy = __builtin_amdgcn_readfirstlane(unit[RU_ITEM]) & RU_HEAVY;
+            break;
+        }
     }
     ctl[RC_QI] = qi;
+    return heavy;
 }
 
 // The last block to finish resets the chunk counters for the next launch (a
@@ -1385,8 +1402,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     __syncthreads();
     if (threadIdx.x < 64) runs_next(items, nitems, counter, ctl, ctl + RC_UNIT);
     __syncthreads();
-    // Unit by unit, two known ahead (one lane looks the second up while the
-    // others work).  The loads of the next unit's fields go out before this
+    // Unit by unit, two known ahead (the last wave looks the second up while the
+    // others work), but none beyond a heavy one: a block that holds two crowded
+    // pieces does them in turn while others have run out (clumped 48^3 in float64,
+    // 8 steps and a sort: 1302 us with the pieces held, 1125 us without).  Past a
+    // heavy unit the next is claimed at its end (RU_LATER) and staged without
+    // loads ahead.  The loads of the next unit's fields go out before this
     // unit's flush and come back before its atomics, and the LDS has them right
     // after it.  What it measured, share of the waves' time on the 128^3 box
     // with 2^24 particles (float32, rho J F): staging 9.4 to 3 %, claims 4.4 to 0
@@ -1399,7 +1420,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     auto known = [&](int slot) -> Ref {
         const int *w = ctl + RC_UNIT + RU_WORDS * slot;
         auto word = [&](int k) -> int { return __builtin_amdgcn_readfirstlane(w[k]); };
-        return Ref{word(RU_ITEM), word(RU_TILE), word(RU_PBEG), word(RU_PEND), word(RU_RLO), word(RU_RHI)};
+        const int it = word(RU_ITEM);
+        return Ref{it < 0 ? it : it & ~RU_HEAVY, word(RU_TILE), word(RU_PBEG), word(RU_PEND), word(RU_RLO), word(RU_RHI)};
     };
     Ref cur = known(0);
     if (cur.iti >= 0) {
@@ -1412,7 +1434,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         unit_shared<PREC, KIND>(G, items[cur.iti].nslot, smem_raw, lds_bytes, flags, S);
         stage_unit<PREC, DIM, KIND>(U, G, const_cast<R *>(S.lds_f), S.lds_d, G.Ld * items[cur.iti].nslot);
         if (tid < 8) S.sums[tid] = 0.0;
-        if (tid >= bd - 64) runs_next(items, nitems, counter, ctl, ctl + RC_UNIT + RU_WORDS);
+        if (tid >= bd - 64) {
+            int *next = ctl + RC_UNIT + RU_WORDS;
+            if (__builtin_amdgcn_readfirstlane(ctl[RC_UNIT]) & RU_HEAVY) next[RU_ITEM] = RU_LATER;
+            else runs_next(items, nitems, counter, ctl, next);
+        }
         auto first_entry = [&](const Ref &u) -> int {
             return u.iti >= 0 && u.r_lo + tid < u.r_hi
                        ? ((gptr<const int32_t>)(items[u.iti].runs + u.pbeg))[u.r_lo + tid] : 0;
@@ -1441,7 +1467,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             };
             unit_runs<PREC, SHAPE, DIM, KIND, CHS, KR>(
                 U, G, S, runs, cur.pbeg, cur.pend, cur.r_lo, cur.r_hi, entry, do_sums, err, ahead, [&]() {
-                    runs_next(items, nitems, counter, ctl, ctl + RC_UNIT + RU_WORDS * slot);
+                    // this unit's words take the claim after the next one; the
+                    // words of a next one not claimed yet, the claim after that
+                    int *mine = ctl + RC_UNIT + RU_WORDS * slot, *other = ctl + RC_UNIT + RU_WORDS * (slot ^ 1);
+                    const bool both = nxt.iti == RU_LATER;
+                    bool hold = nxt.iti >= 0 && (__builtin_amdgcn_readfirstlane(other[RU_ITEM]) & RU_HEAVY);
+#pragma unroll 1
+                    for (int k = 0; k < (both ? 2 : 1); ++k) {
+                        int *w = k ? other : mine;
+                        if (hold) w[RU_ITEM] = RU_LATER;
+                        else hold = runs_next(items, nitems, counter, ctl, w);
+                    }
                 });
             if (do_sums && tid < 8) {
                 const double v = S.sums[tid];
@@ -1449,7 +1485,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 if (v != 0.0) global_add(items[cur.iti].psum + tid, v);
             }
             flush_unit<PREC, DIM, CHS>(U, G, S.lds_d);
+            const bool later = nxt.iti == RU_LATER;              // uniform, as are all of its values
+            if (later) nxt = known(slot);
             if (nxt.iti < 0) break;                              // uniform
+            if (later) unit_geo<DIM, HF, TS>(items[nxt.iti], nxt.t, flags, Gn);
             if (nxt.iti != cur.iti) {
                 load_unit<PREC>(items[nxt.iti], U, Gn.Ld);
                 if (TS == 0) {
@@ -1462,17 +1501,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                     }
             G = Gn;
             R *lds_f = const_cast<R *>(S.lds_f);
+            if (!later) {
 #pragma unroll
-            for (int k = 0; k < NPRE; ++k)
-                if (tid + k * bd < G.Lf) rec_store<PREC, KIND>(G, lds_f, tid + k * bd, pre[k]);
-            for (int e = tid + NPRE * bd; e < G.Lf; e += bd) {
+                for (int k = 0; k < NPRE; ++k)
+                    if (tid + k * bd < G.Lf) rec_store<PREC, KIND>(G, lds_f, tid + k * bd, pre[k]);
+            }
+            for (int e = tid + (later ? 0 : NPRE * bd); e < G.Lf; e += bd) {
                 double v[NC];
                 rec_load<PREC, DIM, KIND>(U, G, e, v);
                 rec_store<PREC, KIND>(G, lds_f, e, v);
             }
             cur = nxt;
-            entry = entry_n;
-            nxt = known(slot);
+            entry = later ? first_entry(cur) : entry_n;
+            nxt = known(later ? slot ^ 1 : slot);
+            if (later) slot ^= 1;                                // (cur stays where it is)
             __syncthreads();
         }
     }
@@ -1499,7 +1541,7 @@ __global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2,
         __syncthreads();
         auto word = [&](int k) -> int { return __builtin_amdgcn_readfirstlane(ctl[RC_UNIT + k]); };
         if (word(RU_ITEM) < 0) break;                         // uniform
-        const ItemDesc &I = items[word(RU_ITEM)];
+        const ItemDesc &I = items[word(RU_ITEM) & ~RU_HEAVY];
         const int t = word(RU_TILE), pbeg = word(RU_PBEG), pend = word(RU_PEND), lo = word(RU_RLO), hi = word(RU_RHI);
         const int kind = __builtin_amdgcn_readfirstlane(I.kind);
         if (kind == PL_LORENTZ)

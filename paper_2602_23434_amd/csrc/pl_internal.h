@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/pl.h"
+#include "unit_chunks.h"
 
 namespace pl {
 
@@ -17,7 +18,6 @@ constexpr int kMaxDigitBits = 8;     // radix digit of the sort (256 counters pe
 constexpr int kRunLen = 4;           // particles per run of the run table (PL_ALGO_RUNS)
 constexpr int kRunsMaxTileCells = 1024;
 constexpr int kRunsSplit = PL_RUNS_SPLIT_UNITS;   // work units beyond one per tile
-constexpr int kQueues = 8;          // run kernels: chunks of the unit slots, one counter each
 constexpr int kCounterStride = 16;  // counters per launch stage (kQueues + 1 used by the run kernels)
 constexpr int kCounterSlots = 4 * kCounterStride;   // one stage per species kind, plus one
 static_assert(kQueues + 1 <= kCounterStride, "a run-kernel stage needs kQueues + 1 counters");
