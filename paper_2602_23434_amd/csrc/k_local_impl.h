@@ -40,10 +40,9 @@
 #pragma once
 
 #include "k_runs_impl.h"
+#include "tile_route.h"
 
 namespace pl {
-
-enum LocalMode { LM_FUSED = 0, LM_PUSH = 1, LM_DEP = 2 };
 
 constexpr int kLocalThreads = 512, kLocalSmall = 256;
 constexpr int kLocalRounds = 5;        // rounds of runs counted together (11 bits each in 64)
@@ -583,14 +582,17 @@ static LocalLds local_item_lds(const Ctx *c, const ItemDesc &it, int mode, int h
 }
 
 // Launch configuration for the items of one species kind: field halo,
-// particles per chunk, LDS bytes.  False when a tile has too many cells or its
-// LDS does not fit with chunks of at least kLocalMinCap particles.
-// Fewer particles per tile than threads do not pay for the grouping (4096
+// particles per chunk, LDS bytes.  False when it does not pay (tile_route.h;
+// binned plain items go by plain_bins), when a tile has too many cells, or when
+// its LDS does not fit with chunks of at least kLocalMinCap particles.  Fewer
+// particles per tile than threads do not pay either (4096
 // particles in 32 tiles: 266 us for ten steps against 251 us of the
 // one-particle-per-thread kernel); up to kLocalSmallPerTile a block of 256
 // threads holds enough of a tile's runs, and the phases of two blocks on a CU
 // overlap (float64 by tile key, 8 x 4 x 4 tiles of 768 particles: eight
-// steps and the sort 5.89 ms with 512 threads, 4.16 ms with 256).
+// steps and the sort 5.89 ms with 512 threads, 4.16 ms with 256).  The tiles of
+// float32 boxes in 3D are larger, and their small blocks have no fixed shapes: dust on
+// 8^3 tiles of 1024 particles 72 us with 256 threads, 41 with 512.
 constexpr int kLocalMinCap = 1024;
 constexpr int kLocalSmallPerTile = 2048;
 
@@ -606,6 +608,14 @@ bool local_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, bool push, 
     pl.mode = push ? (dep ? LM_FUSED : LM_PUSH) : LM_DEP;
     const int d3 = c->d.ndim >= 3;
     const bool group = pl.mode != LM_PUSH;
+    TileLoad w{0, 0, 0};
+    for (int i = 0; i < nitems; ++i) {
+        if (host[i].np == 0) continue;
+        w.np += host[i].np;
+        w.nt += host[i].ntiles;
+        w.cells += (int64_t)host[i].n[0] * host[i].n[1] * host[i].n[2];
+    }
+    if (!host[0].idx && !local_pays(pl.mode, c->d.ndim, PREC, kind, c->d.key_mode, c->num_cu, w)) return false;
     for (int i = 0; i < nitems && group; ++i) {
         const int *T = host[i].tile;
         const int E = (T[0] + 2) * (T[1] + 2) * (d3 ? T[2] + 2 : 1);
@@ -623,14 +633,10 @@ bool local_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, bool push, 
         pl.lds = bytes(pl.hf, pl.cap);
         return pl.lds <= (size_t)c->lds_max;
     }
-    int64_t np = 0, nt = 0;
-    for (int i = 0; i < nitems; ++i) {
-        np += host[i].np;
-        nt += host[i].ntiles;
-    }
+    const int64_t np = w.np, nt = w.nt;
     pl.hf = 1;
     // tiles of few particles whose LDS lets two blocks share a CU: smaller blocks
-    if (np < kLocalSmallPerTile * nt) {
+    if (np < kLocalSmallPerTile * nt && (PREC == PL_F64 || !d3)) {
         pl.nt = kLocalSmall;
         for (pl.cap = 2048; pl.cap >= kLocalMinCap; pl.cap -= 256) {
             pl.lds = bytes(1, pl.cap);

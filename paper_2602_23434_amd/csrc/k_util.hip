@@ -49,10 +49,9 @@ int group_end(const std::vector<ItemDesc> &host, int i0)
 }
 
 // Fused run-based steps of charged and dust species take the run-based kernel
-// (its tables come from the sort).  Everything else that has tiles takes a
-// self-grouping kernel where the tile and its LDS allow it: it needs only the
-// tile offsets, and a quarter to a half of the LDS atomics of the
-// one-particle-per-thread kernel.
+// (its tables come from the sort).  What else has tiles takes a self-grouping
+// kernel, which needs only the tile offsets, where that pays (tile_route.h) and
+// the tile and its LDS allow it; else the one-particle-per-thread kernel.
 Route group_route(const Ctx *c, const ItemDesc *host, int nitems, bool push, bool deposit, LocalPlan &pl)
 {
     RunsPlan rp;

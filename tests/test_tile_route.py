@@ -1,0 +1,70 @@
+"""Which kernel a tiled call takes, compiled for the CPU from the header that the
+launcher uses.  Each line is a call timed with both kernels on the GPU (us with
+one particle per thread, us grouped): the rule takes the faster one."""
+
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2602_23434_amd", "csrc")
+
+PROBE = r"""
+#include "tile_route.h"
+extern "C" int pays(int mode, int ndim, int prec, int kind, int key, int64_t np, int64_t nt, int64_t cells)
+{
+    const pl::TileLoad w{np, nt, cells};
+    return pl::local_pays(mode, ndim, prec, kind, key, 256, w);
+}
+"""
+FUSED, PUSH, DEP = 0, 1, 2
+F64, F32 = 0, 1
+CHARGED, DUST, TRACER = 0, 1, 2
+TILE, CELL, RANK, RUN = 0, 1, 2, 3
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    d = tmp_path_factory.mktemp("route")
+    src, so = d / "probe.cpp", d / "probe.so"
+    src.write_text(PROBE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + CSRC, str(src), "-o", str(so)], check=True)
+    L = C.CDLL(str(so))
+    L.pays.argtypes = [C.c_int] * 5 + [C.c_int64] * 3
+    return L
+
+
+CASES = [
+    # mode, prec, kind, key, box, tiles, particles per cell, step us, grouped us
+    (FUSED, F32, CHARGED, TILE, (512, 512, 1), 4096, 8, 179, 242),
+    (FUSED, F32, CHARGED, RANK, (440, 288, 1), 1980, 6, 62, 83),
+    (FUSED, F32, DUST, TILE, (40, 48, 80), 300, 11, 171, 215),
+    (FUSED, F32, DUST, TILE, (64, 64, 64), 512, 8, 228, 279),
+    (FUSED, F32, DUST, TILE, (32, 32, 32), 64, 4, 75, 43),
+    (FUSED, F64, DUST, RANK, (80, 84, 100), 10500, 10, 860, 885),
+    (FUSED, F64, CHARGED, RANK, (64, 64, 64), 2048, 16, 740, 871),
+    (FUSED, F64, CHARGED, TILE, (64, 64, 64), 2048, 8, 328, 250),
+    (FUSED, F64, CHARGED, TILE, (64, 64, 64), 2048, 2, 176, 178),
+    (FUSED, F32, CHARGED, TILE, (64, 64, 64), 512, 16, 595, 480),
+    (FUSED, F32, CHARGED, RANK, (64, 64, 64), 512, 8, 395, 271),
+    (FUSED, F32, CHARGED, CELL, (64, 64, 64), 512, 8, 1130, 295),
+    (FUSED, F64, DUST, CELL, (512, 512, 1), 8192, 8, 260, 310),
+    (DEP, F64, DUST, RANK, (64, 64, 64), 2048, 16, 285, 384),
+    (DEP, F32, DUST, TILE, (64, 64, 64), 512, 2, 65, 69),
+    (DEP, F32, CHARGED, RUN, (64, 64, 64), 512, 8, 538, 148),
+    (DEP, F32, DUST, RUN, (512, 512, 1), 4096, 4, 106, 128),
+    (DEP, F64, CHARGED, TILE, (32, 32, 1), 32, 16, 20, 23),
+    (PUSH, F64, CHARGED, TILE, (1024, 1024, 1), 32768, 8, 446, 708),
+    (PUSH, F64, DUST, TILE, (128, 128, 128), 16384, 8, 940, 1133),
+    (PUSH, F32, CHARGED, TILE, (64, 64, 64), 512, 8, 187, 86),
+    (PUSH, F64, TRACER, TILE, (64, 64, 64), 2048, 8, 177, 139),
+    (PUSH, F32, DUST, TILE, (64, 64, 64), 512, 2, 44, 49),
+]
+
+
+@pytest.mark.parametrize("mode,prec,kind,key,box,tiles,ppc,step,grouped", CASES)
+def test_the_faster_kernel(rule, mode, prec, kind, key, box, tiles, ppc, step, grouped):
+    cells = box[0] * box[1] * box[2]
+    got = rule.pays(mode, 2 if box[2] == 1 else 3, prec, kind, key, cells * ppc + 7, tiles, cells)
+    assert bool(got) == (grouped < step)
