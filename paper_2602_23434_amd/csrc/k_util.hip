@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "pl_device.h"
+#include "plain_cost.h"
 
 namespace pl {
 
@@ -23,20 +24,6 @@ hipError_t launch_local_f32(Ctx *c, const ItemDesc *table, const ItemDesc *host,
                             unsigned sf, unsigned *counter);
 hipError_t launch_local_f64(Ctx *c, const ItemDesc *table, const ItemDesc *host, int nitems, const LocalPlan &pl,
                             unsigned sf, unsigned *counter);
-
-// Plain algorithm: when binning an item's indices costs less than it saves.
-// The direct kernel's deposits are global atomics (2.4e10/s at random, and a
-// chain of 370 us for even one particle per lane in 3D); a bin's tile costs a
-// work unit (about 10 us on one of 256 CUs).  Measured per step in us, direct
-// and binned (float64, 3D unless said):
-//   with a deposit: 2048 particles on 16^3 cells 370 and 59, on 64^3 (1024
-//     tiles) 512 and 145; in 2D 137 and 56.  So: a few hundred particles, and
-//     at least 6 per tile unless the tiles are few;
-//   push only (tracers): 131072 particles on 32^3 88 and 80, on 64^3 170 and
-//     140, but on 16^3, whose fields stay in the caches, 68 and 104; in 2D
-//     262144 on 256^2 63 and 84, 1048576 250 and 186.
-constexpr int kBinMinDeposit = 512, kBinMinPerTile = 6, kBinFewTiles = 4096;
-constexpr int kBinMinPush = 131072, kBinMinPush2D = 524288, kBinMinPushCells = 20000, kBinMinPushPerTile = 32;
 
 // Items of one launch: those of one species kind; an item whose indices the
 // call bins (plain algorithm) has one of its own.
@@ -64,34 +51,62 @@ Route group_route(const Ctx *c, const ItemDesc *host, int nitems, bool push, boo
 
 // Tiles of a binned item: 8^3 cells (float32) or 8 x 8 x 4 (float64), 32 x 32
 // or 32 x 16 in 2D, the largest whose LDS leaves chunks of a tile's particles;
-// they need not divide the box (a tile past its edge wraps).
-bool plain_bins(const Ctx *c, ItemDesc &it, bool push, bool deposit)
+// they need not divide the box (a tile past its edge wraps).  Their number.
+static int64_t bin_tiles(const Ctx *c, const ItemDesc &it, int tile[3], int ntile[3])
 {
-    if (c->d.algo != PL_ALGO_PLAIN) return false;
-    const bool dep = deposit && it.kind != PL_TRACER && it.nslot > 0;
-    if (!push && !dep) return false;
-    const bool d3 = c->d.ndim == 3;
-    if (it.np < (dep ? kBinMinDeposit : d3 ? kBinMinPush : kBinMinPush2D)) return false;
-    if (!dep && (int64_t)it.n[0] * it.n[1] * it.n[2] < kBinMinPushCells) return false;
-    ItemDesc d = it;
-    const bool f64 = c->d.prec == PL_F64;
-    d.tile[0] = d3 ? 8 : 32;
-    d.tile[1] = d3 ? 8 : (f64 ? 16 : 32);
-    d.tile[2] = d3 ? (f64 || it.nslot > 7 ? 4 : 8) : 1;
+    const bool d3 = c->d.ndim == 3, f64 = c->d.prec == PL_F64;
+    tile[0] = d3 ? 8 : 32;
+    tile[1] = d3 ? 8 : (f64 ? 16 : 32);
+    tile[2] = d3 ? (f64 || it.nslot > 7 ? 4 : 8) : 1;
     int64_t nt = 1;
     for (int a = 0; a < 3; ++a) {
-        d.ntile[a] = (d.n[a] + d.tile[a] - 1) / d.tile[a];
-        nt *= d.ntile[a];
+        ntile[a] = (it.n[a] + tile[a] - 1) / tile[a];
+        nt *= ntile[a];
     }
-    if (nt > c->bin_cap) return false;
-    if (dep ? (it.np / kBinMinPerTile < nt && nt > kBinFewTiles) : it.np / kBinMinPushPerTile < nt) return false;
-    d.ntiles = (int)nt;
-    d.tile_start = c->bin_start;
-    d.idx = c->idx[bins_buffer(d.ntiles)];
-    LocalPlan pl;
-    if (!local_plan(c, &d, 1, push, deposit, pl)) return false;
-    it = d;
-    return true;
+    return nt;
+}
+
+void plain_bins(const Ctx *c, std::vector<ItemDesc> &host, bool push, bool deposit)
+{
+    if (c->d.algo != PL_ALGO_PLAIN) return;
+    const int n = (int)host.size();
+    std::vector<PlainItem> rule(n, PlainItem{0, 0, 0, false, false});
+    std::vector<ItemDesc> bins;
+    for (int i0 = 0, i1 = 0; i0 < n; i0 = i1) {
+        const int kind = host[i0].kind;
+        bool any = false;
+        for (i1 = i0; i1 < n && host[i1].kind == kind; ++i1) {
+            const ItemDesc &it = host[i1];
+            const bool dep = deposit && kind != PL_TRACER && it.nslot > 0;
+            if (it.np == 0 || !(push || dep)) continue;
+            int tile[3], ntile[3];
+            const int64_t nt = bin_tiles(c, it, tile, ntile), cells = (int64_t)it.n[0] * it.n[1] * it.n[2];
+            const bool want = dep ? it.np >= kBinMinDeposit : push_bins(it.np, cells, nt, c->d.ndim, c->d.prec, kind);
+            bool fits = false;
+            if (want && nt <= c->bin_cap) {
+                if (bins.empty()) bins = host;
+                ItemDesc &d = bins[i1];
+                for (int a = 0; a < 3; ++a) {
+                    d.tile[a] = tile[a];
+                    d.ntile[a] = ntile[a];
+                }
+                d.ntiles = (int)nt;
+                d.tile_start = c->bin_start;
+                d.idx = c->idx[bins_buffer(d.ntiles)];
+                LocalPlan pl;
+                fits = local_plan(c, &d, 1, push, deposit, pl);
+            }
+            if (dep) rule[i1] = PlainItem{it.np, nt, it.nslot, fits, false};
+            else if (fits) rule[i1].binned = any = true;     // (a rule of its own: no deposit)
+            any = any || fits;
+        }
+        if (!any) continue;
+        std::vector<PlainItem> dep(rule.begin() + i0, rule.begin() + i1);
+        choose_bins(dep.data(), i1 - i0, c->d.ndim, c->d.prec, kind, c->num_cu);
+        for (int i = i0; i < i1; ++i)
+            if (rule[i].binned || dep[i - i0].binned) host[i] = bins[i];
+        std::stable_partition(host.begin() + i0, host.begin() + i1, [](const ItemDesc &d) { return d.idx != nullptr; });
+    }
 }
 
 // The host table is ordered by species kind, then by particle count.  A fused

@@ -295,11 +295,8 @@ pl_status build_table(Ctx *c, const pl_item *items, int nitems, double dt, Mode 
         one_launch = runs_plan(c, all.data(), nitems, pl);
     }
     const bool push = mode == MODE_STEP;
-    for (int k = 0; k < nitems; ++k) {
-        ItemDesc D = descs[order[k]];
-        plain_bins(c, D, push, deposit);
-        host.push_back(D);
-    }
+    for (int k = 0; k < nitems; ++k) host.push_back(descs[order[k]]);
+    plain_bins(c, host, push, deposit);
     for (int i0 = 0, i1 = 0; i0 < nitems; i0 = i1) {
         i1 = one_launch ? nitems : group_end(host, i0);
         LocalPlan lp;

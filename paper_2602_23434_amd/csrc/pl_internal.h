@@ -190,9 +190,10 @@ bool local_plan(const Ctx *c, const ItemDesc *host, int nitems, bool push, bool 
 enum Route { ROUTE_RUNS, ROUTE_LOCAL, ROUTE_STEP };
 int group_end(const std::vector<ItemDesc> &host, int i0);
 Route group_route(const Ctx *c, const ItemDesc *host, int nitems, bool push, bool deposit, LocalPlan &pl);
-// Plain algorithm: whether the call bins this item's particle indices by tile
-// first; sets the item's tiles, tile offsets and index list if so.
-bool plain_bins(const Ctx *c, ItemDesc &it, bool push, bool deposit);
+// Plain algorithm: the items of the call's ordered table whose particle indices it
+// bins by tile first (plain_cost.h); sets their tiles, tile offsets and index
+// lists, and puts them before the others of their kind.
+void plain_bins(const Ctx *c, std::vector<ItemDesc> &host, bool push, bool deposit);
 
 // Kernel launchers (k_step.hip)
 hipError_t launch_step(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc> &host, int nitems,
