@@ -29,6 +29,7 @@
 #pragma once
 
 #include "k_step_impl.h"
+#include "runs_sums.h"
 #include "unit_chunks.h"
 
 namespace pl {
@@ -1608,22 +1609,15 @@ static size_t runs_item_lds(const Ctx *c, const ItemDesc &it, int hf, int nt)
     return runs_lds_bytes<PREC, PL_TRACER>(Lf, Ld, 0, hf, dq, offs);
 }
 
-// Which particles join their batch's float32 deposit sums decides those sums'
-// last bits: particles up to one cell outside the tile do where 32-byte field
-// records with a two-cell halo and queues of 256 fit the LDS beside the deposit
-// tile, else particles inside the tile only.  (The records take 24 bytes; the
-// rule stays, so the grids do not depend on how much the LDS holds besides.)
+// Whether the footprint that the float32 sums go by (runs_sums.h) fits for every
+// item of a launch with an hf-cell field halo.
 template <int PREC>
-static bool runs_wide_sums(const Ctx *c, const ItemDesc *host, int nitems)
+static bool runs_sums_fit(const Ctx *c, const ItemDesc *host, int nitems, int hf)
 {
-    const int d3 = c->d.ndim >= 3;
-    for (int i = 0; i < nitems; ++i) {
-        const int *T = host[i].tile, ns = host[i].kind == PL_TRACER ? 0 : host[i].nslot;
-        const size_t Lf = (size_t)(T[0] + 4) * (T[1] + 4) * (d3 ? T[2] + 4 : 1);
-        const size_t b = runs_section(Lf * (host[i].kind == PL_LORENTZ ? 32 : 16)) + runs_section(Lf * ns * 8) + 256 +
-                         1024 + 1024 * (size_t)(3 + ns) + 80;
-        if (b > (size_t)c->lds_max) return false;
-    }
+    for (int i = 0; i < nitems; ++i)
+        if (runs_sums_bytes(host[i].kind == PL_LORENTZ, host[i].tile, c->d.ndim,
+                            host[i].kind == PL_TRACER ? 0 : host[i].nslot, hf) > (size_t)c->lds_max)
+            return false;
     return true;
 }
 
@@ -1683,11 +1677,13 @@ bool runs_plan_impl(const Ctx *c, const ItemDesc *host, int nitems, RunsPlan &pl
     // kernel took 1.1 and 1.4 times as long)
     if (d2 && !pl.mixed && 2 * bytes(2, kRunsSmall) <= (size_t)c->lds_max) pl.nt = kRunsSmall;
     else if (d2) pl.ts = pl.chl = pl.chd = 0;
+    // (else the self-grouping kernel and its float64 sums)
+    if (PREC == PL_F32_OFFSET && !runs_sums_fit<PREC>(c, host, nitems, 1)) return false;
     // LDS of the launch: a two-cell field halo when it fits, else one cell
     for (int hf = 2; hf >= 1; --hf) {
         pl.hf = hf;
         pl.lds = bytes(hf, pl.nt);
-        pl.narrow = PREC == PL_F32_OFFSET && hf == 2 && !runs_wide_sums<PREC>(c, host, nitems);
+        pl.narrow = PREC == PL_F32_OFFSET && hf == 2 && !runs_sums_fit<PREC>(c, host, nitems, 2);
         if (pl.lds <= (size_t)c->lds_max) return true;
     }
     return false;
