@@ -51,12 +51,12 @@ constexpr int kLocalMaxCap = 8192;     // particles of a chunk: 13 bits of a run
 constexpr int kLocalSums = 8;          // partial particle-side sums per channel (lanes spread over them)
 
 // Particles per register batch, and capacity of the queue of deposits outside
-// their batch's cell: the run-based kernel's queue, a half of it (the chunk's
+// their batch's cell: about a half of the run-based kernel's (the chunk's
 // order takes the rest: with every channel on an 8^3 tile the larger queue
 // left chunks of under half a tile).
 template <int PREC> struct LocalBatch {
     static constexpr int KR = PREC == PL_F32_OFFSET ? 4 : 2;
-    static constexpr int DQ = RunsQ<PREC>::DQ / 2;
+    static constexpr int DQ = PREC == PL_F32_OFFSET ? 96 : 64;
 };
 
 // Sections of the LDS: field records, deposit tile, work area (cell counts

@@ -29,22 +29,15 @@
 #pragma once
 
 #include "k_step_impl.h"
+#include "runs_lds.h"
 #include "runs_sums.h"
 #include "unit_chunks.h"
 
 namespace pl {
 
-// Capacity of the queue of particles that need the HBM gather: with a
-// two-cell field halo only particles two cells out of their tile land there.
-__host__ __device__ constexpr int gq_cap(int hf) { return hf == 2 ? 64 : 256; }
-
 // Type of a batch's deposit sums.
 template <int PREC, bool DACC> struct AccOf { using T = typename RealOf<PREC>::T; };
 template <int PREC> struct AccOf<PREC, true> { using T = double; };
-
-// Capacity of the queue of deposits outside their batch's cell (float32: what
-// the LDS leaves beside every channel and a two-cell field halo on 8^3 tiles).
-template <int PREC> struct RunsQ { static constexpr int DQ = PREC == PL_F32_OFFSET ? 192 : 128; };
 
 // LDS field records.  Lanes of a wave read records of neighbouring cells, so
 // the record stride decides the bank pattern: float32 charged particles use a
@@ -815,37 +808,20 @@ __device__ __forceinline__ void run_batch(const UnitC<PREC> &U, const RunGeo &G,
     }
 }
 
-// Threads of the small blocks, and the deposit queue of a block.
-constexpr int kRunsSmall = 256;
-template <int PREC> __host__ __device__ constexpr int runs_queue(int threads)
-{
-    return threads == kRunsSmall ? 64 : RunsQ<PREC>::DQ;
-}
-
-// LDS bytes of one work unit: field records, float64 deposit tile, queues,
-// sums, and a control tail (RunsCtl).
 // Control words: queued particles, queued deposits, chunks passed, and
-// the two next units (item or -1, tile, particles, runs).
+// the two next units (item or -1, tile, particles, runs); then the launch's unit
+// table.
 enum RunsCtl { RC_QP = 1, RC_QD = 2, RC_QI = 3, RC_UNIT = 4 };
 enum RunsUnit { RU_ITEM = 0, RU_TILE, RU_PBEG, RU_PEND, RU_RLO, RU_RHI, RU_WORDS };
 constexpr int RU_NONE = -1, RU_LATER = -2, RU_HEAVY = 1 << 30;     // RU_ITEM: no unit left, not claimed yet, a heavy unit
-constexpr int kRunsGroups = 64;        // entries of the launch's unit table
-constexpr int kRunsCtlBytes = 64 + 4 * kRunsGroups;
 enum { RC_ENDS = 16 };                 // unit table: first word
-__host__ __device__ inline size_t runs_section(size_t b) { return (b + 15) & ~(size_t)15; }
+static_assert(RC_UNIT + 2 * RU_WORDS <= RC_ENDS && 4 * (RC_ENDS + kRunsGroups) == kRunsCtlBytes, "control words");
 
 template <int PREC, int KIND>
-__host__ __device__ inline size_t runs_lds_bytes(int Lf, int Ld, int nslot, int hf, int DQ, size_t offs[6])
+__host__ __device__ inline size_t runs_lds_bytes(int Lf, int Ld, int nslot, int hf, int threads, size_t offs[6])
 {
     using R = typename RealOf<PREC>::T;
-    size_t o = 0;
-    offs[0] = o; o += runs_section((size_t)Lf * FieldRec<PREC, KIND>::FS * sizeof(R));
-    offs[1] = o; o += runs_section((size_t)Ld * nslot * sizeof(double));
-    offs[2] = o; o += runs_section((size_t)gq_cap(hf) * sizeof(int));
-    offs[3] = o; o += runs_section((size_t)DQ * sizeof(uint32_t));
-    offs[4] = o; o += runs_section((size_t)DQ * (3 + nslot) * sizeof(R));
-    offs[5] = o; o += 8 * sizeof(double);
-    return o + kRunsCtlBytes;
+    return runs_lds_layout(sizeof(R), FieldRec<PREC, KIND>::FS, Lf, Ld, nslot, hf, threads, offs);
 }
 
 // Threads per block of the run kernel.  One block per CU (the LDS tiles take
@@ -1063,8 +1039,8 @@ __device__ __forceinline__ void unit_shared(const RunGeo &G, int nslot, unsigned
 {
     using R = typename RealOf<PREC>::T;
     size_t offs[6];
-    const int dq = runs_queue<PREC>((int)blockDim.x);
-    runs_lds_bytes<PREC, KIND>(G.Lf, G.Ld, nslot, G.hf, dq, offs);
+    const int dq = runs_queue(sizeof(R), (int)blockDim.x);
+    runs_lds_bytes<PREC, KIND>(G.Lf, G.Ld, nslot, G.hf, (int)blockDim.x, offs);
     S.narrow = PREC == PL_F32_OFFSET && (flags & SF_NARROW);
     S.lds_f = reinterpret_cast<R *>(smem_raw + offs[0]);
     S.lds_d = reinterpret_cast<double *>(smem_raw + offs[1]);
@@ -1600,13 +1576,13 @@ StepKernel pick_runs_mix(int shape, int dim, int hf, int ts, int chl, int chd)
 template <int PREC>
 static size_t runs_item_lds(const Ctx *c, const ItemDesc &it, int hf, int nt)
 {
-    const int d3 = c->d.ndim >= 3, dq = runs_queue<PREC>(nt);
+    const int d3 = c->d.ndim >= 3;
     const int Lf = (it.tile[0] + 2 * hf) * (it.tile[1] + 2 * hf) * (d3 ? it.tile[2] + 2 * hf : 1);
     const int Ld = (it.tile[0] + 4) * (it.tile[1] + 4) * (d3 ? it.tile[2] + 4 : 1);
     size_t offs[6];
-    if (it.kind == PL_LORENTZ) return runs_lds_bytes<PREC, PL_LORENTZ>(Lf, Ld, it.nslot, hf, dq, offs);
-    if (it.kind == PL_DUST) return runs_lds_bytes<PREC, PL_DUST>(Lf, Ld, it.nslot, hf, dq, offs);
-    return runs_lds_bytes<PREC, PL_TRACER>(Lf, Ld, 0, hf, dq, offs);
+    if (it.kind == PL_LORENTZ) return runs_lds_bytes<PREC, PL_LORENTZ>(Lf, Ld, it.nslot, hf, nt, offs);
+    if (it.kind == PL_DUST) return runs_lds_bytes<PREC, PL_DUST>(Lf, Ld, it.nslot, hf, nt, offs);
+    return runs_lds_bytes<PREC, PL_TRACER>(Lf, Ld, 0, hf, nt, offs);
 }
 
 // Whether the footprint that the float32 sums go by (runs_sums.h) fits for every
