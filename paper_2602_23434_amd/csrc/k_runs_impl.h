@@ -1119,10 +1119,11 @@ __device__ __forceinline__ void unit_runs(const UnitC<PREC> &U, const RunGeo &G,
 // One work unit of the kernel that takes every species kind (a piece of tile t
 // of item I): stage the tile's field records (and clear its deposit tile),
 // advance the piece's runs, and flush the deposits; passive tracers are
-// advanced one particle at a time from the same field records.
-template <int PREC, int SHAPE, int DIM, int KIND, int HF, int TS, int CHS>
+// advanced one particle at a time from the same field records.  last(): see
+// unit_runs.
+template <int PREC, int SHAPE, int DIM, int KIND, int HF, int TS, int CHS, class Last>
 __device__ __forceinline__ void runs_unit(const ItemDesc &I, int t, int pbeg, int pend, int r_lo, int r_hi,
-                                          unsigned flags, int lds_bytes, unsigned char *smem_raw, int &err)
+                                          unsigned flags, int lds_bytes, unsigned char *smem_raw, int &err, Last last)
 {
     constexpr int KR = PREC == PL_F32_OFFSET ? 4 : 2;
     const bool do_sums = flags & SF_SUMS;
@@ -1148,9 +1149,10 @@ __device__ __forceinline__ void runs_unit(const ItemDesc &I, int t, int pbeg, in
             run_entry(runs[r], pbeg, pend, rs, rl);
             for (int q = 0; q < rl; ++q) tracer_particle<PREC, SHAPE, DIM>(U, G, S.lds_f, rs + q, err);
         }
+        if ((int)threadIdx.x >= (int)blockDim.x - 64) last();
     } else {
         const int entry = r_lo + (int)threadIdx.x < r_hi ? runs[r_lo + (int)threadIdx.x] : 0;
-        unit_runs<PREC, SHAPE, DIM, KIND, CHS, KR>(U, G, S, runs, pbeg, pend, r_lo, r_hi, entry, do_sums, err, []() {}, []() {});
+        unit_runs<PREC, SHAPE, DIM, KIND, CHS, KR>(U, G, S, runs, pbeg, pend, r_lo, r_hi, entry, do_sums, err, []() {}, last);
         if (do_sums && threadIdx.x < 8 && S.sums[threadIdx.x] != 0.0) global_add(I.psum + threadIdx.x, S.sums[threadIdx.x]);
         flush_unit<PREC, DIM, CHS>(U, G, S.lds_d);
     }
@@ -1502,7 +1504,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // One persistent launch over the items of every species kind of a call: each
 // claimed unit runs the unit body of its item's kind (uniform per block).
 // CHL and CHD fix the channel sets of the charged (rho J F) and dust (rho F)
-// items, or are 0 to take them at run time.
+// items, or are 0 to take them at run time.  The last wave claims and looks up
+// the next unit when it is through its own runs, while the others finish theirs.
 template <int PREC, int SHAPE, int DIM, int HF, int TS, int CHL, int CHD>
 __global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_runs_mix(const ItemDesc *__restrict__ items, int nitems, int total_units,
                                              unsigned *counter, int *errflags, unsigned flags, int lds_bytes)
@@ -1512,21 +1515,23 @@ __global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2,
     int err = 0;
     if (threadIdx.x == 0) ctl[RC_QI] = 0;
     runs_units(items, nitems, errflags, ctl);
-    for (;;) {
+    __syncthreads();
+    if (threadIdx.x < 64) runs_next(items, nitems, counter, ctl, ctl + RC_UNIT);
+    for (int slot = 0;; slot ^= 1) {
         __syncthreads();
-        if (threadIdx.x < 64) runs_next(items, nitems, counter, ctl, ctl + RC_UNIT);
-        __syncthreads();
-        auto word = [&](int k) -> int { return __builtin_amdgcn_readfirstlane(ctl[RC_UNIT + k]); };
+        const int *mine = ctl + RC_UNIT + RU_WORDS * slot;
+        auto word = [&](int k) -> int { return __builtin_amdgcn_readfirstlane(mine[k]); };
         if (word(RU_ITEM) < 0) break;                         // uniform
         const ItemDesc &I = items[word(RU_ITEM) & ~RU_HEAVY];
         const int t = word(RU_TILE), pbeg = word(RU_PBEG), pend = word(RU_PEND), lo = word(RU_RLO), hi = word(RU_RHI);
         const int kind = __builtin_amdgcn_readfirstlane(I.kind);
+        auto last = [&]() { runs_next(items, nitems, counter, ctl, ctl + RC_UNIT + RU_WORDS * (slot ^ 1)); };
         if (kind == PL_LORENTZ)
-            runs_unit<PREC, SHAPE, DIM, PL_LORENTZ, HF, TS, CHL>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err);
+            runs_unit<PREC, SHAPE, DIM, PL_LORENTZ, HF, TS, CHL>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err, last);
         else if (kind == PL_DUST)
-            runs_unit<PREC, SHAPE, DIM, PL_DUST, HF, TS, CHD>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err);
+            runs_unit<PREC, SHAPE, DIM, PL_DUST, HF, TS, CHD>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err, last);
         else
-            runs_unit<PREC, SHAPE, DIM, PL_TRACER, HF, TS, 0>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err);
+            runs_unit<PREC, SHAPE, DIM, PL_TRACER, HF, TS, 0>(I, t, pbeg, pend, lo, hi, flags, lds_bytes, smem_raw, err, last);
     }
     runs_latch(err, errflags);
     release_queues(counter, ctl);
