@@ -772,8 +772,13 @@ __global__ __launch_bounds__(kRunsBuildThreads) void k_runs_build(SortGroup g, c
 // order.  Largest-first claiming keeps a crowded tile from finishing last on
 // its CU, and splitting keeps one tile from outweighing a CU's share of the
 // step.  Every loop that contains a block scan has the same trip count in all
-// threads.
+// threads.  A thread takes kUnitTiles consecutive tiles per scan: a scan costs
+// about 1.5 us whatever it adds up, and the list of
+// 32768 tiles, one per thread and scan, held up the launch that it is part of (256^3
+// cells, 4e6 particles: a sort 853 us with a launch of 1024 threads of its own, 995 us
+// beside the moves, 783 us with eight tiles per thread).
 constexpr int kRankMax = 1024;
+constexpr int kUnitTiles = 8;
 __device__ __forceinline__ void unit_list(int32_t *runs, int np, int ntiles)
 {
     __shared__ uint32_t sh[kPermThreads / 64 + 1];
@@ -788,35 +793,59 @@ __device__ __forceinline__ void unit_list(int32_t *runs, int np, int ntiles)
     if (threadIdx.x == 0) s_total = 0ull;
     __syncthreads();
     unsigned long long mine = 0;
-    for (int t = threadIdx.x; t < ntiles; t += blockDim.x) mine += (unsigned long long)max(cnt[t], 0);
+    for (int t0 = threadIdx.x; t0 < ntiles; t0 += kUnitTiles * (int)blockDim.x) {
+        int c[kUnitTiles];                               // (all of them in flight)
+#pragma unroll
+        for (int q = 0; q < kUnitTiles; ++q) {
+            const int t = t0 + q * (int)blockDim.x;
+            c[q] = t < ntiles ? cnt[t] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < kUnitTiles; ++q) mine += (unsigned long long)max(c[q], 0);
+    }
     atomicAdd(&s_total, mine);
     __syncthreads();
     const long long total = (long long)s_total;
     const long long pz = max((total + kRunsSplit - 1) / kRunsSplit, (long long)kRunsMinPiece);
     const long long thr = 2 * (total / max(ntiles, 1)) + 1;
-    auto pieces = [&](int t) -> int {
-        const long long c = max(cnt[t], 0);
-        return (int)((c + pz - 1) / pz);
+    // (runs of an item < 2^29 and pz < 2^20: 32 bits hold the sum)
+    auto pieces = [&](int c) -> uint32_t { return ((uint32_t)c + (uint32_t)pz - 1u) / (uint32_t)pz; };
+    // this thread's tiles from t on: pieces, and which are split or heavy (bits)
+    auto look = [&](int t, uint32_t k[kUnitTiles], int c[kUnitTiles]) -> uint32_t {
+        uint32_t heavy = 0;
+#pragma unroll
+        for (int q = 0; q < kUnitTiles; ++q) c[q] = t + q < ntiles ? max(cnt[t + q], 0) : 0;
+#pragma unroll
+        for (int q = 0; q < kUnitTiles; ++q) {
+            k[q] = pieces(c[q]);
+            heavy |= (k[q] >= 2 || (long long)c[q] > thr ? 1u : 0u) << q;
+        }
+        return heavy;
     };
+    const int stride = (int)blockDim.x * kUnitTiles;
+    typedef int32_t I2 __attribute__((ext_vector_type(2), aligned(4)));
     auto emit = [&](long long at, int t, int k) {
         for (int p = 0; p < k; ++p)
-            if (at + p < cap) {
-                units[2 * (at + p)] = t;
-                units[2 * (at + p) + 1] = p | (k << 16);
-            }
+            if (at + p < cap) *reinterpret_cast<I2 *>(units + 2 * (at + p)) = I2{t, p | (k << 16)};
     };
     // ranked tiles: the first kRankMax split or heavy tiles in index order
     uint32_t hbase = 0;
-    for (int t0 = 0; t0 < ntiles; t0 += blockDim.x) {
-        const int t = t0 + threadIdx.x;
-        const int k = t < ntiles ? pieces(t) : 0;
-        const bool h = t < ntiles && (k >= 2 || (long long)cnt[t] > thr);
+    for (int t0 = 0; t0 < ntiles; t0 += stride) {
+        const int t = t0 + (int)threadIdx.x * kUnitTiles;
+        uint32_t k[kUnitTiles];
+        int c[kUnitTiles];
+        const uint32_t heavy = look(t, k, c);
         uint32_t tot;
-        const uint32_t hp = hbase + block_exclusive_scan(h ? 1u : 0u, sh, tot);
-        if (h && hp < (uint32_t)kRankMax) {
-            rk_tile[hp] = t;
-            rk_cnt[hp] = cnt[t];
-            rk_k[hp] = k;
+        uint32_t hp = hbase + block_exclusive_scan((uint32_t)__popc(heavy), sh, tot);
+#pragma unroll
+        for (int q = 0; q < kUnitTiles; ++q) {
+            if (!((heavy >> q) & 1u)) continue;
+            if (hp < (uint32_t)kRankMax) {
+                rk_tile[hp] = t + q;
+                rk_cnt[hp] = c[q];
+                rk_k[hp] = (int)k[q];
+            }
+            ++hp;
         }
         hbase += tot;
     }
@@ -846,16 +875,27 @@ __device__ __forceinline__ void unit_list(int32_t *runs, int np, int ntiles)
     // every other non-empty tile in index order
     uint32_t hb = 0;
     long long lb = nranked;
-    for (int t0 = 0; t0 < ntiles; t0 += blockDim.x) {
-        const int t = t0 + threadIdx.x;
-        const int k = t < ntiles ? pieces(t) : 0;
-        const bool h = t < ntiles && (k >= 2 || (long long)cnt[t] > thr);
+    for (int t0 = 0; t0 < ntiles; t0 += stride) {
+        const int t = t0 + (int)threadIdx.x * kUnitTiles;
+        uint32_t k[kUnitTiles];
+        int c[kUnitTiles];
+        const uint32_t heavy = look(t, k, c);
         uint32_t toth, totl;
-        const uint32_t hp = hb + block_exclusive_scan(h ? 1u : 0u, sh, toth);
-        const bool ranked = h && hp < (uint32_t)kRankMax;
-        const uint32_t kl = (t < ntiles && !ranked) ? (uint32_t)k : 0u;
-        const uint32_t lp = block_exclusive_scan(kl, sh, totl);
-        if (kl) emit(lb + lp, t, (int)kl);
+        uint32_t hp = hb + block_exclusive_scan((uint32_t)__popc(heavy), sh, toth);
+        uint32_t mine_l = 0;
+#pragma unroll
+        for (int q = 0; q < kUnitTiles; ++q) {
+            const bool h = (heavy >> q) & 1u;
+            if (h && hp < (uint32_t)kRankMax) k[q] = 0;      // ranked
+            hp += h ? 1u : 0u;
+            mine_l += k[q];
+        }
+        long long at = lb + block_exclusive_scan(mine_l, sh, totl);
+#pragma unroll
+        for (int q = 0; q < kUnitTiles; ++q) {
+            if (k[q]) emit(at, t + q, (int)k[q]);
+            at += k[q];
+        }
         hb += toth;
         lb += totl;
     }
