@@ -31,14 +31,21 @@ struct GroupSize {
 };
 
 // Whether an item of np particles and `keys` distinct keys joins a group:
-// while the scratch holds the particles (cap), the keys stay below the run
-// table's sentinel 2^32 - 1 (k_runs_build marks "no neighbour" with it, so no
-// particle may have it as its key), and the group takes at most one pass more
-// than its largest item.
+//  * the scratch holds the particles (cap);
+//  * the keys stay below the run table's sentinel 2^32 - 1 (k_runs_build marks "no
+//    neighbour" with it, so no particle may have it as its key);
+//  * the digits' passes stay as many as its largest item's, or the group is small:
+//    one pass more over all its particles costs more than the launches that
+//    sorting the item by itself takes.  us per sort, together and apart: 256^3 cells,
+//    whose 2^24 keys take three passes and with any other item four, 1e6 particles
+//    with 5000 on 32^3 602 and 627, 4e6 802 and 823, 2^24 1810 and 1774; 1e6 with 5e5
+//    979 and 1115.
+constexpr int64_t kExtraPass = 1 << 22;
 inline bool group_takes(const GroupSize &g, int64_t np, uint64_t keys, int64_t cap)
 {
     const uint64_t most = g.most > keys ? g.most : keys;
-    return g.np + np <= cap && g.keys + keys <= 0xffffffffull && sort_passes(g.keys + keys) <= sort_passes(most) + 1;
+    if (g.np + np > cap || g.keys + keys > 0xffffffffull) return false;
+    return sort_passes(g.keys + keys) <= sort_passes(most) + (g.np + np <= kExtraPass ? 1 : 0);
 }
 
 // Memory that the items of a group read and write.  Sorted one after another,

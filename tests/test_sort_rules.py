@@ -71,6 +71,17 @@ def test_keys_up_to_the_sentinel_join(rules):
     assert not rules.takes(10, 2 ** 31, 2 ** 31, 91, 1, 100)      # the scratch's particles
 
 
+@pytest.mark.parametrize("cells,np,small_cells,small_np,want", [
+    (256 ** 3, 1 << 24, 32 ** 3, 1000, False),      # 2^24 keys, three passes: a fourth over 16 million particles
+    (255 ** 3, 1 << 24, 32 ** 3, 1000, True),       # three passes with both
+    (256 ** 3, 500_000, 32 ** 3, 1000, True),       # a fourth pass over half a million
+    (16 ** 3, 60_000, 4096 * 15, 4000, True),
+    (96 ** 3, 5_000_000, 96 ** 3, 1_000_000, True),
+])
+def test_no_further_pass_over_many_particles(rules, cells, np, small_cells, small_np, want):
+    assert bool(rules.takes(np, cells, cells, small_np, small_cells, 1 << 30)) == want
+
+
 def _joined(rules, ranges):
     flat = [int(v) for r in ranges for v in r]
     return rules.joined((C.c_int64 * len(flat))(*flat), len(ranges))
