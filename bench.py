@@ -304,7 +304,7 @@ def spectra_leg(torch, B, driver, inputs, steps=10):
              "unit": "particle-spectra/s",
              "roofline": {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                           "frac": ach / HBM_PEAK_GBS, "alg_bytes_per_launch": alg,
-                          "kernel": "pl::k_spectra<1, 2, 3>"},
+                          "kernel": "pl::k_spectra<1, 2, 3, 1>"},
              "paper_context": "Particles_Spectra: 190 ms per step for 16.4 M particles on one A100 (Table 1)"}
         log(f"[bench] spectra: {ms:.3f} ms/step, {ach:.0f} GB/s algorithmic")
         return r

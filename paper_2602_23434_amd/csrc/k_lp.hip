@@ -3,7 +3,10 @@
 // with the holes-and-fillers compaction and injection (Sec. 3.2).
 #include <hip/hip_runtime.h>
 
+#include <string.h>
+
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "pl_device.h"
@@ -168,10 +171,47 @@ __device__ __forceinline__ void sample_records(const ItemDesc &I, gptr<const dou
     }
 }
 
-// Fluid records of an item's box: B, gas velocity, four-divergence, 0 per cell.
-__global__ __launch_bounds__(256) void k_fluid_records(const ItemDesc *items, int k, double *rec)
+// Cell of particle p for the order check (any cell for a bad coordinate).
+template <int PREC, int DIM>
+__device__ __forceinline__ void rough_cell(const ItemDesc &I, int p, int c[3])
 {
-    const ItemDesc &I = items[k];
+    if (PREC == PL_F32_OFFSET) {
+        unpack_cell(I.cell[p], c[0], c[1], c[2]);
+    } else {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) c[a] = a < DIM ? (int)((const double *)I.x[a])[p] : 0;
+    }
+}
+
+// Fluid records of an item's box: B, gas velocity, four-divergence, 0 per cell;
+// or none when the particles are in some order of place, whose neighbours in the
+// arrays read the same lines of the fields (flag: whether the records are there).
+// Every block looks at the same 64 pairs of consecutive particles, in two
+// stretches (64 places all over the arrays cost 25 us in address translation): in
+// order when most are within 8 cells of each other.
+template <int PREC, int DIM>
+__global__ __launch_bounds__(256) void k_fluid_records(TableArgs<1> item, double *rec, int *flag)
+{
+    const ItemDesc &I = item[0];
+    __shared__ int s_near;
+    if (threadIdx.x < 64) {
+        const int p = (threadIdx.x < 32 ? I.np / 3 : I.np / 3 * 2) + (int)(threadIdx.x & 31);
+        int a[3], b[3];
+        rough_cell<PREC, DIM>(I, p, a);
+        rough_cell<PREC, DIM>(I, p + 1, b);
+        bool near = true;
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+            const int gap = abs(a[d] - b[d]);
+            near = near && min(gap, abs(I.n[d] - gap)) <= 8;
+        }
+        const int n = __popcll(__ballot(near));
+        if (threadIdx.x == 0) s_near = n;
+    }
+    __syncthreads();
+    const bool ordered = s_near > 32;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *flag = !ordered;
+    if (ordered) return;
     const long cells = (long)I.n[0] * I.n[1] * I.n[2];
     typedef double D2 __attribute__((ext_vector_type(2)));
     for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < cells; e += (long)gridDim.x * blockDim.x) {
@@ -310,7 +350,7 @@ __device__ __forceinline__ void spectra_coef(const ItemDesc &I, const double q[7
 // One block per 256 particles of one item: each thread samples the fluid at
 // its particle and leaves the step's coefficients in LDS; the block then
 // streams its 256 contiguous spectral rows (particle-major).
-template <int PREC, int SHAPE, int DIM, int W>
+template <int PREC, int SHAPE, int DIM, int W, bool REC>
 __device__ __forceinline__ void spectra_block(const ItemDesc &I, int p0, int cnt, const SpecPar &sp,
                                               gptr<const double> rec, double *sq, double *sE, double *siE, double *sb,
                                               int &err)
@@ -321,7 +361,7 @@ __device__ __forceinline__ void spectra_block(const ItemDesc &I, int p0, int cnt
     {
         const int t = threadIdx.x;
         double E = 1.0, iE = 1.0, bphi = 0.0, q[7];
-        if (rec) {
+        if constexpr (REC) {
             // (each wave reads back what it wrote itself)
             double *out = sq + 7 * (t & ~63);
             sample_records<PREC, SHAPE, DIM>(I, rec, t < cnt, p0 + t, out, err);
@@ -340,11 +380,18 @@ __device__ __forceinline__ void spectra_block(const ItemDesc &I, int p0, int cnt
     spectra_rows<W>(S, sE, siE, sb);
 }
 
-template <int PREC, int SHAPE, int DIM>
-__global__ __launch_bounds__(kSpecThreads) void k_spectra(const ItemDesc *__restrict__ items, int nitems, SpecPar sp,
+// The descriptors of up to N items as kernel arguments, or (0) a pointer to them.
+// Three waves per SIMD: with four the compiler keeps fewer loads of the rows in
+// flight (1e6 particles of 128 points in order of place, a launch that can sample
+// either way: 865 us against 824).
+template <int N> struct SpecItems { using T = TableArgs<N>; };
+template <> struct SpecItems<0> { using T = const ItemDesc *; };
+
+template <int PREC, int SHAPE, int DIM, int N, bool REC>
+__global__ __launch_bounds__(kSpecThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_spectra(typename SpecItems<N>::T items, int nitems, SpecPar sp,
                                                           const double *rec, int *errflags)
 {
-    __shared__ double s_q[7 * kSpecThreads];
+    __shared__ double s_q[REC ? 7 * kSpecThreads : 1];
     __shared__ double s_E[kSpecThreads], s_iE[kSpecThreads], s_b[kSpecThreads];
     const int g = blockIdx.x;
     int iti = 0;
@@ -355,22 +402,65 @@ __global__ __launch_bounds__(kSpecThreads) void k_spectra(const ItemDesc *__rest
     const int cnt = min(kSpecThreads, I.np - p0);
     int err = 0;
     const gptr<const double> gr = (gptr<const double>)rec;
-    if ((I.nb & 1) == 0) spectra_block<PREC, SHAPE, DIM, 2>(I, p0, cnt, sp, gr, s_q, s_E, s_iE, s_b, err);
-    else spectra_block<PREC, SHAPE, DIM, 1>(I, p0, cnt, sp, gr, s_q, s_E, s_iE, s_b, err);
+    auto block = [&](auto with) {
+        constexpr bool R = decltype(with)::value;
+        if ((I.nb & 1) == 0) spectra_block<PREC, SHAPE, DIM, 2, R>(I, p0, cnt, sp, gr, s_q, s_E, s_iE, s_b, err);
+        else spectra_block<PREC, SHAPE, DIM, 1, R>(I, p0, cnt, sp, gr, s_q, s_E, s_iE, s_b, err);
+    };
+    // (the word after the error bits: whether the records were made)
+    if constexpr (REC) {
+        if (errflags[1]) block(std::true_type{});             // uniform
+        else block(std::false_type{});
+    } else {
+        block(std::false_type{});
+    }
     if (err) atomicOr(errflags, err);
 }
 
-// Records pay where the particles are not too few for the pass that builds them
-// (120 bytes per cell) and the scratch holds them.  Measured on 2^18 cells with
-// 1e6 particles of 128 points: in no order 2364 us per call from the fields,
-// 874 from records; stored cell by cell 839 and 852 (the rows' traffic
-// bounds both).
+// Records are worth their launch where the particles are not too few for the
+// pass that makes them (120 bytes per cell) and the scratch holds them, which is
+// that of one box: a call of several items samples the fields.  Particles in some
+// order of place only pay for the check.  us per call from the fields and by this
+// rule, in no order and cell by cell: 64^3 cells, 1e6 particles of 128 points 2364
+// and 874, 833 and 824; 262144 of 32 points 533 and 121, 73 and 66; 32^3 cells,
+// 32768 of 32 points 48 and 30, 24.5 and 19.3 (the smaller ones also for the
+// descriptors that go with the launch: a copy before it cost 5 to 7 us).
+constexpr int kRecordsMinNp = 32768;
 static bool spectra_records(const Ctx *c, const ItemDesc &it)
 {
     const long cells = (long)it.n[0] * it.n[1] * it.n[2];
-    return cells <= c->record_cells && it.np >= cells / 2 && it.np >= 32768;
+    return cells <= c->record_cells && it.np >= cells / 2 && it.np >= kRecordsMinNp;
 }
 
+template <int N, bool REC>
+static hipError_t spectra_items(Ctx *c, const typename SpecItems<N>::T &items, int nitems, int units, const SpecPar &sp,
+                                const double *rec)
+{
+    using K = void (*)(typename SpecItems<N>::T, int, SpecPar, const double *, int *);
+    K k = nullptr;
+    const bool f64 = c->d.prec == PL_F64, tsc = c->d.shape == PL_TSC, d3 = c->d.ndim == 3;
+#define PL_SK(P, S, D) \
+    if (f64 == (P == PL_F64) && tsc == (S == PL_TSC) && d3 == (D == 3)) k = k_spectra<P, S, D, N, REC>;
+    PL_SK(PL_F64, PL_TSC, 3) PL_SK(PL_F64, PL_TSC, 2) PL_SK(PL_F64, PL_CIC, 3) PL_SK(PL_F64, PL_CIC, 2)
+    PL_SK(PL_F32_OFFSET, PL_TSC, 3) PL_SK(PL_F32_OFFSET, PL_TSC, 2) PL_SK(PL_F32_OFFSET, PL_CIC, 3)
+    PL_SK(PL_F32_OFFSET, PL_CIC, 2)
+#undef PL_SK
+    if (!k) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k, dim3(units), dim3(kSpecThreads), 0, c->stream, items, nitems, sp, rec, c->errflags);
+    c->stats[0]++;
+    return hipGetLastError();
+}
+
+template <int N> static TableArgs<N> table_args(const std::vector<ItemDesc> &host)
+{
+    TableArgs<N> t;
+    memset(&t, 0, sizeof(t));
+    for (size_t i = 0; i < host.size(); ++i) t.d[i] = host[i];
+    return t;
+}
+
+// The descriptors of up to kTableArgs items go with the launch: no copy or
+// kernel of their own before it.
 hipError_t launch_spectra(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc> &host, double cr,
                           double u_rad, double ub)
 {
@@ -378,27 +468,20 @@ hipError_t launch_spectra(Ctx *c, const ItemDesc *table, const std::vector<ItemD
     for (const ItemDesc &it : host) units = std::max(units, it.unit_begin + it.nunits);
     if (units == 0) return hipSuccess;
     SpecPar sp{cr, u_rad, ub, c->d.c > 0.0 ? 1.0 / (c->d.c * c->d.c) : 0.0};
-    using K = void (*)(const ItemDesc *, int, SpecPar, const double *, int *);
-    K k = nullptr;
-    const bool f64 = c->d.prec == PL_F64, tsc = c->d.shape == PL_TSC, d3 = c->d.ndim == 3;
-#define PL_SK(P, S, D) \
-    if ((P == PL_F64) == f64 && (S == PL_TSC) == tsc && (D == 3) == d3) k = k_spectra<P, S, D>;
-    PL_SK(PL_F64, PL_TSC, 3) PL_SK(PL_F64, PL_TSC, 2) PL_SK(PL_F64, PL_CIC, 3) PL_SK(PL_F64, PL_CIC, 2)
-    PL_SK(PL_F32_OFFSET, PL_TSC, 3) PL_SK(PL_F32_OFFSET, PL_TSC, 2) PL_SK(PL_F32_OFFSET, PL_CIC, 3)
-    PL_SK(PL_F32_OFFSET, PL_CIC, 2)
-#undef PL_SK
-    if (!k) return hipErrorInvalidConfiguration;
-    const double *rec = nullptr;
-    if (host.size() == 1 && spectra_records(c, host[0])) {
-        const long cells = (long)host[0].n[0] * host[0].n[1] * host[0].n[2];
-        hipLaunchKernelGGL(k_fluid_records, dim3((int)std::min<long>((cells + 255) / 256, 16L * c->num_cu)), dim3(256), 0,
-                           c->stream, table, 0, c->records);
-        c->stats[0]++;
-        rec = c->records;
-    }
-    hipLaunchKernelGGL(k, dim3(units), dim3(kSpecThreads), 0, c->stream, table, (int)host.size(), sp, rec, c->errflags);
+    const int n = (int)host.size();
+    if (n > kTableArgs) return spectra_items<0, false>(c, table, n, units, sp, nullptr);
+    if (n > 1) return spectra_items<kTableArgs, false>(c, table_args<kTableArgs>(host), n, units, sp, nullptr);
+    const TableArgs<1> item = table_args<1>(host);
+    if (!spectra_records(c, host[0])) return spectra_items<1, false>(c, item, 1, units, sp, nullptr);
+    const long cells = (long)host[0].n[0] * host[0].n[1] * host[0].n[2];
+    using K = void (*)(TableArgs<1>, double *, int *);
+    const bool f64 = c->d.prec == PL_F64, d3 = c->d.ndim == 3;
+    const K k = f64 ? (d3 ? k_fluid_records<PL_F64, 3> : k_fluid_records<PL_F64, 2>)
+                    : (d3 ? k_fluid_records<PL_F32_OFFSET, 3> : k_fluid_records<PL_F32_OFFSET, 2>);
+    hipLaunchKernelGGL(k, dim3((int)std::min<long>((cells + 255) / 256, 16L * c->num_cu)), dim3(256), 0, c->stream,
+                       item, c->records, c->errflags + 1);
     c->stats[0]++;
-    return hipGetLastError();
+    return spectra_items<1, true>(c, item, 1, units, sp, c->records);
 }
 
 // ---------------------------------------------------------------------------

@@ -183,11 +183,6 @@ __global__ void k_zero_items(const ItemDesc *items)
 // 32 x 32 box with 4096 particles took 23.9 us from call to call with the copy
 // and 18.8 us with this kernel (10 eager steps and a sort: 239 and 188 us).  More
 // items than fit 4 KB of arguments take the ring.
-template <int N> struct TableArgs {
-    ItemDesc d[N];
-};
-static_assert(sizeof(TableArgs<kTableArgs>) + 32 <= 4096, "kernel arguments");
-
 template <int N>
 __global__ void k_zero_table(TableArgs<N> t, int n, bool zero, ItemDesc *table)
 {

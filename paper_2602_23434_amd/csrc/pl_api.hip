@@ -711,8 +711,10 @@ pl_status pl_part_spectra(pl_ctx *ctx, const pl_item *items, int nitems, double 
         host[i].nunits = host[i].np > 0 ? (host[i].np + 255) / 256 : 0;
         units += host[i].nunits;
     }
-    pl_status st = upload_table(c, host, c->table);
-    if (st != PL_OK) return st;
+    if (host.size() > (size_t)kTableArgs) {
+        const pl_status st = upload_table(c, host, c->table);
+        if (st != PL_OK) return st;
+    }
     hipError_t e = launch_spectra(c, c->table, host, sd->cr, sd->u_rad, sd->ub);
     if (e == hipErrorInvalidConfiguration) return PL_EUNSUPPORTED;
     return e == hipSuccess ? PL_OK : PL_EHIP;

@@ -126,7 +126,7 @@ struct Ctx {
     // device scratch
     ItemDesc *table = nullptr;       // max_items descriptors for non-graph calls
     unsigned *counters = nullptr;    // work counters: kCounterStride per launch stage
-    int *errflags = nullptr;         // latched error bits
+    int *errflags = nullptr;         // [0] latched error bits, [1] whether the spectral update made its records
     double *sums = nullptr;          // max_items * 16
     uint32_t *keys[2] = {nullptr, nullptr};
     uint32_t *idx[2] = {nullptr, nullptr};
@@ -202,6 +202,12 @@ hipError_t launch_zero(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc
 // The table of a call of up to kTableArgs items, written by a kernel that also
 // zeroes their moments (zero).
 constexpr int kTableArgs = 4;
+// Descriptors as kernel arguments.  More than kTableArgs do not fit 4 KB.
+template <int N> struct TableArgs {
+    ItemDesc d[N];
+    __host__ __device__ const ItemDesc &operator[](int k) const { return d[k]; }
+};
+static_assert(sizeof(TableArgs<kTableArgs>) + 64 <= 4096, "kernel arguments");
 hipError_t launch_table(Ctx *c, const std::vector<ItemDesc> &host, bool zero, ItemDesc *table);
 hipError_t launch_zero_sums(Ctx *c, double *sums, int n);
 hipError_t launch_grid_sums(Ctx *c, const ItemDesc &it, double *out8);
@@ -210,6 +216,7 @@ hipError_t launch_unpack(Ctx *c, const ItemDesc &it, int prec, int ndim, double 
 
 // Lagrangian-particle extras (k_lp.hip)
 constexpr int kMaxBins = 4096;
+// (table: the items' descriptors on the device, for more than kTableArgs items)
 hipError_t launch_spectra(Ctx *c, const ItemDesc *table, const std::vector<ItemDesc> &host, double cr,
                           double u_rad, double ub);
 // Deletion at open boundaries and compaction of one item; writes the new
