@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "pl_internal.h"
+#include "scratch.h"
 
 using namespace pl;
 
@@ -548,13 +549,15 @@ pl_status pl_part_init(pl_ctx **out, const pl_init_desc *d)
               hipMalloc(&c->hist, (size_t)c->hist_cap * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&c->hist_scan, (size_t)c->hist_cap * sizeof(uint32_t)) == hipSuccess &&
               hipHostMalloc(&c->pinned, Ctx::kRing * mi * sizeof(ItemDesc), hipHostMallocDefault) == hipSuccess;
-    // keys and indices in one allocation, which also holds the spectral update's
-    // 64-byte fluid records of every cell where there is a particle per cell or
-    // more (with four or more it needs nothing beyond the keys)
+    // keys and indices in one allocation, with the spectral update's records
     const size_t npa = (np + 63) & ~(size_t)63;
-    size_t slab = 4 * npa * sizeof(uint32_t);
-    if (ok && max_cells <= (int64_t)np) slab = std::max(slab, (size_t)max_cells * 64);
-    ok = ok && hipMalloc(&c->slab, slab) == hipSuccess;
+    size_t slab = (size_t)slab_bytes((int64_t)np, max_cells);
+    if (ok && hipMalloc(&c->slab, slab) != hipSuccess) {
+        (void)hipGetLastError();
+        c->slab = nullptr;
+        slab = (size_t)keys_bytes((int64_t)np);
+        ok = hipMalloc(&c->slab, slab) == hipSuccess;
+    }
     for (int k = 0; ok && k < 2; ++k) {
         c->keys[k] = static_cast<uint32_t *>(c->slab) + (size_t)k * npa;
         c->idx[k] = static_cast<uint32_t *>(c->slab) + (size_t)(2 + k) * npa;
