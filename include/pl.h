@@ -446,8 +446,12 @@ pl_status pl_part_set_stream(pl_ctx *ctx, void *stream);
  * (1: rho J F of charged particles, 2: rho F of dust, 3: every channel of
  * charged particles, 0: taken at run time;
  * a mixed launch reports its charged items' set)
- * and hf the field halo in cells (1 or 2). */
-#define PL_NSTATS 8
+ * and hf the field halo in cells (1 or 2), out[8] launches of the tile kernels
+ * that group their particles by cell themselves (tiled calls, push-only and
+ * deposit-only calls of the run algorithm, and binned plain calls where they
+ * pay).  out[0] leaves out what only brings a call's item table to the device (a
+ * copy, or a kernel with the table as its arguments). */
+#define PL_NSTATS 9
 pl_status pl_part_stats(pl_ctx *ctx, int64_t *out, int n);
 
 /* Free the context and its scratch (synchronises first).  NULL is a no-op. */

@@ -15,7 +15,7 @@ LIB_PATH = os.path.join(HERE, "libpl.so")
 
 PL_OK, PL_EINVAL, PL_ENOMEM, PL_EHIP, PL_EUNSUPPORTED, PL_ECFL, PL_ENONFINITE, PL_ENOTSORTED, PL_ENOSPACE = range(9)
 PL_NOALLOC_MAX_NP = 1 << 20
-PL_NSTATS = 8
+PL_NSTATS = 9
 PL_F64, PL_F32_OFFSET = 0, 1
 PL_CIC, PL_TSC = 1, 2
 PL_LORENTZ, PL_DUST, PL_TRACER = 0, 1, 2

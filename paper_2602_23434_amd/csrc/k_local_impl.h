@@ -45,6 +45,7 @@
 namespace pl {
 
 constexpr int kLocalThreads = 512, kLocalSmall = 256;
+static_assert(kLocalThreads <= 8 * 64, "scan words of local_scan");
 constexpr int kLocalRounds = 5;        // rounds of runs counted together (11 bits each in 64)
 constexpr int kLocalMaxCells = 2047;   // cells of a tile and its ring: fits 11 bits
 constexpr int kLocalMaxCap = 8192;     // particles of a chunk: 13 bits of a run entry, 2 bits of length
@@ -95,7 +96,7 @@ __host__ __device__ inline LocalLds local_lds(int mode, int Lf, int Ld, int E, i
 }
 
 // Block-wide exclusive sums of a 64-bit and a 32-bit value; the totals go to
-// ta and tb.  sh: 16 64-bit words per wave of the block.
+// ta and tb.  sh: 16 64-bit words (of up to eight waves).
 __device__ __forceinline__ void local_scan(unsigned long long a, unsigned b, unsigned long long *sh,
                                            unsigned long long &ea, unsigned &eb, unsigned long long &ta, unsigned &tb)
 {
@@ -692,6 +693,7 @@ hipError_t launch_local_impl(Ctx *c, const ItemDesc *table, const ItemDesc *host
     hipLaunchKernelGGL(k, dim3(grid), dim3(pl.nt), pl.lds, c->stream, table, nitems, units, counter,
                        c->errflags, sf, pl.cap, (int)pl.lds - 64);
     c->stats[0]++;
+    c->stats[8]++;
     return hipGetLastError();
 }
 

@@ -152,8 +152,8 @@ struct Ctx {
 
     // launches, graph replays, graph captures, sorts, run-kernel launches, run
     // groups on the tiled kernel, fixed-shape run-kernel launches, variant of
-    // the last run-kernel launch (pl.h, pl_part_stats)
-    int64_t stats[PL_NSTATS] = {0, 0, 0, 0, 0, 0, 0, 0};
+    // the last run-kernel launch, self-grouping launches (pl.h, pl_part_stats)
+    int64_t stats[PL_NSTATS] = {};
 
     // p.fp arrays whose particles a sort has reordered since a gather_push
     // last wrote them: a deposit of F from them is refused
