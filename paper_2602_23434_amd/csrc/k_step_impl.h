@@ -24,9 +24,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <map>
+#include <tuple>
 #include <vector>
 
+#include "launch_cache.h"
 #include "pl_device.h"
 
 namespace pl {
@@ -617,15 +618,13 @@ static StepKernel pick_kernel(int shape, int dim, bool tiled, int kind, int ts, 
 
 static inline int resident_blocks(Ctx *c, StepKernel k, int block, size_t lds)
 {
-    static std::map<std::pair<const void *, std::pair<int, size_t>>, int> cache;
-    auto key = std::make_pair((const void *)k, std::make_pair(block, lds));
-    auto f = cache.find(key);
-    if (f != cache.end()) return f->second;
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, block, lds) != hipSuccess || per_cu < 1) per_cu = 1;
-    int r = per_cu * c->num_cu;
-    cache[key] = r;
-    return r;
+    using Key = std::tuple<int, const void *, int, size_t>;          // device, kernel, threads, LDS bytes
+    static LaunchCache<Key> cache;
+    return cache.get(Key(c->device, (const void *)k, block, lds), [&]() {
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, block, lds) != hipSuccess || per_cu < 1) per_cu = 1;
+        return per_cu * c->num_cu;
+    });
 }
 
 template <int PREC>
