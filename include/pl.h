@@ -163,14 +163,15 @@ typedef struct {
     const pl_species_desc *species;  /* host array, copied */
     int max_items;                   /* most items any one call passes (>= 1) */
     int64_t max_np;                  /* most particles in any one item (sizes the sort scratch) */
-    int block;                       /* threads per block of the particle kernels (64..512, multiple of 64;
-                                        with PL_ALGO_RUNS: 512, the run-based kernel's block (on small
-                                        2D tiles it takes its own choice));
-                                        0 = default */
+    int block;                       /* threads per block of the one-particle-per-thread kernels
+                                        (64..512, multiple of 64; with PL_ALGO_RUNS: 512); 0 = default.
+                                        The run-based kernel and the tile kernels that group their
+                                        particles themselves have blocks of their own */
     void *stream;                    /* hipStream_t for all work; NULL = the null stream */
-    const char *tune_cache;          /* nullable: file written by the autotuner ("key value" lines: block,
-                                        runs_block, tile, and one_launch 0 to give each species kind its
-                                        own launch in fused run-based steps) */
+    const char *tune_cache;          /* nullable: file written by the autotuner ("key value" lines: block
+                                        and runs (a contiguous stretch of particles per thread) of the
+                                        one-particle-per-thread kernels, tile, and one_launch 0 to give
+                                        each species kind its own launch in fused run-based steps) */
 } pl_init_desc;
 
 /*

@@ -669,8 +669,8 @@ __device__ __forceinline__ void batch_dep(const UnitC<PREC> &U, const RunGeo &G,
     if (any_dco) batch_deposit<PREC, SHAPE, DIM, CHS, KR, DACC>(U, G, S, db, pos, mu, dco);
 }
 
-// Stored state of one batch (up to KR consecutive particles), fetched from
-// HBM one batch ahead of its use so the loads overlap the previous batch.
+// Stored state of one batch (up to KR particles): fetched when the batch starts
+// (run kernel) or while the batch before it deposits (self-grouping kernels).
 template <int PREC, int DIM, int KR> struct BatchRaw {
     using R = typename RealOf<PREC>::T;
     typename Pos<PREC, DIM>::Raw pr[KR];
@@ -1360,7 +1360,7 @@ __device__ __forceinline__ void runs_latch(int err, int *errflags)
 // the launch flags; TS and HF fixed make every LDS stencil offset an
 // immediate.  NT: threads per block; with kRunsSmall two blocks share a CU.
 template <int PREC, int SHAPE, int DIM, int KIND, int HF, int TS, int CHS, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_runs(const ItemDesc *__restrict__ items, int nitems, int total_units,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_runs(const ItemDesc *__restrict__ items, int nitems,
                                              unsigned *counter, int *errflags, unsigned flags, int lds_bytes)
 {
     using R = typename RealOf<PREC>::T;
@@ -1507,7 +1507,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // items, or are 0 to take them at run time.  The last wave claims and looks up
 // the next unit when it is through its own runs, while the others finish theirs.
 template <int PREC, int SHAPE, int DIM, int HF, int TS, int CHL, int CHD>
-__global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_runs_mix(const ItemDesc *__restrict__ items, int nitems, int total_units,
+__global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_runs_mix(const ItemDesc *__restrict__ items, int nitems,
                                              unsigned *counter, int *errflags, unsigned flags, int lds_bytes)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1541,39 +1541,52 @@ __global__ __launch_bounds__(kRunsThreads) __attribute__((amdgpu_waves_per_eu(2,
 // Host side
 // ---------------------------------------------------------------------------
 
+using RunsKernel = void (*)(const ItemDesc *, int, unsigned *, int *, unsigned, int);
+
+// The variants with fixed shapes are those whose LDS (160 KB) allows them and
+// that no wider halo replaces: with a two-cell field halo, and in float64 on 8^3
+// tiles with one cell and seven channels; float64 with every channel has no room
+// on 8^3.  A launch that none of them fits takes the run-time shapes.
 template <int PREC>
-static StepKernel pick_runs(int shape, int dim, int kind, int hf, int ts, int chs, int nt)
+static RunsKernel pick_runs(int shape, int dim, int kind, int hf, int ts, int chs, int nt)
 {
 #define PL_RN(S, D, K, HF_, TS_, CHS_, NT_) \
     if (shape == S && dim == D && kind == K && hf == HF_ && ts == TS_ && chs == CHS_ && nt == NT_) \
         return k_runs<PREC, S, D, K, HF_, TS_, CHS_, NT_>;
 #define PL_R(S, D, K, HF_, TS_, CHS_) PL_RN(S, D, K, HF_, TS_, CHS_, kRunsThreads)
 #define PL_RG(S, D) PL_R(S, D, PL_LORENTZ, 0, 0, 0) PL_R(S, D, PL_DUST, 0, 0, 0)
-#define PL_RF(HF_, TS_) PL_R(PL_TSC, 3, PL_LORENTZ, HF_, TS_, 1) PL_R(PL_TSC, 3, PL_DUST, HF_, TS_, 2)
     PL_RG(PL_TSC, 3) PL_RG(PL_TSC, 2) PL_RG(PL_CIC, 3) PL_RG(PL_CIC, 2)
-    PL_RF(1, 1) PL_RF(2, 1) PL_RF(1, 2) PL_RF(2, 2)
     PL_RN(PL_TSC, 2, PL_LORENTZ, 0, 0, 0, kRunsSmall) PL_RN(PL_TSC, 2, PL_DUST, 0, 0, 0, kRunsSmall)
     PL_RN(PL_CIC, 2, PL_LORENTZ, 0, 0, 0, kRunsSmall) PL_RN(PL_CIC, 2, PL_DUST, 0, 0, 0, kRunsSmall)
     PL_RN(PL_TSC, 2, PL_LORENTZ, 2, 3, 1, kRunsSmall) PL_RN(PL_TSC, 2, PL_LORENTZ, 2, 3, 3, kRunsSmall)
     PL_RN(PL_TSC, 2, PL_DUST, 2, 3, 2, kRunsSmall)
-    PL_R(PL_TSC, 3, PL_LORENTZ, 1, 1, 3) PL_R(PL_TSC, 3, PL_LORENTZ, 2, 1, 3) PL_R(PL_TSC, 3, PL_LORENTZ, 1, 2, 3)
-    PL_R(PL_TSC, 3, PL_LORENTZ, 2, 2, 3)
-#undef PL_RF
+    PL_R(PL_TSC, 3, PL_DUST, 2, 1, 2) PL_R(PL_TSC, 3, PL_DUST, 2, 2, 2)
+    PL_R(PL_TSC, 3, PL_LORENTZ, 2, 2, 1) PL_R(PL_TSC, 3, PL_LORENTZ, 2, 2, 3)
+    if constexpr (PREC == PL_F32_OFFSET) {
+        PL_R(PL_TSC, 3, PL_LORENTZ, 2, 1, 1) PL_R(PL_TSC, 3, PL_LORENTZ, 2, 1, 3)
+    } else {
+        PL_R(PL_TSC, 3, PL_LORENTZ, 1, 1, 1)
+    }
 #undef PL_RG
 #undef PL_R
 #undef PL_RN
     return nullptr;
 }
 
+// (float64 on 8^3: with charged items one cell, dust and tracers alone two)
 template <int PREC>
-StepKernel pick_runs_mix(int shape, int dim, int hf, int ts, int chl, int chd)
+static RunsKernel pick_runs_mix(int shape, int dim, int hf, int ts, int chl, int chd)
 {
 #define PL_M(S, D, HF_, TS_, CL, CD) \
     if (shape == S && dim == D && hf == HF_ && ts == TS_ && chl == CL && chd == CD) \
         return k_runs_mix<PREC, S, D, HF_, TS_, CL, CD>;
     PL_M(PL_TSC, 3, 0, 0, 0, 0) PL_M(PL_TSC, 2, 0, 0, 0, 0) PL_M(PL_CIC, 3, 0, 0, 0, 0) PL_M(PL_CIC, 2, 0, 0, 0, 0)
-    PL_M(PL_TSC, 3, 1, 1, 1, 2) PL_M(PL_TSC, 3, 2, 1, 1, 2) PL_M(PL_TSC, 3, 1, 2, 1, 2) PL_M(PL_TSC, 3, 2, 2, 1, 2)
-    PL_M(PL_TSC, 3, 1, 1, 3, 2) PL_M(PL_TSC, 3, 2, 1, 3, 2) PL_M(PL_TSC, 3, 1, 2, 3, 2) PL_M(PL_TSC, 3, 2, 2, 3, 2)
+    PL_M(PL_TSC, 3, 2, 1, 1, 2) PL_M(PL_TSC, 3, 2, 2, 1, 2) PL_M(PL_TSC, 3, 2, 2, 3, 2)
+    if constexpr (PREC == PL_F32_OFFSET) {
+        PL_M(PL_TSC, 3, 2, 1, 3, 2)
+    } else {
+        PL_M(PL_TSC, 3, 1, 1, 1, 2)
+    }
 #undef PL_M
     return nullptr;
 }
@@ -1679,23 +1692,26 @@ hipError_t launch_runs_impl(Ctx *c, const ItemDesc *table, const ItemDesc *host,
     if (!runs_plan_impl<PREC>(c, host, nitems, pl)) return hipErrorInvalidConfiguration;
     if (pl.hf == 2) sf |= SF_FHALO2;
     if (pl.narrow) sf |= SF_NARROW;
-    StepKernel k;
+    RunsKernel k = nullptr;
     int chs = 0;
-    if (pl.mixed) {
+    auto pick = [&]() {
         // compile-time halo in the fixed-shape kernels, from the flags otherwise
-        k = pick_runs_mix<PREC>(c->d.shape, c->d.ndim, pl.ts ? pl.hf : 0, pl.ts, pl.chl, pl.chd);
-        chs = pl.chl;
-    } else {
-        const int kind = host[0].kind;
-        chs = pl.ts ? (kind == PL_LORENTZ ? pl.chl : pl.chd) : 0;
-        k = pick_runs<PREC>(c->d.shape, c->d.ndim, kind, pl.ts ? pl.hf : 0, pl.ts, chs, pl.nt);
+        const int kind = host[0].kind, hf = pl.ts ? pl.hf : 0;
+        chs = pl.mixed || kind == PL_LORENTZ ? pl.chl : pl.chd;
+        k = pl.mixed ? pick_runs_mix<PREC>(c->d.shape, c->d.ndim, hf, pl.ts, pl.chl, pl.chd)
+                     : pick_runs<PREC>(c->d.shape, c->d.ndim, kind, hf, pl.ts, chs, pl.nt);
+    };
+    pick();
+    if (!k) {
+        pl.ts = pl.chl = pl.chd = 0;
+        pick();
     }
     if (!k) return hipErrorInvalidConfiguration;
     const int rb = pl.nt;
     // every item has kRunsSplit units beyond its tiles for the pieces of crowded tiles
     const int units = total_units + nitems * kRunsSplit;
-    const int grid = std::min(units, resident_blocks(c, k, rb, pl.lds));
-    hipLaunchKernelGGL(k, dim3(grid), dim3(rb), pl.lds, c->stream, table, nitems, units, counter, c->errflags, sf,
+    const int grid = std::min(units, resident_blocks(c, (StepKernel)k, rb, pl.lds));
+    hipLaunchKernelGGL(k, dim3(grid), dim3(rb), pl.lds, c->stream, table, nitems, counter, c->errflags, sf,
                        (int)pl.lds);
     c->stats[0]++;
     c->stats[4]++;

@@ -79,7 +79,7 @@ int divisor_at_most(int n, int want)
     return 1;
 }
 
-void read_tune_cache(const char *path, int &block, int tile[3], int &runs, int &runs_block, int &one_launch)
+void read_tune_cache(const char *path, int &block, int tile[3], int &runs, int &one_launch)
 {
     if (!path) return;
     FILE *f = fopen(path, "r");
@@ -96,8 +96,8 @@ void read_tune_cache(const char *path, int &block, int tile[3], int &runs, int &
             int v;
             if (fscanf(f, "%d", &v) == 1) one_launch = v != 0;
         } else if (!strcmp(key, "runs_block")) {
-            int v;
-            if (fscanf(f, "%d", &v) == 1 && v == 512) runs_block = v;
+            int v;                       // read by the Python side; the run kernel's block is its own
+            if (fscanf(f, "%d", &v) != 1) continue;
         } else if (!strcmp(key, "tile")) {
             int a, b, c;
             if (fscanf(f, "%d %d %d", &a, &b, &c) == 3 && a > 0 && b > 0 && c > 0) {
@@ -494,15 +494,14 @@ pl_status pl_part_init(pl_ctx **out, const pl_init_desc *d)
     c->max_np = d->max_np;
     c->fp_stale.reserve(4 * (size_t)d->max_items + 16);
 
-    int tuned_block = 256, tuned_tile[3] = {8, 8, 8}, tuned_runs = 0, tuned_runs_block = 512, tuned_one = 1;
+    int tuned_block = 256, tuned_tile[3] = {8, 8, 8}, tuned_runs = 0, tuned_one = 1;
     if (d->prec == PL_F64 && d->algo == PL_ALGO_TILED) { tuned_tile[1] = 4; tuned_tile[2] = 4; }
     if (d->prec == PL_F64 && d->algo == PL_ALGO_RUNS) tuned_tile[2] = 4;
-    read_tune_cache(d->tune_cache, tuned_block, tuned_tile, tuned_runs, tuned_runs_block, tuned_one);
+    read_tune_cache(d->tune_cache, tuned_block, tuned_tile, tuned_runs, tuned_one);
     c->one_launch = tuned_one != 0;
     const bool runs_algo = d->algo == PL_ALGO_RUNS;
     c->block = (d->block && !runs_algo) ? d->block : tuned_block;
     c->runs = tuned_runs != 0;
-    c->runs_block = (d->block && runs_algo) ? d->block : tuned_runs_block;
     for (auto &b : c->boxes) {
         if (b.tile[0] == 0) {
             for (int a = 0; a < 3; ++a) b.tile[a] = divisor_at_most(b.n[a], tuned_tile[a]);

@@ -116,10 +116,9 @@ struct Ctx {
     hipStream_t stream = nullptr;
     int device = 0;
     int num_cu = 0;
-    int block = 256;
+    int block = 256;                 // threads of the one-particle-per-thread kernels
     int lds_max = 65536;
     bool runs = false;               // tiled: contiguous per-thread particle runs (tune cache "runs 1")
-    int runs_block = 512;            // block size of the run-based kernels (init block or tune cache "runs_block")
     bool one_launch = true;          // fused run-based steps over several kinds: one launch (tune cache
                                      // "one_launch 0": one launch per kind)
 

@@ -12,8 +12,8 @@ with charged, dust and tracer particles plus 16 boxes of 64^3) and times
 `steps` fused steps with the sort repeated at the candidate cadence (one
 graph sorts, zeroes and steps), so the sort's cost is amortised into the
 per-step time exactly as in the benchmark.  The winner is written as "key value" lines:
-pl_part_init reads block, runs_block and tile; the Python side reads algo,
-key and sort_every.  Without --out the file is the package's tune file for
+pl_part_init reads block, tile and one_launch; the Python side reads algo,
+key, runs_block and sort_every.  Without --out the file is the package's tune file for
 the precision (tune_mi355x_f32.txt / tune_mi355x_f64.txt).
 """
 
