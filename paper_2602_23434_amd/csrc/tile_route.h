@@ -10,7 +10,8 @@
 // cell (lanes of one cell), not rank by rank (lanes of distinct cells); and where
 // few tiles hold many particles, since a tile of several chunks takes several
 // CUs.  Times below are us per call on MI355X, one particle per thread and
-// grouped, 64^3 cells (512^2 in 2D) and TSC unless said, p particles per cell.
+// grouped, 64^3 cells (512^2 in 2D), TSC and the default tiles (8^3 in float32,
+// 8 x 4 x 4 in float64, 8 x 8 and 8 x 4 in 2D) unless said, p particles per cell.
 #pragma once
 
 #include <stdint.h>
@@ -29,6 +30,7 @@ struct TileLoad {
 inline bool local_pays(int mode, int ndim, int prec, int kind, int key, int num_cu, const TileLoad &w)
 {
     const int64_t pt = w.nt > 0 ? w.np / w.nt : 0;                 // particles per tile
+    const int64_t ct = w.nt > 0 ? w.cells / w.nt : 0;              // cells per tile
     const bool f64 = prec == PL_F64, charged = kind == PL_LORENTZ, d2 = ndim == 2;
     const bool by_cell = key == PL_KEY_TILE_CELL || key == PL_KEY_TILE_RUN;
     auto per_cell = [&](double p) { return (double)w.np >= p * (double)w.cells; };
@@ -38,18 +40,26 @@ inline bool local_pays(int mode, int ndim, int prec, int kind, int key, int num_
         //  a tile per CU or fewer: charged 32^3 float32 p 8 113 and 36, 32 x 32 float64
         //    p 256 96 and 30
         //  2D: float32 charged p 8 102 and 89, dust 105 and 85, on 1024^2 (16384
-        //    tiles) 306 and 325, 267 and 307; float64 charged 145 and 167
+        //    tiles) 306 and 325, 267 and 307; float64 charged 145 and 167; 16 x 8 tiles
+        //    97 and 72, 98 and 69, float64 dust 100 and 78; 16 x 16 float32 charged 58 and
+        //    67, float64 74 and 128, tracers p 4 25 and 52
         //  3D float32: charged p 8 187 and 86; dust p 2 44 and 49 (two blocks a CU,
         //    two particles a thread), p 4 62 and 55, 128^3 p 2 185 and 164
         //  3D float64: charged p 8 250 and 196, 128^3 p 2 642 and 655, p 4 1063
-        //    and 984; dust 136 and 129, 128^3 940 and 1133; tracers 177 and 139
+        //    and 984, 8 x 8 x 4 tiles p 8 263 and 196, but 8^3, whose 48-byte records
+        //    leave two blocks a CU a field halo of one cell only, 235 and 391, 16 x 8 x 4
+        //    243 and 338; dust 136 and 129, 128^3 940 and 1133, 8^3 tiles 125 and 181, on 48^3
+        //    (216 tiles) 97 and 65, 48^3 in 8 x 8 x 4 80 and 67; tracers 177 and 139, 8 x 8 x 4
+        //    p 1 40 and 56, p 2 61 and 67, p 4 100 and 92, 8^3 p 1 44 and 50, p 2 68 and 58
+        if (f64 && charged && ct >= 512) return false;
         if (w.nt <= num_cu) return true;
-        if (d2) return (!f64 || !charged) && w.cells >= 64 * w.nt && w.nt <= 4096;
+        if (d2) return (!f64 || !charged) && ct >= 64 && ct < 256 && w.nt <= 4096;
         if (!f64) return charged || pt >= 2048 || w.nt > 1024;
-        if (kind == PL_DUST) return w.nt <= 1024;
+        if (kind == PL_DUST) return w.nt < 2 * num_cu;
+        if (kind == PL_TRACER && ct >= 256) return pt >= 768;
         return w.nt <= 4096 || per_cell(3.5);
     }
-    const bool fused = mode == LM_FUSED, few = w.nt <= num_cu / 4;
+    const bool fused = mode == LM_FUSED, few = w.nt <= num_cu / 4, half = w.nt <= num_cu / 2;
     // Few tiles of many particles each: 32 x 32 float32 charged p 32 57 and 35,
     // 16^3 float64 dust p 16 by rank 71 and 50, float32 deposit p 2 by rank 39 and 28.
     if (few && pt >= (f64 || d2 ? 2048 : 1024)) return true;
@@ -81,24 +91,56 @@ inline bool local_pays(int mode, int ndim, int prec, int kind, int key, int num_
         // 32^3 p 4 75 and 43; 48^3 (216 tiles) p 16 128 and 111; dust deposit p 2 65 and 69,
         // p 4 105 and 82.  Tiles between a quarter of the CUs' number and it leave some
         // CUs two chunks of a tile and others one: 48^3 by rank p 4 76 and 86.
+        // 8 x 8 x 4 tiles: charged fused p 4 250 and 224, by rank 212 and 223; 32^3 (128
+        // tiles) p 4 84 and 53, by rank 78 and 52, dust 48 and 39, deposits 50 and 32, 33
+        // and 24, by rank p 8 62 and 58, 41 and 42; 16 x 8 x 4 dust deposit by rank p 4 82 and
+        // 90, p 8 123 and 114.
         const bool between = !few && w.nt <= num_cu;
+        if (half && pt >= 1024) return true;
         if (charged && fused) return pt >= 1280 || few;
         if (charged) return pt >= (between ? 2560 : key == PL_KEY_TILE_RANK ? 1280 : 1024);
         if (fused) return between && pt >= 4096;
-        return pt >= (between ? 2560 : 2048);
+        return pt >= (between || key == PL_KEY_TILE_RANK ? 2560 : 2048);
     }
-    // Float64: tiles of 8 x 4 x 4 and blocks of 256 threads up to 2048 particles a
-    // tile.  Charged fused p 2 176 and 178, p 4 191 and 181, p 8 328 and 250, p 16 812
+    // Float64.  Blocks of 256 threads up to 2048 particles a tile, one of 512 per CU
+    // beyond, which pays on tiles of 256 cells or more.  8 x 4 x 4 tiles:
+    // charged fused p 2 176 and 178, p 4 191 and 181, p 8 328 and 250, p 16 812
     // and 804; by rank p 4 162 and 176, p 8 270 and 243, p 16 740 and 871; 32^3 (256
     // tiles) p 8 98 and 92, p 16 167 and 172; 24 x 40 x 20 (150 tiles) p 2 45 and 42.
     // Deposit p 4 158 and 128, p 8 244 and 156, p 16 557 and 530; by rank p 8 241 and
-    // 218.  Dust fused p 8 276 and 286; deposit p 8 184 and 147, by rank 158 and 153.
-    const bool small = pt < 2048 && w.nt >= 512;
-    const bool fill = w.nt < num_cu * 3 / 4;
+    // 218, p 12 333 and 333.  Dust fused p 8 276 and 286; deposit p 8 184 and 147, by rank
+    // 158 and 153.
+    // 8 x 8 x 4: charged fused p 4 290 and 250, p 8 524 and 403, p 16 973 and 973, by
+    // rank p 4 241 and 246, p 8 406 and 366, p 12 596 and 501; deposit p 8 313 and 227, p
+    // 16 580 and 592, by rank p 8 256 and 208, p 16 476 and 517, 64 x 64 x 32 (512 tiles) p 4
+    // 77 and 88; dust fused p 8 278 and 312, deposit p 4 110 and 120, p 8 184 and 156, by
+    // rank 140 and 146, 32^3 (128 tiles) fused p 8 87 and 78, deposit p 4 32 and 38, p 8 53
+    // and 47, by rank 40 and 46, p 16 70 and 61; 48^3 (432 tiles) charged fused p 4 152 and
+    // 127, deposit 88 and 79.
+    // 8^3: charged fused p 8 521 and 417, by rank 450 and 375, 48^3 (216 tiles) p 2 103
+    // and 107, p 8 286 and 215; deposit p 8 301 and 239, p 16 565 and 642, by rank 226 and
+    // 193, 64 x 64 x 32 (256 tiles) by rank 126 and 136; dust deposit p 8 176 and 148.
+    // 4^3: charged fused p 8 502 and 523, p 16 950 and 896, by rank 790 and 868; deposit p
+    // 8 364 and 289, by rank 253 and 288; dust 219 and 231.
+    const bool fill = w.nt < num_cu * 3 / 4, many = w.nt >= num_cu * 3 / 2;
+    const bool big = pt >= 2048;
     const bool rank = key == PL_KEY_TILE_RANK;
-    if (!charged) return !fused && !rank && pt >= 1024 && (small || fill);
-    if (rank) return pt >= 1024 && (small || (fused && fill));
-    return fill || (small && pt >= 512);
+    const bool thin = !per_cell(14.0);
+    if (!charged) {
+        if (half && pt >= (fused || !rank ? 2048 : 4096)) return true;
+        if (fused || rank) return false;
+        return (many || (fill && big)) && ct >= 128 && per_cell(7.0) && thin && pt >= 1024;
+    }
+    if (fused) {
+        if (big) return ct >= 256 || fill;
+        if (rank) return pt >= 1024 && (fill || (many && ct >= 128));
+        return fill || (many && pt >= (ct >= 128 ? 512 : 1024));
+    }
+    if (rank) {
+        if (half && pt >= 4096) return true;
+        return ct >= 128 && thin && (big ? ct >= 256 && w.nt >= 2 * num_cu : pt >= 1024 && w.nt >= 4 * num_cu);
+    }
+    return fill || (big ? ct >= 256 && thin : many && pt >= 512);
 }
 
 }  // namespace pl

@@ -60,6 +60,33 @@ CASES = [
     (PUSH, F32, CHARGED, TILE, (64, 64, 64), 512, 8, 187, 86),
     (PUSH, F64, TRACER, TILE, (64, 64, 64), 2048, 8, 177, 139),
     (PUSH, F32, DUST, TILE, (64, 64, 64), 512, 2, 44, 49),
+    # tiles other than the default ones
+    (FUSED, F64, CHARGED, TILE, (64, 64, 64), 1024, 8, 524, 403),      # 8 x 8 x 4
+    (FUSED, F64, CHARGED, RANK, (64, 64, 64), 1024, 12, 596, 501),
+    (FUSED, F64, CHARGED, RANK, (64, 64, 64), 512, 8, 450, 375),       # 8^3
+    (FUSED, F64, CHARGED, TILE, (48, 48, 48), 216, 8, 286, 215),
+    (FUSED, F64, CHARGED, TILE, (48, 48, 48), 216, 2, 103, 107),
+    (FUSED, F64, CHARGED, RANK, (64, 64, 64), 4096, 16, 790, 868),     # 4^3
+    (FUSED, F64, DUST, TILE, (32, 32, 32), 128, 8, 87, 78),
+    (FUSED, F64, DUST, TILE, (64, 64, 64), 1024, 8, 278, 312),
+    (FUSED, F32, CHARGED, TILE, (32, 32, 32), 128, 4, 84, 53),
+    (DEP, F64, CHARGED, RANK, (64, 64, 64), 1024, 8, 256, 208),
+    (DEP, F64, CHARGED, RANK, (64, 64, 64), 1024, 16, 476, 517),
+    (DEP, F64, CHARGED, RANK, (64, 64, 32), 512, 4, 77, 88),
+    (DEP, F64, CHARGED, TILE, (64, 64, 64), 512, 16, 565, 642),
+    (DEP, F64, DUST, TILE, (64, 64, 64), 512, 8, 176, 148),
+    (DEP, F64, DUST, TILE, (32, 32, 32), 128, 4, 32, 38),
+    (DEP, F32, DUST, RANK, (64, 64, 64), 512, 4, 82, 90),              # 16 x 8 x 4
+    (PUSH, F64, CHARGED, TILE, (64, 64, 64), 512, 8, 235, 391),
+    (PUSH, F64, CHARGED, RANK, (48, 48, 48), 216, 8, 177, 192),
+    (PUSH, F64, CHARGED, TILE, (64, 64, 64), 1024, 8, 263, 196),
+    (PUSH, F64, DUST, TILE, (64, 64, 64), 512, 8, 125, 181),
+    (PUSH, F64, DUST, TILE, (48, 48, 48), 216, 8, 97, 65),
+    (PUSH, F64, TRACER, TILE, (64, 64, 64), 1024, 1, 40, 56),
+    (PUSH, F64, TRACER, TILE, (64, 64, 64), 512, 2, 68, 58),
+    (PUSH, F32, CHARGED, TILE, (512, 512, 1), 1024, 8, 58, 67),        # 16 x 16
+    (PUSH, F32, DUST, TILE, (512, 512, 1), 2048, 8, 98, 69),           # 16 x 8
+    (PUSH, F32, TRACER, TILE, (512, 512, 1), 1024, 4, 25, 52),
 ]
 
 
