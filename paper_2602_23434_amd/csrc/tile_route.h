@@ -9,7 +9,11 @@
 // in 3D, not 9 points in 2D or the 4 channels of dust; particles stored cell by
 // cell (lanes of one cell), not rank by rank (lanes of distinct cells); and where
 // few tiles hold many particles, since a tile of several chunks takes several
-// CUs.  Times below are us per call on MI355X, one particle per thread and
+// CUs.  Where a launch has more units than the chip holds blocks, its blocks
+// claim them from one counter, about 20 ns a claim: 2D float32 pushes of 600
+// particles a tile take 11 us on 192 tiles, 36 on 500 and 48 on 1024, which one
+// particle per thread, with more and smaller blocks resident, does in 19, 20 and 29.
+// So the lines lie at the tiles that are resident, too.  Times below are us per call on MI355X, one particle per thread and
 // grouped, 64^3 cells (512^2 in 2D), TSC and the default tiles (8^3 in float32,
 // 8 x 4 x 4 in float64, 8 x 8 and 8 x 4 in 2D) unless said, p particles per cell.
 #pragma once
@@ -51,12 +55,18 @@ inline bool local_pays(int mode, int ndim, int prec, int kind, int key, int num_
         //    243 and 338; dust 136 and 129, 128^3 940 and 1133, 8^3 tiles 125 and 181, on 48^3
         //    (216 tiles) 97 and 65, 48^3 in 8 x 8 x 4 80 and 67; tracers 177 and 139, 8 x 8 x 4
         //    p 1 40 and 56, p 2 61 and 67, p 4 100 and 92, 8^3 p 1 44 and 50, p 2 68 and 58
+        //  resident or not (two blocks of 512 per CU): float64 charged 480 tiles of 280
+        //    particles 38 and 26, of 400 44 and 49; dust 23 and 19, of 520 29 and 42, 800 tiles
+        //    66 and 56; float32 dust 384 tiles of 900 32 and 22, 512 38 and 48, of 2000 66 and
+        //    58; 2D dust 1024 tiles of 600 20 and 48, float64 2048 tiles 78 and 59
+        const bool resident = w.nt <= num_cu || w.nt + w.np / 4096 <= 2 * num_cu;
         if (f64 && charged && ct >= 512) return false;
-        if (w.nt <= num_cu) return true;
-        if (d2) return (!f64 || !charged) && ct >= 64 && ct < 256 && w.nt <= 4096;
-        if (!f64) return charged || pt >= 2048 || w.nt > 1024;
-        if (kind == PL_DUST) return w.nt < 2 * num_cu;
+        if (resident) return true;
+        if (d2) return w.nt >= 7 * num_cu && w.nt <= 16 * num_cu && ct < (f64 && charged ? 64 : 256);
+        if (!f64) return charged || pt >= 1800 || w.nt > 1024;
+        if (kind == PL_DUST) return ct < 256 && 2 * w.nt >= 5 * num_cu && w.nt <= 1600;
         if (kind == PL_TRACER && ct >= 256) return pt >= 768;
+        if (2 * w.nt < 5 * num_cu && pt < 512) return false;
         return w.nt <= 4096 || per_cell(3.5);
     }
     const bool fused = mode == LM_FUSED, few = w.nt <= num_cu / 4, half = w.nt <= num_cu / 2;
@@ -95,12 +105,19 @@ inline bool local_pays(int mode, int ndim, int prec, int kind, int key, int num_
         // tiles) p 4 84 and 53, by rank 78 and 52, dust 48 and 39, deposits 50 and 32, 33
         // and 24, by rank p 8 62 and 58, 41 and 42; 16 x 8 x 4 dust deposit by rank p 4 82 and
         // 90, p 8 123 and 114.
+        // Chunks are of 1024 particles or more, so between a quarter of the CUs' number of
+        // tiles and it a tile of a few more becomes two: 200 tiles of 900 charged fused 81 and
+        // 74, of 1200 99 and 114, of 2000 143 and 129, deposit 55 and 50, 66 and 80, 90 and 85.
+        // More: 512 tiles of 900 charged fused 146 and 140, by rank 136 and 139, deposit 106
+        // and 98, by rank of 1200 105 and 102, dust of 1200 75 and 72; 96 tiles of 700 charged
+        // 63 and 57, deposit 41 and 35.
         const bool between = !few && w.nt <= num_cu;
-        if (half && pt >= 1024) return true;
-        if (charged && fused) return pt >= 1280 || few;
-        if (charged) return pt >= (between ? 2560 : key == PL_KEY_TILE_RANK ? 1280 : 1024);
+        const bool rank = key == PL_KEY_TILE_RANK;
+        if (half && pt >= (charged ? 700 : 1024)) return true;
+        if (charged && fused) return between ? pt >= 1600 || (pt >= 800 && pt <= 1000) : pt >= 1280 || few;
+        if (charged) return between ? pt >= 2560 || (!rank && pt >= 850 && pt <= 1000) : pt >= (rank ? 1150 : 850);
         if (fused) return between && pt >= 4096;
-        return pt >= (between || key == PL_KEY_TILE_RANK ? 2560 : 2048);
+        return pt >= (between || rank ? 2560 : 1150);
     }
     // Float64.  Blocks of 256 threads up to 2048 particles a tile, one of 512 per CU
     // beyond, which pays on tiles of 256 cells or more.  8 x 4 x 4 tiles:
@@ -122,25 +139,36 @@ inline bool local_pays(int mode, int ndim, int prec, int kind, int key, int num_
     // 193, 64 x 64 x 32 (256 tiles) by rank 126 and 136; dust deposit p 8 176 and 148.
     // 4^3: charged fused p 8 502 and 523, p 16 950 and 896, by rank 790 and 868; deposit p
     // 8 364 and 289, by rank 253 and 288; dust 219 and 231.
-    const bool fill = w.nt < num_cu * 3 / 4, many = w.nt >= num_cu * 3 / 2;
+    // Few of the smaller tiles, 8 x 4 x 4: 320 of 280 charged fused 57 and 52, by rank 50 and
+    // 51, of 1100 149 and 105, 117 and 103, deposit 33 and 31, 97 and 57, by rank of 700 48 and
+    // 41, dust deposit of 520 33 and 28, by rank 27 and 28; 480 of 280 charged fused 65 and 68,
+    // of 700 109 and 93, by rank 98 and 92, deposit of 400 45 and 53, of 700 66 and 62, by rank
+    // 52 and 64; 800 of 280 109 and 102, of 700 185 and 148, by rank 152 and 145, deposit of 280
+    // 73 and 70, by rank of 700 105 and 93.
+    const bool flat = ct < 256;
+    const bool fill = 4 * w.nt < (flat ? 6 : 3) * num_cu, many = 2 * w.nt >= 3 * num_cu, lots = 2 * w.nt >= 5 * num_cu;
     const bool big = pt >= 2048;
     const bool rank = key == PL_KEY_TILE_RANK;
     const bool thin = !per_cell(14.0);
     if (!charged) {
         if (half && pt >= (fused || !rank ? 2048 : 4096)) return true;
         if (fused || rank) return false;
+        if (flat && fill && 4 * w.nt >= 3 * num_cu) return pt >= 500;
         return (many || (fill && big)) && ct >= 128 && per_cell(7.0) && thin && pt >= 1024;
     }
     if (fused) {
-        if (big) return ct >= 256 || fill;
-        if (rank) return pt >= 1024 && (fill || (many && ct >= 128));
-        return fill || (many && pt >= (ct >= 128 ? 512 : 1024));
+        if (big) return !flat || (fill && !rank);
+        if (fill) return flat || !rank || pt >= 1024;
+        if (rank) return many && ct >= 128 && pt >= (flat ? 650 : 1024);
+        return many && pt >= (ct < 128 ? 1024 : lots ? 272 : 512);
     }
     if (rank) {
         if (half && pt >= 4096) return true;
-        return ct >= 128 && thin && (big ? ct >= 256 && w.nt >= 2 * num_cu : pt >= 1024 && w.nt >= 4 * num_cu);
+        if (big) return !flat && thin && w.nt >= 2 * num_cu;
+        if (flat && fill) return 4 * w.nt >= 3 * num_cu && pt >= 600;
+        return ct >= 128 && thin && (flat ? lots && pt >= 650 : pt >= 1024 && w.nt >= 4 * num_cu);
     }
-    return fill || (big ? ct >= 256 && thin : many && pt >= 512);
+    return fill || (big ? !flat && thin : many && pt >= (ct < 128 ? 512 : lots ? 272 : 650));
 }
 
 }  // namespace pl

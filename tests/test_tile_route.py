@@ -89,9 +89,45 @@ CASES = [
     (PUSH, F32, TRACER, TILE, (512, 512, 1), 1024, 4, 25, 52),
 ]
 
+# The same for calls of few tiles, by particles per tile.
+FEW = [
+    # mode, ndim, prec, kind, key, cells per tile, tiles, particles per tile, step us, grouped us
+    (FUSED, 3, F64, CHARGED, RANK, 128, 320, 900, 103, 87),
+    (FUSED, 3, F64, CHARGED, TILE, 128, 320, 1100, 149, 105),
+    (FUSED, 3, F64, CHARGED, TILE, 128, 480, 280, 65, 68),
+    (FUSED, 3, F64, CHARGED, RANK, 128, 480, 700, 98, 92),
+    (FUSED, 3, F64, CHARGED, RANK, 128, 800, 520, 123, 132),
+    (DEP, 3, F64, CHARGED, TILE, 128, 320, 1100, 97, 57),
+    (DEP, 3, F64, CHARGED, RANK, 128, 480, 700, 52, 64),
+    (DEP, 3, F64, CHARGED, RANK, 128, 800, 700, 105, 93),
+    (DEP, 3, F64, DUST, TILE, 128, 320, 520, 33, 28),
+    (DEP, 3, F64, DUST, TILE, 128, 480, 520, 34, 45),
+    (FUSED, 3, F32, CHARGED, TILE, 512, 200, 900, 81, 74),
+    (FUSED, 3, F32, CHARGED, TILE, 512, 200, 1200, 99, 114),
+    (DEP, 3, F32, CHARGED, TILE, 512, 200, 1200, 66, 80),
+    (DEP, 3, F32, DUST, TILE, 512, 512, 1200, 75, 72),
+    (DEP, 3, F32, CHARGED, TILE, 512, 96, 700, 41, 35),
+    (PUSH, 2, F32, CHARGED, TILE, 64, 192, 600, 19, 13),
+    (PUSH, 2, F32, CHARGED, TILE, 64, 500, 600, 21, 36),
+    (PUSH, 2, F32, DUST, TILE, 64, 1024, 600, 20, 48),
+    (PUSH, 2, F64, DUST, TILE, 32, 2048, 520, 78, 59),
+    (PUSH, 3, F64, DUST, TILE, 128, 480, 280, 24, 20),
+    (PUSH, 3, F64, DUST, TILE, 128, 480, 520, 30, 43),
+    (PUSH, 3, F64, DUST, TILE, 128, 800, 520, 67, 58),
+    (PUSH, 3, F64, CHARGED, TILE, 128, 480, 400, 45, 49),
+    (PUSH, 3, F32, DUST, TILE, 512, 384, 900, 35, 22),
+    (PUSH, 3, F32, DUST, TILE, 512, 512, 900, 39, 49),
+]
+
 
 @pytest.mark.parametrize("mode,prec,kind,key,box,tiles,ppc,step,grouped", CASES)
 def test_the_faster_kernel(rule, mode, prec, kind, key, box, tiles, ppc, step, grouped):
     cells = box[0] * box[1] * box[2]
     got = rule.pays(mode, 2 if box[2] == 1 else 3, prec, kind, key, cells * ppc + 7, tiles, cells)
+    assert bool(got) == (grouped < step)
+
+
+@pytest.mark.parametrize("mode,ndim,prec,kind,key,ct,tiles,pt,step,grouped", FEW)
+def test_few_tiles(rule, mode, ndim, prec, kind, key, ct, tiles, pt, step, grouped):
+    got = rule.pays(mode, ndim, prec, kind, key, pt * tiles + 7, tiles, ct * tiles)
     assert bool(got) == (grouped < step)
