@@ -52,7 +52,7 @@ def kernel_name(cfg, B):
         ts = {(8, 8, 8): 1, (8, 8, 4): 2}.get(tile, 0)
         return f"pl::k_runs<1, 2, 3, 0, {2 if ts else 0}, {ts}, {1 if ts else 0}, 512>"
     ts = {(8, 8, 8): 1, (8, 8, 4): 2}.get(tile, 0)
-    return f"pl::k_step<1, 2, 3, true, 0, {ts}, {1 if ts else 0}>"
+    return f"pl::k_local<1, 2, 3, 0, 0, {ts}, {1 if ts else 0}, 512>"
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_runs_f32_turbulent128_traffic.json")
 INSTR_FILE = os.path.join(ROOT, "profiles", "k_runs_f32_turbulent128_instructions.json")
@@ -304,7 +304,7 @@ def spectra_leg(torch, B, driver, inputs, steps=10):
              "unit": "particle-spectra/s",
              "roofline": {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                           "frac": ach / HBM_PEAK_GBS, "alg_bytes_per_launch": alg,
-                          "kernel": "pl::k_spectra<1, 2, 3, 1>"},
+                          "kernel": "pl::k_spectra<1, 2, 3, 1, true>"},
              "paper_context": "Particles_Spectra: 190 ms per step for 16.4 M particles on one A100 (Table 1)"}
         log(f"[bench] spectra: {ms:.3f} ms/step, {ach:.0f} GB/s algorithmic")
         return r
